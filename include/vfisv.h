@@ -105,7 +105,10 @@ typedef struct {
   uint32_t free_mask;  /* bit p set: parameter p free (0x3FF)               */
   int grid_waves;      /* persistent grid size in waves; 0 = auto: the      */
                        /* vfisv_autotune choice for the instrument's layout */
-                       /* if there is one, else CUs x occupancy             */
+                       /* if there is one, else CUs x occupancy.  With every */
+                       /* scheduling field automatic, launches of few pixels */
+                       /* take a pixel per wave pass instead of per lane     */
+                       /* (the same results)                                */
   int chunk_log2;      /* pixel queue block = 2^chunk_log2 consecutive      */
                        /* pixels, 0..20, or -1 = auto (default: the tuned   */
                        /* value, else 8).  Scheduling only: the per-pixel   */

@@ -145,6 +145,10 @@ static int lm_grid(vfisv_ctx* ctx, int64_t n, int bpc, const vfisv_options& o, i
   return grid_for(n, cap);
 }
 
+FitUse fit_use(const vfisv_options& o, FitUse use) {
+  return o.grid_waves == 0 && o.chunk_log2 < 0 && o.deriv_split < 0 ? use : FIT_SCHEDULED;
+}
+
 // The context's buffer for interleaved observations, grown to at least
 // `bytes` (hipFree waits for the work that may still read the old one).
 static int grow_obs4(vfisv_ctx* ctx, size_t bytes) {
@@ -161,11 +165,33 @@ static int grow_obs4(vfisv_ctx* ctx, size_t bytes) {
   return VFISV_OK;
 }
 
+// The pixels up to which the group inverter takes a launch, by layout and
+// use (FitUse), where it is faster than lm_kernel on 65,536 lanes.  Measured
+// (group / lm_kernel): plain HMI fits 4,096 pixels 0.65 / 3.95 ms, 65,536
+// 4.0 / 4.7, 131,072 7.6 / 8.0, 196,608 11.1 / 11.3, 262,144 14.5 / 14.4;
+// fine spectra 1,000 pixels 1.7 / 29, 100,003 38 / 64, 262,144 96 / 104,
+// 400,000 147 / 144.  From the network's start more trials are accepted and
+// need their Jacobian, which lm_kernel computes ahead: short fits of HMI
+// pixels 20,011 0.61 / 1.18 ms, 100,000 2.15 / 2.40, 131,072 2.73 / 2.69.
+// Re-fits, which lm_kernel runs in lane pairs up to 36,044 pixels: 1,139
+// pixels 0.61 / 2.36 ms, 11,673 1.19 / 2.51, 51,330 4.0 / 3.7.
+constexpr int64_t GROUP_MAX[2][4] = {{0, 196608, 131072, 32768}, {0, 262144, 131072, 131072}};
+
+// The largest batch that the group inverter takes under these options, 0 if
+// none: it has Weideman's series and the fit with convergence exits only.
+static int64_t group_limit(const vfisv_ctx* ctx, const vfisv_instrument* inst,
+                           const vfisv_options& o, FitUse use) {
+  if (o.voigt != 0 || o.fixed_iters != 0 || o.lanes_per_pixel != 1 || !inst->d_group) return 0;
+  // (a layout with a tuned schedule keeps it where a schedule matters)
+  const int64_t most = GROUP_MAX[inst->kind][use];
+  return ctx->tuned[inst->kind].valid ? std::min<int64_t>(most, 16384) : most;
+}
+
 int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
                const unsigned long long* n_dev, const int32_t* idx, const float* stokes,
                const float* W, int W_pp, const float* init, const vfisv_options& o,
                double inv_dof, float* params, double* chi2, int32_t* iters, int32_t* status,
-               hipStream_t s, bool reset_all, int lpp_max, bool may_alloc) {
+               hipStream_t s, bool reset_all, int lpp_max, bool may_alloc, FitUse use) {
   LMArgs a;
   fill_lm_args(ctx, inst, n, n_dev, idx, stokes, W, W_pp, init, o, inv_dof, params, chi2, iters,
                status, a);
@@ -185,6 +211,24 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
   // when all pixels fit in pairs, 0.83x with 6.6% of them waiting (34,936
   // pixels on 65,536 lanes) and 1.4x with 29% waiting (42,324 pixels).
   a.pair_max = a.lane_cap / 2 + a.lane_cap / 20;
+  // Few pixels: a wave per pixel pass (the same results).  A count that only
+  // the device knows is compared there: the group kernel exits at once when
+  // it is above the limit, and tells lm_kernel what is left to do.
+  const int64_t group_max = group_limit(ctx, inst, o, use);
+  hipError_t e = launch_reset(ctx->d_work, reset_all, s);
+  if (e != hipSuccess) return hip_fail(ctx, e, "invert: counter reset");
+  if (group_max > 0 && (n_dev || n <= group_max)) {
+    GroupArgs g;
+    g.A = a;
+    g.T = inst->group;
+    g.n_max = group_max;
+    const int64_t most = n < group_max ? n : group_max;
+    const int64_t cap = (int64_t)ctx->num_cus * ctx->group_blocks_per_cu[inst->kind];
+    e = launch_lm_group(g, inst->kind, (int)(most < cap ? most : cap), s);
+    if (e != hipSuccess) return hip_fail(ctx, e, "invert launch");
+    if (n <= group_max) return VFISV_OK;
+    a.n_dev = ctx->d_work + GROUP_LEFT_SLOT;
+  }
   if (inst->kind == KIND_BAND && !idx && !n_dev && n > 0 && may_alloc) {
     // a whole banded batch: the pass reads an interleaved copy
     const int no = inst->C.n_obs;
@@ -195,8 +239,6 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
     if (e0 != hipSuccess) return hip_fail(ctx, e0, "invert: interleave");
     a.stokes4 = o4;
   }
-  hipError_t e = launch_reset(ctx->d_work, reset_all, s);
-  if (e != hipSuccess) return hip_fail(ctx, e, "invert: counter reset");
   e = launch_lm(a, inst->kind, o.voigt, grid, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "invert launch");
   return VFISV_OK;
@@ -305,6 +347,11 @@ int vfisv_create(vfisv_ctx** out, int device) {
   e = band_blocks_per_cu(&bpc);
   if (e != hipSuccess || bpc < 1) bpc = 1;
   c->band_blocks_per_cu = bpc;
+  for (int kind = 0; kind < 2; ++kind) {
+    bpc = 0;
+    e = lm_group_blocks_per_cu(kind, &bpc);
+    if (e == hipSuccess && bpc > 0) c->group_blocks_per_cu[kind] = bpc;
+  }
   // the largest persistent grid: 8 waves per CU
   c->max_lanes = (int64_t)c->num_cus * 8 * 64;
   e = hipMalloc(&c->d_work, sizeof(unsigned long long) * (WORK_SLOTS + HIST_MAX));
@@ -556,6 +603,42 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
   inst->info.lm_register_rows =
       inst->kind == KIND_BAND ? BAND_R : (inst->C.sw_k >= 0 ? 5 : NOBS_HMI);
 
+  // Tables of the group inverter: the points in whole chunks; the taps by row
+  // (dense: over all points; banded: over the row's 16 points) and, banded,
+  // as matrix operands: lane l of chunk ch feeds row 16 ch - 3 + l % 16 with
+  // point 4 i + l / 16 of the chunk's window in step i.  Dense instruments of
+  // more than one chunk are left to lm_kernel.
+  std::vector<float> gdl, gtaps, gop;
+  {
+    const int n_pts = inst->kind == KIND_BAND ? BAND_S * (int)blocks.size() : (int)pts.size();
+    const int n_chunk = (n_pts + GROUP_PTS - 1) / GROUP_PTS;
+    inst->group.n_chunk = n_chunk;
+    gdl.assign((size_t)n_chunk * GROUP_PTS, 0.f);
+    if (inst->kind == KIND_BAND) {
+      constexpr int RT = BAND_S * BAND_R, RC = GROUP_PTS / BAND_S, OPS = GROUP_WIN + 1;
+      gtaps.assign((size_t)no * RT, 0.f);
+      for (int k = 0; k < n_pts; ++k) gdl[(size_t)k] = blocks[(size_t)(k / BAND_S)].dl[k % BAND_S];
+      for (int j = 0; j < no; ++j)
+        for (int i = 0; i < BAND_R; ++i)
+          for (int q = 0; q < BAND_S; ++q)
+            gtaps[(size_t)(j * RT + i * BAND_S + q)] = blocks[(size_t)(j + i)].w[q][BAND_R - 1 - i];
+      gop.assign((size_t)n_chunk * 64 * OPS, 0.f);
+      for (int ch = 0; ch < n_chunk; ++ch)
+        for (int l = 0; l < 64; ++l)
+          for (int i = 0; i < GROUP_WIN; ++i) {
+            const int r = l % 16, j = RC * ch - (BAND_R - 1) + r, t = 4 * (i - r) + l / 16;
+            if (j >= 0 && j < no && t >= 0 && t < RT)
+              gop[(size_t)((ch * 64 + l) * OPS + i)] = gtaps[(size_t)(j * RT + t)];
+          }
+    } else if (n_chunk == 1) {
+      gtaps.assign((size_t)no * GROUP_PTS, 0.f);
+      for (int k = 0; k < n_pts; ++k) {
+        gdl[(size_t)k] = pts[(size_t)k].dl;
+        for (int i = 0; i < no; ++i) gtaps[(size_t)(i * GROUP_PTS + k)] = pts[(size_t)k].w[i];
+      }
+    }
+  }
+
   hipError_t e = use_device(ctx);
   if (e != hipSuccess) {
     delete inst;
@@ -606,10 +689,23 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
       e = hipMemcpy(inst->d_row_sums, row_sum.data(), sizeof(float) * (size_t)no,
                     hipMemcpyHostToDevice);
   }
+  if (e == hipSuccess && (inst->kind == KIND_BAND || inst->group.n_chunk == 1)) {
+    std::vector<float> host(gdl);
+    host.insert(host.end(), gtaps.begin(), gtaps.end());
+    while (host.size() % 4 != 0) host.push_back(0.f);
+    const size_t o_op = host.size();
+    host.insert(host.end(), gop.begin(), gop.end());
+    e = hipMalloc(&inst->d_group, sizeof(float) * host.size());
+    if (e == hipSuccess)
+      e = hipMemcpy(inst->d_group, host.data(), sizeof(float) * host.size(), hipMemcpyHostToDevice);
+    inst->group.dl = inst->d_group;
+    inst->group.taps = inst->d_group + gdl.size();
+    inst->group.taps_a = inst->d_group + o_op;
+  }
   if (e != hipSuccess) {
+    if (inst->d_group) hipFree(inst->d_group);
     if (inst->d_pts) hipFree(inst->d_pts);
     if (inst->d_pts5) hipFree(inst->d_pts5);
-  if (inst->d_ptsv) hipFree(inst->d_ptsv);
     if (inst->d_ptsv) hipFree(inst->d_ptsv);
     if (inst->d_blocks) hipFree(inst->d_blocks);
     if (inst->d_row_sums) hipFree(inst->d_row_sums);
@@ -637,6 +733,7 @@ int vfisv_instrument_destroy(vfisv_instrument* inst) {
   if (inst->d_blocks) hipFree(inst->d_blocks);
   if (inst->d_row_sums) hipFree(inst->d_row_sums);
   if (inst->d_obs_x) hipFree(inst->d_obs_x);
+  if (inst->d_group) hipFree(inst->d_group);
   delete inst;
   return VFISV_OK;
 }
@@ -702,7 +799,8 @@ int vfisv_invert(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n, const 
   hipError_t e = use_device(ctx);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   return enqueue_lm(ctx, inst, n, nullptr, nullptr, stokes, W, W_per_pixel, init, o, inv_dof,
-                    params, chi2, iters, status, (hipStream_t)stream, true);
+                    params, chi2, iters, status, (hipStream_t)stream, true, 1, true,
+                    fit_use(o, FIT_PLAIN));
 }
 
 int vfisv_invert_batches(vfisv_ctx* ctx, const vfisv_batch* batches, int n_batches,

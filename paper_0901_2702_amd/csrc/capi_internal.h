@@ -8,6 +8,7 @@
 
 #include <rocprofiler-sdk-roctx/roctx.h>
 
+#include "group.h"
 #include "kernels.h"
 #include "vfisv.h"
 
@@ -28,6 +29,7 @@ struct vfisv_ctx {
   int num_cus = 0;
   int lm_blocks_per_cu = 1;
   int band_blocks_per_cu = 1;
+  int group_blocks_per_cu[2] = {1, 1};  // group inverter, per instrument layout (KIND_*)
   unsigned long long* d_work = nullptr;  // WORK_SLOTS counters
   int64_t max_lanes = 0;                 // lanes of the largest persistent grid
   float2* d_vtab = nullptr;              // Taylor table {H, F}, built on first use
@@ -70,6 +72,8 @@ struct vfisv_instrument {
   vfisv::Block* d_blocks = nullptr;    // KIND_BAND
   float* d_row_sums = nullptr;         // KIND_BAND
   float* d_obs_x = nullptr;            // [n_obs] observed wavelength of each sample
+  float* d_group = nullptr;            // tables of the group inverter
+  vfisv::GroupTables group;
   vfisv::Consts C;
   vfisv_instrument_info info;
 };
@@ -95,11 +99,18 @@ int ensure_vtab(vfisv_ctx* ctx);
 // the library allocate (the Taylor table before it exists).
 int check_options(vfisv_ctx* ctx, const vfisv_instrument* inst, const vfisv_options* opt,
                   vfisv_options* out, double* inv_dof, bool may_alloc = true);
+// What a fit is for, which decides with its size whether the group inverter
+// takes it: a launch whose schedule the caller chose (never), a plain fit,
+// the learned path's short fit and its re-fit.
+enum FitUse { FIT_SCHEDULED, FIT_PLAIN, FIT_SHORT, FIT_REFIT };
+// `use`, or FIT_SCHEDULED when the options fix the launch schedule.
+FitUse fit_use(const vfisv_options& o, FitUse use);
 // Resolve the device address of the allocation-free path's scratch array on
 // ctx's device (current on the calling thread); once per device.
 int noalloc_scratch_setup(vfisv_ctx* ctx);
 
-// Enqueue the persistent LM kernel.  With idx != NULL the pixels are
+// Enqueue the LM fit: the group inverter for few pixels, else the persistent
+// LM kernel (the same results).  With idx != NULL the pixels are
 // idx[0 .. count), count read from n_dev on the device (n bounds the grid);
 // reset_all clears every work counter, otherwise only the queue heads.
 // lpp_max = 2 lets dense pixels use a pair of lanes each when the resident
@@ -112,6 +123,7 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
                const unsigned long long* n_dev, const int32_t* idx, const float* stokes,
                const float* W, int W_pp, const float* init, const vfisv_options& o,
                double inv_dof, float* params, double* chi2, int32_t* iters, int32_t* status,
-               hipStream_t s, bool reset_all, int lpp_max = 1, bool may_alloc = true);
+               hipStream_t s, bool reset_all, int lpp_max = 1, bool may_alloc = true,
+               FitUse use = FIT_SCHEDULED);
 
 }  // namespace vfisv_capi

@@ -1,0 +1,891 @@
+// The group inverter: the Levenberg-Marquardt fit of kernels.hip with the
+// lanes of a wave on one pixel's synthesis points instead of on 64 pixels.
+//
+// lm_kernel keeps a pixel per lane, so a launch takes as long as one lane's
+// fit however few pixels it has: up to 51 passes of 59 (HMI) or 460 (fine
+// spectra) synthesis points one after the other.  Here a wave works on a few
+// pixels (slots).  Lane k owns slot k: it keeps the pixel's model, takes the
+// decisions and solves the damped system; the synthesis passes of the slots
+// follow one another with a point per lane, and the sums over the points are
+// formed in the order in which lm_kernel forms them: every row sum adds the
+// points in record order, chi^2 the rows in slot order, H and g the residuals
+// in the same order.  The row sums with derivatives run on the matrix cores:
+// v_mfma_f32_16x16x4_f32 adds its four products one after the other, each
+// with one float32 rounding, as a chain of fmaf does, so rows x quantities
+// over 4 points are one instruction and the same bits.  All products, sums
+// and decisions being those of lm_kernel, so are the results, bit for bit.
+//
+// Trials run without derivatives; only a start and an accepted model that
+// does not end its fit get their Jacobian (Fig. 6), with no wave-mates to
+// wait for.  The normal equations are equilibrated once per Jacobian and stay
+// in LDS for the rejected trials after it.
+//
+// Few pixels are bound by one fit's serial chain (points, row sums, chi^2,
+// Cholesky: 8 us per trial), many by VALU issue, at about 760 wave
+// instructions per trial of an HMI pixel (lm_kernel: 510, with lanes and
+// derivative passes that wait for each other).  Eight slots share the solve,
+// the decisions and the set-up of a turn, which one lane each would otherwise
+// run alone (two pixels per wave, 32 lanes each: 1,750 instructions per
+// trial, 131,072 pixels in 18.2 ms instead of 7.6).  Measured, default
+// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.40 ms, 4,096 3.95 -> 0.65,
+// 65,536 4.7 -> 4.0; 1,000 fine spectra 29.5 -> 1.66 ms, 100,003 63.7 -> 38.1.
+#include <hip/hip_runtime.h>
+
+#include "group.h"
+#include "me_device.h"
+
+namespace vfisv {
+
+namespace {
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+
+// Orders this wave's LDS accesses (a workgroup is one wave, whose LDS
+// operations complete in order: the compiler alone must not move them).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A value whose last operation is not contracted with what follows:
+// lm_kernel rounds here, at the end of a basic block.
+__device__ __forceinline__ double rounded(double x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+constexpr int NEQ = 64;               // chains of the normal equations
+constexpr int CSTR = GROUP_PTS + 4;   // a quantity's points in LDS
+constexpr int CN = NACC * CSTR;       // floats of a chunk's contributions
+constexpr int ASTR = 33;              // row sums of a row
+// dense: J [10], r, W J [10] over the 24 residuals (padded), JB pixels at a time
+constexpr int DJ = 28, JB = 3, JPIX = (2 * NPAR + 1) * DJ;
+static_assert(JB * JPIX <= CN, "J and W J fit the contributions' space");
+// banded: the same over a chunk's 16 rows
+constexpr int BROWS = 16, BJ = 4 * BROWS + 4, BPREV = 4 * (BAND_R - 1);
+constexpr int WSTR = BPREV + GROUP_PTS + 8;  // values-only window of a quantity
+static_assert((2 * NPAR + 1) * BJ <= CN, "J and W J fit the contributions' space");
+static_assert(BPREV + GROUP_PTS == 4 * GROUP_WIN, "window");
+
+// Equilibrated normal equations of a slot's best model.
+struct EqLds {
+  double c[55];     // sc_p H_pq sc_q below the diagonal
+  double b[NPAR];   // sc_p g_p
+  double sc[NPAR];  // 1 / sqrt(H_pp), 0 for a frozen parameter
+  float hg[66];     // H (packed) and g
+};
+struct SlotLds {
+  EqLds eq;
+  float px[18];  // the fields of Pix that Weideman's series needs
+  float rf[10];  // RowFactors
+};
+
+template <bool BAND>
+struct Lds;
+template <>
+struct Lds<false> {
+  double2 c2[(CN + 3) / 4];  // contributions [29][CSTR]; chi^2 terms; J and W J
+  float a[JB * NOBS_HMI * ASTR];  // row sums
+  float obs[GROUP_SLOTS[KIND_DENSE6]][2 * 4 * NOBS_HMI];  // observations, weights
+  SlotLds slot[GROUP_SLOTS[KIND_DENSE6]];
+};
+template <>
+struct Lds<true> {
+  double2 c2[(CN + 3) / 4];
+  float a[BROWS * ASTR];
+  float prev[NACC * BPREV];  // the last 12 points of the chunk before
+  SlotLds slot[GROUP_SLOTS[KIND_BAND]];
+};
+constexpr int TSTR_D = 4 * NOBS_HMI + 1, TSTR_B = 4 * BROWS + 1;  // chi^2 terms of a slot
+constexpr int T_B = (4 * WSTR + 3) / 4;  // first chi^2 term behind the banded window
+static_assert(GROUP_SLOTS[KIND_DENSE6] * TSTR_D <= CN / 4, "chi^2 terms");
+static_assert(T_B + GROUP_SLOTS[KIND_BAND] * TSTR_B <= CN / 4, "window and chi^2 terms");
+static_assert(GROUP_SLOTS[KIND_DENSE6] * NOBS_HMI <= 64 &&
+                  GROUP_SLOTS[KIND_DENSE6] * NOBS_HMI * 8 <= JB * NOBS_HMI * ASTR,
+              "values-only row sums of every slot");
+static_assert(GROUP_SLOTS[KIND_BAND] * 4 * BPREV <= NACC * BPREV, "values-only tails");
+static_assert(4 * CN >= (int)sizeof(double) * WS_DOUBLES, "the eigen fallback's record fits");
+
+// The normal equations as 64 independent chains of sums over the residuals:
+// chain e < 55 is H's packed entry e = (p, q), chain 55 + p is g[p]; H's
+// entry 30 (azimuth x S0) is zero by construction and its chain takes g[9].
+// Column 10 of J is the residual itself.
+__device__ __forceinline__ void chain_of(int e, int& p, int& q) {
+  if (e == 30) {
+    p = 9;
+    q = NPAR;
+  } else if (e >= 55) {
+    p = e - 55;
+    q = NPAR;
+  } else {
+    p = 0;
+    while ((p + 1) * (p + 2) / 2 <= e) ++p;
+    q = e - p * (p + 1) / 2;
+  }
+}
+static_assert(pk_row(30) == 7 && pk_col(30) == 2 && hzero(0, 30) && hzero(1, 30) && hzero(2, 30) &&
+                  hzero(3, 30),
+              "entry 30 of H is zero");
+
+__device__ __forceinline__ float fma4(float4 w, float4 c, float s) {
+  return fmaf(w.w, c.w, fmaf(w.z, c.z, fmaf(w.y, c.y, fmaf(w.x, c.x, s))));
+}
+__device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ void st4(float* p, float a, float b, float c, float d) {
+  *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
+}
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ void put_model(SlotLds& S, const Pix& p, const RowFactors& f) {
+  const float px[18] = {p.vsi, p.invD, p.zs, p.a,      p.denr, p.denr2, p.c0,  p.hs2,  p.hc,
+                        p.hI,  p.hq,   p.hsin2g, p.hsg, p.s2h,  p.cgh,   p.eta0, p.alpha, p.oma};
+  const float rf[10] = {f.S0, f.S1, f.alpha, f.S1a, f.c2p, f.s2p, f.fB, f.fg, f.fv, f.fD};
+#pragma unroll
+  for (int k = 0; k < 18; ++k) S.px[k] = px[k];
+#pragma unroll
+  for (int k = 0; k < 10; ++k) S.rf[k] = rf[k];
+}
+__device__ __forceinline__ Pix get_pix(const SlotLds& S) {
+  Pix p;
+  float* const f[18] = {&p.vsi, &p.invD, &p.zs,     &p.a,   &p.denr, &p.denr2, &p.c0,   &p.hs2,
+                        &p.hc,  &p.hI,   &p.hq,     &p.hsin2g, &p.hsg, &p.s2h, &p.cgh,  &p.eta0,
+                        &p.alpha, &p.oma};
+#pragma unroll
+  for (int k = 0; k < 18; ++k) *f[k] = S.px[k];
+  p.ja = 0;
+  p.a0 = p.da = 0.f;
+  return p;
+}
+__device__ __forceinline__ RowFactors get_rf(const SlotLds& S) {
+  RowFactors r;
+  r.S0 = S.rf[0];
+  r.S1 = S.rf[1];
+  r.alpha = S.rf[2];
+  r.S1a = S.rf[3];
+  r.c2p = S.rf[4];
+  r.s2p = S.rf[5];
+  r.fB = S.rf[6];
+  r.fg = S.rf[7];
+  r.fv = S.rf[8];
+  r.fD = S.rf[9];
+  return r;
+}
+
+// Scale of parameter p in the equilibration of solve_cholesky.
+__device__ __forceinline__ double scale_of(const EqLds& E, uint32_t free_mask, int p) {
+  double maxd = 0.0;
+#pragma unroll
+  for (int k = 0; k < NPAR; ++k)
+    if ((free_mask >> k) & 1u) maxd = fmax(maxd, (double)E.hg[pk(k, k)]);
+  const double d = (double)E.hg[p * (p + 3) / 2];
+  const bool act = ((free_mask >> p) & 1u) && maxd > 0.0 && d > 1e-30 * maxd;
+  return act ? 1.0 / sqrt(d) : 0.0;
+}
+// This lane's chain (p, q) of the equilibrated system.
+__device__ __forceinline__ void scale_entry(EqLds& E, int e, int p, int q) {
+  if (q < NPAR) E.c[e] = E.sc[p] * (double)E.hg[e] * E.sc[q];
+  else E.b[p] = E.sc[p] * (double)E.hg[55 + p];
+}
+
+// The factorisation and substitutions of solve_cholesky on an equilibrated
+// system.  Returns 0, 1 (broken down) or 2 (nothing free).
+__device__ __forceinline__ int solve_equilibrated(const EqLds& E, double eps, double* delta) {
+  double sc[NPAR], L[55];
+  bool any = false;
+#pragma unroll
+  for (int p = 0; p < NPAR; ++p) {
+    sc[p] = E.sc[p];
+    any = any || sc[p] != 0.0;
+    delta[p] = 0.0;
+#pragma unroll
+    for (int q = 0; q < p; ++q) L[pk(p, q)] = E.c[pk(p, q)];
+    L[pk(p, p)] = (sc[p] != 0.0) ? 1.0 + eps : 1.0;
+  }
+  if (!any) return 2;
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < NPAR; ++j) {
+    double d = L[pk(j, j)];
+#pragma unroll
+    for (int k = 0; k < j; ++k) d = fma(-L[pk(j, k)], L[pk(j, k)], d);
+    ok = ok && (d > 0.0) && (d < 1.0e300);
+    const double ljj = sqrt(fmax(d, 1e-300));
+    const double rl = 1.0 / ljj;
+    L[pk(j, j)] = ljj;
+#pragma unroll
+    for (int i = j + 1; i < NPAR; ++i) {
+      double s = L[pk(i, j)];
+#pragma unroll
+      for (int k = 0; k < j; ++k) s = fma(-L[pk(i, k)], L[pk(j, k)], s);
+      L[pk(i, j)] = s * rl;
+    }
+  }
+  if (!ok) return 1;
+  double y[NPAR];
+#pragma unroll
+  for (int i = 0; i < NPAR; ++i) {
+    double s = E.b[i];
+#pragma unroll
+    for (int k = 0; k < i; ++k) s = fma(-L[pk(i, k)], y[k], s);
+    y[i] = s / L[pk(i, i)];
+  }
+#pragma unroll
+  for (int i = NPAR - 1; i >= 0; --i) {
+    double s = y[i];
+#pragma unroll
+    for (int k = i + 1; k < NPAR; ++k) s = fma(-L[pk(k, i)], y[k], s);
+    y[i] = s / L[pk(i, i)];
+  }
+#pragma unroll
+  for (int p = 0; p < NPAR; ++p) delta[p] = rounded(sc[p] * y[p]);
+  return 0;
+}
+
+// Slots of a mask, lowest first (wave-uniform).
+__device__ __forceinline__ int first_slot(unsigned m) {
+  return __builtin_amdgcn_readfirstlane(__ffs((int)m) - 1);
+}
+
+template <bool BAND>
+struct Layout;
+
+// ---- dense layout ----------------------------------------------------------
+// At most 64 synthesis points: one per lane.  MFMA lane (col, kq) = (lane % 16,
+// lane / 16) feeds tap A[row = col][point 4 i + kq] and quantity B[col] at that
+// point in step i, and receives rows 4 kq .. + 3 of quantity col.
+// The row sums of a launch in lane pairs (lm_kernel with two lanes per pixel)
+// are those of the even and of the odd records, added: the odd ones take MFMA
+// rows 8 .. 13.
+template <>
+struct Layout<false> {
+  Lds<false>& S;
+  const GroupArgs& ga;
+  const int lane, col, kq;
+  float* const c;
+  bool pair;
+  float dl, tap[16], rs;
+  int row;  // filter row in row slot lane % 6
+
+  __device__ __forceinline__ int row_of(int q) const {
+    const Consts& C = ga.A.C;
+    int r = q;
+    if (C.sw_k >= 0 && !pair) {
+#pragma unroll
+      for (int k = 0; k < NOBS_HMI; ++k)
+        if (q == k) r = C.slot_row[k];
+    }
+    return r;
+  }
+
+  __device__ __forceinline__ Layout(Lds<false>& S_, const GroupArgs& g, int lane_, bool pair_)
+      : S(S_), ga(g), lane(lane_), col(lane_ & 15), kq(lane_ >> 4),
+        c(reinterpret_cast<float*>(S_.c2)), pair(pair_) {
+    row = row_of(lane % NOBS_HMI);
+    rs = g.A.C.row_sum[0];
+#pragma unroll
+    for (int k = 1; k < NOBS_HMI; ++k)
+      if (row == k) rs = g.A.C.row_sum[k];
+    dl = g.T.dl[lane];
+    const int q = col & 7;
+    const bool mine = q < NOBS_HMI && (col < 8 || pair);
+    const float* w = g.T.taps + (mine ? row_of(q) : 0) * GROUP_PTS;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      tap[i] = mine && (!pair || (kq & 1) == (col >> 3)) ? w[4 * i + kq] : 0.f;
+  }
+
+  __device__ __forceinline__ bool take(int k, int64_t pix) {
+    constexpr int R = 4 * NOBS_HMI;
+    const float* W = ga.A.W_pp ? ga.A.W + pix * R : ga.A.W;
+    if (lane < R) S.obs[k][lane] = ga.A.stokes[pix * R + lane];
+    else if (lane < 2 * R) S.obs[k][lane] = W[lane - R];
+    return false;
+  }
+
+  __device__ __forceinline__ void store_rows(f32x4 v, float* a, int astr, int m, bool ok) const {
+    if (pair) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] += __shfl_xor(v[r], 32);
+    }
+    if (ok && kq < 2) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * kq + r < NOBS_HMI) a[(4 * kq + r) * astr + m] = v[r];
+    }
+  }
+
+  // chi^2 (without 1/dof) of the slots in lm, each in its owner's lane
+  __device__ __forceinline__ double values(unsigned lm, bool, int64_t, double) {
+    for (unsigned m = lm; m != 0u;) {
+      // up to three slots share the 16 columns of the MFMA
+      const unsigned m0 = m;
+#pragma unroll 1
+      for (int b = 0; b < 3 && m != 0u; ++b, m &= m - 1u) {
+        const Pix px = get_pix(S.slot[first_slot(m)]);
+        float v[NACC];
+        point_contrib<false>(dl, px, ga.A.C, v);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) c[(5 * b + k) * CSTR + lane] = v[k];
+      }
+      wave_fence();
+      const int b = col < 15 ? col / 5 : 2;
+      unsigned mb = m0;
+      if (b > 0) mb &= mb - 1u;
+      if (b > 1) mb &= mb - 1u;
+      // columns without a slot read the first slot's points
+      const bool ok = mb != 0u && col < 15;
+      const float* src = c + (ok ? col : 0) * CSTR + kq;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc = mfma4(tap[i], src[4 * i], acc);
+      wave_fence();
+      const int k = ok ? __ffs((int)mb) - 1 : 0;
+      store_rows(acc, S.a + k * (NOBS_HMI * 8), 8, col - 5 * b, ok);
+    }
+    wave_fence();
+    double2* T = S.c2;
+    const int k = lane / NOBS_HMI, q = lane - k * NOBS_HMI;
+    if ((lm >> k) & 1u) {
+      const float* a = S.a + k * (NOBS_HMI * 8) + q * 8;
+      const float4 h = ld4(a);
+      const float av[5] = {h.x, h.y, h.z, h.w, a[4]};
+      const RowFactors rf = get_rf(S.slot[k]);
+      float Sv[4], J[4][NPAR];
+      assemble_sample<false>(av, rs, rf, Sv, J);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float r = S.obs[k][s * NOBS_HMI + row] - Sv[s];
+        const float w = S.obs[k][(4 + s) * NOBS_HMI + row];
+        T[k * TSTR_D + 4 * q + s] = make_double2((double)w * (double)r, (double)r);
+      }
+    }
+    wave_fence();
+    double chi = 0.0;
+    if (lane < 32 && ((lm >> lane) & 1u)) {
+#pragma unroll
+      for (int i = 0; i < 4 * NOBS_HMI; ++i) {
+        const double2 t = T[lane * TSTR_D + i];
+        chi = fma(t.x, t.y, chi);
+      }
+    }
+    wave_fence();
+    return chi;
+  }
+
+  // Jacobian and equilibrated normal equations of the slots in jm; those in
+  // keep leave H as it is (Sect. 4.4) and take the new gradient
+  __device__ __forceinline__ void normal(unsigned jm, unsigned keep, int64_t, int cp, int cq) {
+    for (unsigned m = jm; m != 0u;) {
+      const unsigned m0 = m;
+      int nb = 0;
+#pragma unroll 1
+      for (; nb < JB && m != 0u; ++nb, m &= m - 1u) {
+        const Pix px = get_pix(S.slot[first_slot(m)]);
+        {
+          float v[NACC];
+          point_contrib<true>(dl, px, ga.A.C, v);
+#pragma unroll
+          for (int k = 0; k < NACC; ++k) c[k * CSTR + lane] = v[k];
+        }
+        wave_fence();
+        const float* s0 = c + col * CSTR + kq;
+        const float* s1 = c + (col + 16 < NACC ? col + 16 : col) * CSTR + kq;
+        f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          a0 = mfma4(tap[i], s0[4 * i], a0);
+          a1 = mfma4(tap[i], s1[4 * i], a1);
+        }
+        wave_fence();
+        float* a = S.a + nb * (NOBS_HMI * ASTR);
+        store_rows(a0, a, ASTR, col, true);
+        store_rows(a1, a, ASTR, col + 16, col + 16 < NACC);
+      }
+      wave_fence();
+      const int b = lane / NOBS_HMI, q = lane - b * NOBS_HMI;
+      if (b < nb) {
+        unsigned mb = m0;
+        if (b > 0) mb &= mb - 1u;
+        if (b > 1) mb &= mb - 1u;
+        const int k = __ffs((int)mb) - 1;
+        float a[NACC];
+#pragma unroll
+        for (int i = 0; i < NACC; ++i) a[i] = S.a[lane * ASTR + i];
+        const RowFactors rf = get_rf(S.slot[k]);
+        float Sv[4], J[4][NPAR], w[4];
+        assemble_sample<true>(a, rs, rf, Sv, J);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) w[s] = S.obs[k][(4 + s) * NOBS_HMI + row];
+        float* Jt = c + b * JPIX + 4 * q;
+        float* WJt = Jt + (NPAR + 1) * DJ;
+#pragma unroll
+        for (int p = 0; p < NPAR; ++p) {
+          st4(Jt + p * DJ, J[0][p], J[1][p], J[2][p], J[3][p]);
+          st4(WJt + p * DJ, w[0] * J[0][p], w[1] * J[1][p], w[2] * J[2][p], w[3] * J[3][p]);
+        }
+        float r[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) r[s] = S.obs[k][s * NOBS_HMI + row] - Sv[s];
+        st4(Jt + NPAR * DJ, r[0], r[1], r[2], r[3]);
+      }
+      wave_fence();
+      unsigned mb = m0;
+      for (int i = 0; i < nb; ++i, mb &= mb - 1u) {
+        const float* Jt = c + i * JPIX + cq * DJ;
+        const float* WJt = c + i * JPIX + (NPAR + 1 + cp) * DJ;
+        float h = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4 * NOBS_HMI; k += 4) h = fma4(ld4(WJt + k), ld4(Jt + k), h);
+        const int k0 = first_slot(mb);
+        EqLds& E = S.slot[k0].eq;
+        if (cq == NPAR || !((keep >> k0) & 1u)) E.hg[cq < NPAR ? lane : 55 + cp] = h;
+        if (lane == 0) E.hg[30] = 0.f;
+      }
+      wave_fence();
+      {
+        const int i = lane / NPAR, p = lane - i * NPAR;
+        if (i < nb) {
+          unsigned mk = m0;
+          if (i > 0) mk &= mk - 1u;
+          if (i > 1) mk &= mk - 1u;
+          EqLds& E = S.slot[__ffs((int)mk) - 1].eq;
+          E.sc[p] = scale_of(E, ga.A.free_mask, p);
+        }
+      }
+      wave_fence();
+      mb = m0;
+      for (int i = 0; i < nb; ++i, mb &= mb - 1u) {
+        EqLds& E = S.slot[first_slot(mb)].eq;
+        scale_entry(E, lane, cp, cq);
+        if (lane == 0) E.c[30] = 0.0;
+      }
+      wave_fence();
+    }
+  }
+};
+
+// ---- banded layout ---------------------------------------------------------
+// A chunk of 64 points is 16 blocks and completes 16 rows, whose points lie
+// in the chunk and in the last three blocks (12 points) of the one before.
+// Lane (jr, s) = (lane % 16, lane / 16) carries row jr of the chunk and its
+// Stokes parameter s.
+template <>
+struct Layout<true> {
+  Lds<true>& S;
+  const GroupArgs& ga;
+  const int lane, jr, s;
+  float* const c;
+
+  __device__ __forceinline__ Layout(Lds<true>& S_, const GroupArgs& g, int lane_, bool)
+      : S(S_), ga(g), lane(lane_), jr(lane_ & 15), s(lane_ >> 4),
+        c(reinterpret_cast<float*>(S_.c2)) {}
+
+  // Whether no weight of the pixel is negative (the running chi^2 never
+  // falls then).
+  __device__ __forceinline__ bool take(int, int64_t pix) {
+    const int rows = 4 * ga.A.C.n_obs;
+    const float* W = ga.A.W_pp ? ga.A.W + pix * rows : ga.A.W;
+    bool ok = true;
+    for (int r = lane; r < rows; r += 64) ok = ok && W[r] >= 0.f;
+    return __ballot(!ok) == 0ull;
+  }
+
+  struct Row {
+    float ob[4], wb[4], rs;
+    int j;
+    bool valid;
+  };
+  __device__ __forceinline__ Row load_row(int64_t pix, int ch) const {
+    const int no = ga.A.C.n_obs;
+    Row r;
+    r.j = ch * BROWS - (BAND_R - 1) + jr;
+    r.valid = r.j >= 0 && r.j < no;
+    if (!r.valid) r.j = 0;
+    const float* o = ga.A.stokes + pix * (int64_t)(4 * no) + r.j;
+    const float* W = (ga.A.W_pp ? ga.A.W + pix * (int64_t)(4 * no) : ga.A.W) + r.j;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      r.ob[k] = o[k * no];
+      r.wb[k] = W[k * no];
+    }
+    r.rs = ga.A.row_sums[r.j];
+    return r;
+  }
+  __device__ __forceinline__ static int64_t pix_of(int64_t pix, int k) {
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)(pix & 0xffffffffll), k);
+    const unsigned hi = __builtin_amdgcn_readlane((unsigned)(pix >> 32), k);
+    return (int64_t)(((unsigned long long)hi << 32) | lo);
+  }
+
+  // chi^2 (without 1/dof) of the slots in lm, each in its owner's lane.  A
+  // slot whose running sum has reached its bound (chi^2 of its best model) is
+  // left there: with weights >= 0 the rest cannot bring it back below.
+  __device__ __forceinline__ double values(unsigned lm, bool monotone, int64_t pix, double bound) {
+    double2* T = S.c2 + T_B;
+    double chi = 0.0;
+    for (int i = lane; i < GROUP_SLOTS[KIND_BAND] * 4 * BPREV; i += 64) S.prev[i] = 0.f;
+#pragma unroll 1
+    for (int ch = 0; ch < ga.T.n_chunk && lm != 0u; ++ch) {
+      const float dl = ga.T.dl[ch * GROUP_PTS + lane];
+#pragma unroll 1
+      for (unsigned m = lm; m != 0u; m &= m - 1u) {
+        const int k = first_slot(m);
+        const Row r = load_row(pix_of(pix, k), ch);
+        float4 w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = ld4(ga.T.taps + r.j * 16 + 4 * i);
+        const Pix px = get_pix(S.slot[k]);
+        float v[NACC];
+        point_contrib<false>(dl, px, ga.A.C, v);
+        // the quantities that the Stokes values need
+        const float u[4] = {v[0], v[2], v[3], v[4]};
+        float* prev = S.prev + k * (4 * BPREV);
+        if (lane < 4 * BPREV) c[(lane / BPREV) * WSTR + lane % BPREV] = prev[lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          c[i * WSTR + BPREV + lane] = u[i];
+          if (lane >= GROUP_PTS - BPREV) prev[i * BPREV + lane - (GROUP_PTS - BPREV)] = u[i];
+        }
+        wave_fence();
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum = fma4(w[i], ld4(&c[s * WSTR + 4 * (jr + i)]), sum);
+        S.a[jr * 5 + s] = sum;
+        wave_fence();
+        const float a[5] = {S.a[jr * 5], 0.f, S.a[jr * 5 + 1], S.a[jr * 5 + 2], S.a[jr * 5 + 3]};
+        const RowFactors rf = get_rf(S.slot[k]);
+        float Sv[4], J[4][NPAR], rr[4];
+        assemble_sample<false>(a, r.rs, rf, Sv, J);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rr[i] = r.ob[i] - Sv[i];
+        const float res = s == 0 ? rr[0] : s == 1 ? rr[1] : s == 2 ? rr[2] : rr[3];
+        const float wt = s == 0 ? r.wb[0] : s == 1 ? r.wb[1] : s == 2 ? r.wb[2] : r.wb[3];
+        T[k * TSTR_B + 4 * jr + s] = r.valid ? make_double2((double)wt * (double)res, (double)res)
+                                             : make_double2(0.0, 0.0);
+        wave_fence();
+      }
+      const bool mine = lane < 32 && ((lm >> lane) & 1u);
+      if (mine) {
+#pragma unroll 8
+        for (int i = 0; i < 4 * BROWS; ++i) {
+          const double2 t = T[lane * TSTR_B + i];
+          chi = fma(t.x, t.y, chi);
+        }
+      }
+      wave_fence();
+      lm &= ~(unsigned)__ballot(mine && monotone && rounded(chi * ga.A.inv_dof) >= bound);
+    }
+    return chi;
+  }
+
+  __device__ __forceinline__ void normal(unsigned jm, unsigned keep, int64_t pix, int cp, int cq) {
+    const float* Jt = c + cq * BJ;
+    const float* WJt = c + (NPAR + 1 + cp) * BJ;
+    for (unsigned m = jm; m != 0u; m &= m - 1u) {
+      const int k = first_slot(m);
+      const int64_t pk_ = pix_of(pix, k);
+      float h = 0.f;
+      for (int i = lane; i < NACC * BPREV; i += 64) S.prev[i] = 0.f;
+#pragma unroll 1
+      for (int ch = 0; ch < ga.T.n_chunk; ++ch) {
+        const Row r = load_row(pk_, ch);
+        float tap[GROUP_WIN + 1];
+#pragma unroll
+        for (int i = 0; i < GROUP_WIN + 1; i += 4) {
+          const float4 t = ld4(ga.T.taps_a + (ch * 64 + lane) * (GROUP_WIN + 1) + i);
+          tap[i] = t.x;
+          tap[i + 1] = t.y;
+          tap[i + 2] = t.z;
+          tap[i + 3] = t.w;
+        }
+        {
+          const Pix px = get_pix(S.slot[k]);
+          float v[NACC];
+          point_contrib<true>(ga.T.dl[ch * GROUP_PTS + lane], px, ga.A.C, v);
+#pragma unroll
+          for (int i = 0; i < NACC; ++i) c[i * CSTR + lane] = v[i];
+        }
+        wave_fence();
+        // row sums: rows jr, quantities jr and 16 + jr of this lane's column
+        {
+          const int m1 = jr + 16 < NACC ? jr + 16 : jr;
+          f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < GROUP_WIN; ++i) {
+            constexpr int PW = BAND_R - 1;
+            const float b0 = i < PW ? S.prev[jr * BPREV + 4 * i + s] : c[jr * CSTR + 4 * (i - PW) + s];
+            const float b1 = i < PW ? S.prev[m1 * BPREV + 4 * i + s] : c[m1 * CSTR + 4 * (i - PW) + s];
+            a0 = mfma4(tap[i], b0, a0);
+            a1 = mfma4(tap[i], b1, a1);
+          }
+          wave_fence();
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            S.a[(4 * s + i) * ASTR + jr] = a0[i];
+            if (jr + 16 < NACC) S.a[(4 * s + i) * ASTR + jr + 16] = a1[i];
+          }
+          for (int i = lane; i < NACC * (BPREV / 4); i += 64) {
+            const int q = i / (BPREV / 4), p = 4 * (i % (BPREV / 4));
+            const float4 v = ld4(&c[q * CSTR + GROUP_PTS - BPREV + p]);
+            st4(&S.prev[q * BPREV + p], v.x, v.y, v.z, v.w);
+          }
+        }
+        wave_fence();
+        {
+          float a[NACC];
+#pragma unroll
+          for (int i = 0; i < NACC; ++i) a[i] = S.a[jr * ASTR + i];
+          const RowFactors rf = get_rf(S.slot[k]);
+          float Sv[4], J[4][NPAR], rr[4];
+          assemble_sample<true>(a, r.rs, rf, Sv, J);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) rr[i] = r.ob[i] - Sv[i];
+          const float w = s == 0 ? r.wb[0] : s == 1 ? r.wb[1] : s == 2 ? r.wb[2] : r.wb[3];
+          const float res = s == 0 ? rr[0] : s == 1 ? rr[1] : s == 2 ? rr[2] : rr[3];
+#pragma unroll
+          for (int p = 0; p < NPAR; ++p) {
+            const float d = s == 0 ? J[0][p] : s == 1 ? J[1][p] : s == 2 ? J[2][p] : J[3][p];
+            c[p * BJ + 4 * jr + s] = r.valid ? d : 0.f;
+            c[(NPAR + 1 + p) * BJ + 4 * jr + s] = r.valid ? w * d : 0.f;
+          }
+          c[NPAR * BJ + 4 * jr + s] = r.valid ? res : 0.f;
+        }
+        wave_fence();
+#pragma unroll 4
+        for (int i = 0; i < 4 * BROWS; i += 4) h = fma4(ld4(WJt + i), ld4(Jt + i), h);
+        wave_fence();
+      }
+      EqLds& E = S.slot[k].eq;
+      if (cq == NPAR || !((keep >> k) & 1u)) E.hg[cq < NPAR ? lane : 55 + cp] = h;
+      if (lane == 0) E.hg[30] = 0.f;
+      wave_fence();
+      if (lane < NPAR) E.sc[lane] = scale_of(E, ga.A.free_mask, lane);
+      wave_fence();
+      scale_entry(E, lane, cp, cq);
+      if (lane == 0) E.c[30] = 0.0;
+      wave_fence();
+    }
+  }
+};
+
+__device__ __forceinline__ unsigned long long wave_total(unsigned v) {
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+}  // namespace
+
+template <bool BAND>
+__global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
+  __shared__ Lds<BAND> S;
+  const LMArgs& A = ga.A;
+  const unsigned long long n_total = A.n_dev ? *A.n_dev : (unsigned long long)A.n;
+  const int lane = threadIdx.x;
+  const bool serve = n_total <= (unsigned long long)ga.n_max;
+  if (A.n_dev && blockIdx.x == 0 && lane == 0) A.work[GROUP_LEFT_SLOT] = serve ? 0ull : n_total;
+  if (!serve) return;
+  // the launch's own rule for lane pairs, whose sums differ by rounding
+  const bool pair = A.lpp_max >= 2 && n_total <= (unsigned long long)A.pair_max;
+  Layout<BAND> lay(S, ga, lane, pair);
+  // as many slots as the launch's pixels fill: a wave's slots share its turns
+  const unsigned long long fill = (n_total + gridDim.x - 1) / gridDim.x;
+  const int slots = fill < (unsigned)GROUP_SLOTS[BAND] ? (int)fill : GROUP_SLOTS[BAND];
+  const int rows = 4 * A.C.n_obs;
+  int cp, cq;
+  chain_of(lane, cp, cq);
+  bool live = false, fresh = false, exhausted = lane >= slots, need_fb = false;
+  bool monotone = false;
+  int64_t pix = 0;
+  float Mb[NPAR], Mc[NPAR];
+#pragma unroll
+  for (int k = 0; k < NPAR; ++k) Mb[k] = Mc[k] = 0.f;
+  double chib = 0.0, eps = 0.0;
+  int it = 0;
+  unsigned n_pix = 0, n_trial = 0, n_acc = 0, n_pass = 0, n_fb = 0, n_jac = 0, n_hess = 0;
+
+  for (;;) {
+    // ---- slots whose pixel has finished take the next -----------------------
+    const unsigned long long nm = __ballot(!live && !exhausted);
+    if (nm != 0ull) {
+      unsigned long long k0 = 0;
+      if (lane == 0) k0 = atomicAdd(&A.work[A.qbase], (unsigned long long)__popcll(nm));
+      const unsigned k_lo = __builtin_amdgcn_readfirstlane((unsigned)(k0 & 0xffffffffull));
+      const unsigned k_hi = __builtin_amdgcn_readfirstlane((unsigned)(k0 >> 32));
+      if (!live && !exhausted) {
+        const unsigned long long pos = (((unsigned long long)k_hi << 32) | k_lo) +
+                                       (unsigned)__popcll(nm & ((1ull << lane) - 1ull));
+        if (pos >= n_total) {
+          exhausted = true;
+        } else {
+          pix = A.idx ? (int64_t)A.idx[pos] : (int64_t)pos;
+          double M0[NPAR];
+          if (A.init) {
+#pragma unroll
+            for (int k = 0; k < NPAR; ++k) M0[k] = (double)A.init[pix * NPAR + k];
+          } else {
+            const double d0[NPAR] = {1500.0, 90.0, 90.0, 0.0, 35.0, 0.25, 15.5, 0.3, 0.7, 0.6};
+#pragma unroll
+            for (int k = 0; k < NPAR; ++k) M0[k] = d0[k];
+          }
+          project(M0);
+#pragma unroll
+          for (int k = 0; k < NPAR; ++k) Mc[k] = (float)M0[k];
+          live = true;
+          fresh = true;
+          eps = A.eps0;
+          it = 0;
+        }
+      }
+      for (unsigned m = (unsigned)__ballot(live && fresh); m != 0u; m &= m - 1u) {
+        const int k = first_slot(m);
+        const unsigned lo = __builtin_amdgcn_readlane((unsigned)(pix & 0xffffffffll), k);
+        const unsigned hi = __builtin_amdgcn_readlane((unsigned)(pix >> 32), k);
+        const bool f = lay.take(k, (int64_t)(((unsigned long long)hi << 32) | lo));
+        if (lane == k) monotone = f;
+      }
+    }
+    // ---- eigen/SVD fallbacks of the last steps, one slot at a time ----------
+    for (unsigned fbm = (unsigned)__ballot(need_fb); fbm != 0u; fbm &= fbm - 1u) {
+      const int L = first_slot(fbm);
+      double* sws = reinterpret_cast<double*>(S.c2);
+      const float* hg = S.slot[L].eq.hg;
+      solve_eigen_wave(hg, 1, hg + 55, 1, __shfl(eps, L), A.free_mask, sws, lane);
+      if (lane == L) {
+        ++n_fb;
+        double Mt[NPAR];
+#pragma unroll
+        for (int k = 0; k < NPAR; ++k) Mt[k] = (double)Mb[k] + sws[200 + k];
+        project(Mt);
+#pragma unroll
+        for (int k = 0; k < NPAR; ++k) Mc[k] = (float)Mt[k];
+        need_fb = false;
+      }
+      __syncthreads();  // the step is read before the record is reused
+    }
+    const unsigned lm = (unsigned)__ballot(live);
+    if (lm == 0u) break;
+
+    // ---- the trials (or starts): chi^2 without derivatives ------------------
+    if (live) {
+      Pix px;
+      RowFactors rf;
+      pix_setup(Mc, A.C, px);
+      row_factors(Mc, px, A.C, rf);
+      put_model(S.slot[lane], px, rf);
+    }
+    wave_fence();
+    const double chi =
+        rounded(lay.values(lm, monotone, pix, fresh ? (double)INFINITY : chib) * A.inv_dof);
+    bool want_j = false, keep_h = false;
+    if (live) {
+      ++n_pass;
+      int done = -1;
+      bool bad_input = false, new_best = true;
+      if (fresh) {
+        if (!isfinite(chi)) {
+          done = 3;
+          // a non-finite observation or weight: the pixel is not fitted
+          const float* obs = A.stokes + pix * rows;
+          const float* W = A.W_pp ? A.W + pix * rows : A.W;
+          for (int r = 0; r < rows; ++r)
+            bad_input = bad_input || !isfinite(obs[r]) || !isfinite(W[r]);
+          if (bad_input) --n_pass;
+        }
+        chib = chi;
+      } else {
+        ++it;
+        ++n_trial;
+        new_best = isfinite(chi) && chi < chib;
+        if (new_best) {
+          const double dec = chib - chi;
+          keep_h = chib < A.hess_reuse;
+          chib = chi;
+          eps = eps_down(eps);
+          ++n_acc;
+          if (dec < A.rel_tol * (chi + dec)) done = 0;
+        } else {
+          eps = eps_up(eps);
+          if (eps > A.eps_max) done = 2;
+        }
+      }
+      fresh = false;
+      if (new_best) {
+#pragma unroll
+        for (int k = 0; k < NPAR; ++k) Mb[k] = Mc[k];
+      }
+      if (done < 0 && it >= A.max_iter) done = 1;
+      if (done >= 0) {
+        if (bad_input) {
+#pragma unroll
+          for (int k = 0; k < NPAR; ++k) A.params[pix * NPAR + k] = __builtin_nanf("");
+          A.chi2[pix] = __builtin_nan("");
+          A.iters[pix] = 0;
+          if (A.status) A.status[pix] = 3;
+        } else {
+#pragma unroll
+          for (int k = 0; k < NPAR; ++k) A.params[pix * NPAR + k] = Mb[k];
+          A.chi2[pix] = chib;
+          A.iters[pix] = it;
+          if (A.status) A.status[pix] = done;
+        }
+        ++n_pix;
+        live = false;
+      }
+      want_j = live && new_best;
+    }
+    // ---- derivatives and normal equations of the new best models ------------
+    const unsigned jm = (unsigned)__ballot(want_j);
+    const unsigned keep = (unsigned)__ballot(want_j && keep_h);
+    if (want_j) {
+      ++n_jac;
+      if (!keep_h) ++n_hess;
+    }
+    if (jm != 0u) lay.normal(jm, keep, pix, cp, cq);
+    // ---- damped float64 steps from the best models --------------------------
+    if (live) {
+      double delta[NPAR];
+      if (solve_equilibrated(S.slot[lane].eq, eps, delta) == 1) {
+        need_fb = true;  // taken at the top of the next turn, by the whole wave
+      } else {
+        double Mt[NPAR];
+#pragma unroll
+        for (int k = 0; k < NPAR; ++k) Mt[k] = (double)Mb[k] + delta[k];
+        project(Mt);
+#pragma unroll
+        for (int k = 0; k < NPAR; ++k) Mc[k] = (float)Mt[k];
+      }
+    }
+    wave_fence();
+  }
+  const unsigned long long tp = wave_total(n_pix), tt = wave_total(n_trial), ta = wave_total(n_acc),
+                           ts = wave_total(n_pass), tf = wave_total(n_fb), tj = wave_total(n_jac),
+                           th = wave_total(n_hess);
+  if (lane == 0) {
+    atomicAdd(&A.work[0], tj);
+    atomicAdd(&A.work[1], tp);
+    atomicAdd(&A.work[2], tt);
+    atomicAdd(&A.work[3], ta);
+    atomicAdd(&A.work[4], ts);
+    if (tf) atomicAdd(&A.work[5], tf);
+    atomicAdd(&A.work[6], 1ull);
+    atomicAdd(&A.work[7], th);
+    atomicAdd(&A.work[8], tj);
+  }
+}
+
+hipError_t launch_lm_group(const GroupArgs& a, int kind, int grid, hipStream_t s) {
+  if (kind == KIND_BAND) lm_group_kernel<true><<<grid, 64, 0, s>>>(a);
+  else lm_group_kernel<false><<<grid, 64, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+hipError_t lm_group_blocks_per_cu(int kind, int* out) {
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      out, kind == KIND_BAND ? (const void*)lm_group_kernel<true> : (const void*)lm_group_kernel<false>,
+      64, 0);
+}
+
+}  // namespace vfisv

@@ -805,6 +805,7 @@ int invert_learned_impl(vfisv_ctx* ctx, const vfisv_instrument* inst, vfisv_mlp*
     return fail(ctx, VFISV_E_UNSUPPORTED, "invert_learned: the fixed-iteration scheme is not served here");
   // from the network's start most trials are accepted (about half, against
   // a third from the default model), so the fused pass is the default here
+  const FitUse use_short = fit_use(o, FIT_SHORT), use_refit = fit_use(o, FIT_REFIT);
   if (o.deriv_split < 0) o.deriv_split = 0;
   if (learned_max_iter < 0) return fail(ctx, VFISV_E_INVALID, "invert_learned: learned_max_iter < 0");
   if (n < 0) return fail(ctx, VFISV_E_INVALID, "invert_learned: n < 0");
@@ -874,7 +875,7 @@ int invert_learned_impl(vfisv_ctx* ctx, const vfisv_instrument* inst, vfisv_mlp*
   vfisv_options ol = o;
   ol.max_iter = learned_max_iter;
   rc = enqueue_lm(ctx, inst, n, nullptr, nullptr, stokes, W, W_per_pixel, init, ol, inv_dof,
-                  params, chi2, iters, s_short, s, true, 1, !noalloc);
+                  params, chi2, iters, s_short, s, true, 1, !noalloc, use_short);
   if (rc) return rc;
   e = mark(2);
   if (e == hipSuccess && timing) e = copy_u64(ctx->d_phase_snap, ctx->d_work, 16, s);
@@ -896,7 +897,7 @@ int invert_learned_impl(vfisv_ctx* ctx, const vfisv_instrument* inst, vfisv_mlp*
   e = mark(3);
   if (e != hipSuccess) return hip_fail(ctx, e, "invert_learned: phase event");
   rc = enqueue_lm(ctx, inst, n, count, list, stokes, W, W_per_pixel, combined ? init : nullptr, o,
-                  inv_dof, p_fb, c_fb, i_fb, s_fb, s, false, 2, !noalloc);
+                  inv_dof, p_fb, c_fb, i_fb, s_fb, s, false, 2, !noalloc, use_refit);
   if (rc) return rc;
   e = mark(4);
   if (e == hipSuccess && timing) e = copy_u64(ctx->d_phase_snap + 16, ctx->d_work, 16, s);
