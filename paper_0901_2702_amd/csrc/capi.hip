@@ -187,6 +187,19 @@ static int64_t group_limit(const vfisv_ctx* ctx, const vfisv_instrument* inst,
   return ctx->tuned[inst->kind].valid ? std::min<int64_t>(most, 16384) : most;
 }
 
+// Enqueue the group inverter for `a`, a launch of at most n pixels that it
+// takes up to group_max.
+static hipError_t enqueue_group(vfisv_ctx* ctx, const vfisv_instrument* inst, const LMArgs& a,
+                                int64_t n, int64_t group_max, hipStream_t s) {
+  GroupArgs g;
+  g.A = a;
+  g.T = inst->group;
+  g.n_max = group_max;
+  const int64_t most = n < group_max ? n : group_max;
+  const int64_t cap = (int64_t)ctx->num_cus * ctx->group_blocks_per_cu[inst->kind];
+  return launch_lm_group(g, inst->kind, (int)(most < cap ? most : cap), s);
+}
+
 int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
                const unsigned long long* n_dev, const int32_t* idx, const float* stokes,
                const float* W, int W_pp, const float* init, const vfisv_options& o,
@@ -218,13 +231,7 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
   hipError_t e = launch_reset(ctx->d_work, reset_all, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "invert: counter reset");
   if (group_max > 0 && (n_dev || n <= group_max)) {
-    GroupArgs g;
-    g.A = a;
-    g.T = inst->group;
-    g.n_max = group_max;
-    const int64_t most = n < group_max ? n : group_max;
-    const int64_t cap = (int64_t)ctx->num_cus * ctx->group_blocks_per_cu[inst->kind];
-    e = launch_lm_group(g, inst->kind, (int)(most < cap ? most : cap), s);
+    e = enqueue_group(ctx, inst, a, n, group_max, s);
     if (e != hipSuccess) return hip_fail(ctx, e, "invert launch");
     if (n <= group_max) return VFISV_OK;
     a.n_dev = ctx->d_work + GROUP_LEFT_SLOT;
@@ -841,6 +848,24 @@ int vfisv_invert_batches(vfisv_ctx* ctx, const vfisv_batch* batches, int n_batch
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const int grid = lm_grid(ctx, total, ctx->band_blocks_per_cu, o, -1);
   hipStream_t s = (hipStream_t)stream;
+  // Few pixels in all: the batches one after the other in the group inverter,
+  // whose time goes with their sizes (20,000 fine spectra and 50,001 HMI
+  // pixels 13 ms), where one lane's fit of the slowest layout sets the time
+  // of lm_batches_kernel (36 ms) until the batches are a share of their
+  // limits each that adds up to one.
+  double share = 0.0;
+  for (int i = 0; i < n_batches; ++i) {
+    const int64_t most = group_limit(ctx, batches[i].inst, o, fit_use(o, FIT_PLAIN));
+    share += batches[i].n == 0 ? 0.0 : most > 0 ? (double)batches[i].n / (double)most : 2.0;
+  }
+  if (share <= 1.0) {
+    e = launch_reset(ctx->d_work, true, s);
+    for (int i = 0; i < n_batches && e == hipSuccess; ++i)
+      if (batches[i].n > 0)
+        e = enqueue_group(ctx, batches[i].inst, B.a[i], batches[i].n, batches[i].n, s);
+    if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches launch");
+    return VFISV_OK;
+  }
   // banded batches read interleaved copies, side by side in one buffer
   size_t need = 0;
   for (int i = 0; i < n_batches; ++i)

@@ -143,3 +143,28 @@ def test_learned_path(ctx, name):
         out = learned.invert_learned(ctx, inst, net, o, W, chi2_accept=tau)
         _same(ref, out, (name, tau))
         assert int((out["status"] & vf.FALLBACK_USED).ne(0).sum()) > 0
+
+
+def test_batches(ctx):
+    """Batches of both layouts, one of them empty, one with weights per pixel."""
+    dev = ctx.device
+    hs, fs = wl.hmi_instrument(), wl.fine_instrument()
+    hi, fi = vf.Instrument.from_spec(ctx, hs), vf.Instrument.from_spec(ctx, fs)
+    rng = np.random.default_rng(39)
+    Wh = (wl.weights(6)[None] * rng.uniform(0.5, 1.5, (900, 4, 6))).astype(np.float32)
+    batches = [dict(inst=fi, stokes=torch.tensor(_obs(fs, 300, 40), device=dev),
+                    W=torch.tensor(wl.weights(fs.n_obs), device=dev)),
+               dict(inst=hi, stokes=torch.zeros((0, 4, 6), device=dev),
+                    W=torch.tensor(wl.weights(6), device=dev)),
+               dict(inst=hi, stokes=torch.tensor(_obs(hs, 900, 41), device=dev),
+                    W=torch.tensor(Wh, device=dev))]
+    print("[gpu] group batches: lanes", flush=True)
+    ref = vf.invert_batches(ctx, batches, opts=vf.Options(**LANES))
+    cr = ctx.counters()
+    print("[gpu] group batches: group", flush=True)
+    out = vf.invert_batches(ctx, batches)
+    c = ctx.counters()
+    for i, (a, b) in enumerate(zip(ref, out)):
+        _same(a, b, ("batches", i))
+    for k in ("pixels", "trials", "accepts", "jacobians"):
+        assert c[k] == cr[k], k
