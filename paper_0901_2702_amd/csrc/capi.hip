@@ -99,9 +99,8 @@ static void fill_lm_args(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n
                          int32_t* iters, int32_t* status, LMArgs& a) {
   a.C = inst->C;
   a.C.vtab = ctx->d_vtab;
-  a.pts = inst->d_pts;
-  a.pts5 = inst->d_pts5;
-  a.ptsv = inst->d_ptsv ? inst->d_ptsv : inst->d_pts;
+  a.rows = inst->rows;
+  a.rows_nat = inst->rows_nat;
   a.blocks = inst->d_blocks;
   a.row_sums = inst->d_row_sums;
   a.qbase = QUEUE_SLOT0;
@@ -167,15 +166,15 @@ static int grow_obs4(vfisv_ctx* ctx, size_t bytes) {
 
 // The pixels up to which the group inverter takes a launch, by layout and
 // use (FitUse), where it is faster than lm_kernel on 65,536 lanes.  Measured
-// (group / lm_kernel): plain HMI fits 4,096 pixels 0.65 / 3.95 ms, 65,536
-// 4.0 / 4.7, 131,072 7.6 / 8.0, 196,608 11.1 / 11.3, 262,144 14.5 / 14.4;
-// fine spectra 1,000 pixels 1.7 / 29, 100,003 38 / 64, 262,144 96 / 104,
-// 400,000 147 / 144.  From the network's start more trials are accepted and
-// need their Jacobian, which lm_kernel computes ahead: short fits of HMI
-// pixels 20,011 0.61 / 1.18 ms, 100,000 2.15 / 2.40, 131,072 2.73 / 2.69.
-// Re-fits, which lm_kernel runs in lane pairs up to 36,044 pixels: 1,139
-// pixels 0.61 / 2.36 ms, 11,673 1.19 / 2.51, 51,330 4.0 / 3.7.
-constexpr int64_t GROUP_MAX[2][4] = {{0, 196608, 131072, 32768}, {0, 262144, 131072, 131072}};
+// (group / lm_kernel): plain HMI fits 4,096 pixels 0.65 / 3.95 ms, 50,000
+// 3.35 / 4.04, 65,536 4.11 / 4.05, 114,688 6.7 / 7.5, 131,072 7.6 / 7.0; fine
+// spectra 1,000 pixels 1.7 / 29, 100,003 38 / 64, 262,144 95.6 / 97.2, 400,000
+// 147 / 136.  From the network's start more trials are accepted and need
+// their Jacobian, which lm_kernel computes ahead: short fits of HMI pixels
+// 20,011 0.60 / 1.12 ms, 50,000 1.19 / 1.22, 65,536 1.49 / 1.29.  Re-fits,
+// which lm_kernel runs in lane pairs up to 36,044 pixels: 1,139 pixels 0.65 /
+// 2.36 ms, 34,776 2.77 / 2.80, 40,263 2.98 / 3.40, 51,000 3.9 / 3.4.
+constexpr int64_t GROUP_MAX[2][4] = {{0, 122880, 53248, 45056}, {0, 262144, 131072, 131072}};
 
 // The largest batch that the group inverter takes under these options, 0 if
 // none: it has Weideman's series and the fit with convergence exits only.
@@ -469,7 +468,7 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
     if (rsum > 0.0) max_drop = std::fmax(max_drop, drop / rsum);
     row_sum[(size_t)i] = (float)ksum;
   }
-  std::vector<Point> pts, pts5, ptsv;
+  std::vector<Point> pts;
   std::vector<Block> blocks;
   int n_taps = 0, n_active = 0;
   if (no == NOBS_HMI) {
@@ -491,9 +490,9 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
       if (mask) pts.push_back(p);
     }
     n_active = (int)pts.size();
-    // Windowed records: row a (the first to end) and row b (the last to
-    // start) share register slot 4 when they overlap on at most OV_MAX
-    // records; the other four rows take slots 0-3 in order.
+    // Order of the rows in chi^2 and the normal equations: when row a (the
+    // first to end) and row b (the last to start) overlap on at most OV_MAX
+    // records, b and a come last, after the other four in order.
     std::vector<int> fr(no, -1), lr(no, -1);
     for (int k = 0; k < (int)pts.size(); ++k)
       for (int i = 0; i < no; ++i)
@@ -511,42 +510,13 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
       if (i != ra && (rb < 0 || fr[(size_t)i] > fr[(size_t)rb])) rb = i;
     if (all_rows && ra >= 0 && rb >= 0 && fr[(size_t)ra] < fr[(size_t)rb] &&
         lr[(size_t)ra] - fr[(size_t)rb] + 1 <= OV_MAX) {
-      const int sw = fr[(size_t)rb];
       int slot = 0;
       for (int i = 0; i < no; ++i)
         if (i != ra && i != rb) inst->C.slot_row[slot++] = i;
       inst->C.slot_row[4] = rb;
       inst->C.slot_row[5] = ra;
       for (int q = 0; q < 6; ++q) inst->C.slot_rs[q] = row_sum[(size_t)inst->C.slot_row[q]];
-      pts5.resize(pts.size());
-      for (int k = 0; k < (int)pts.size(); ++k) {
-        const Point& P = pts[(size_t)k];
-        Point& Q = pts5[(size_t)k];
-        std::memset(&Q, 0, sizeof Q);
-        Q.dl = P.dl;
-        for (int q = 0; q < 4; ++q) Q.w[q] = P.w[inst->C.slot_row[q]];
-        Q.w[4] = k < sw ? P.w[ra] : P.w[rb];
-        Q.w[5] = k < sw ? 0.f : P.w[ra];
-        uint32_t m = 0;
-        for (int q = 0; q < 6; ++q)
-          if (Q.w[q] != 0.f) m |= 1u << q;
-        std::memcpy(&Q.w[6], &m, 4);
-      }
-      inst->C.sw_k = sw;
-      // the values-only pass: all six rows in the slot order above
-      ptsv.resize(pts.size());
-      for (int k = 0; k < (int)pts.size(); ++k) {
-        const Point& P = pts[(size_t)k];
-        Point& Q = ptsv[(size_t)k];
-        std::memset(&Q, 0, sizeof Q);
-        Q.dl = P.dl;
-        uint32_t m = 0;
-        for (int q = 0; q < 6; ++q) {
-          Q.w[q] = P.w[inst->C.slot_row[q]];
-          if (Q.w[q] != 0.f) m |= 1u << q;
-        }
-        std::memcpy(&Q.w[6], &m, 4);
-      }
+      inst->C.sw_k = fr[(size_t)rb];
     }
   } else {
     // banded: row i's kept taps must lie in points a0 + 4 i .. a0 + 4 i + 15
@@ -610,6 +580,33 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
   inst->info.lm_register_rows =
       inst->kind == KIND_BAND ? BAND_R : (inst->C.sw_k >= 0 ? 5 : NOBS_HMI);
 
+  // Tap tables of lm_kernel's dense row sums: per point the taps by MFMA row,
+  // in both orders of the rows, then the offsets.
+  std::vector<float> mtab;
+  size_t o_nat = 0, o_dl = 0;
+  auto dense_taps = [&](bool slots, DenseTaps* T) {
+    T->n = T->b_beg = (int)pts.size();
+    T->a_end = 0;
+    for (int k = 0; k < (int)pts.size(); ++k) {
+      float t[4][2] = {};
+      for (int q = 0; q < NOBS_HMI; ++q) {
+        const float w = pts[(size_t)k].w[slots ? inst->C.slot_row[q] : q];
+        t[SLOT_ROW[q]][SLOT_GROUP[q]] = w;
+        if (w == 0.f) continue;
+        if (SLOT_GROUP[q] == 1) T->b_beg = std::min(T->b_beg, k);
+        else T->a_end = k + 1;
+      }
+      mtab.insert(mtab.end(), &t[0][0], &t[0][0] + 8);
+    }
+    T->a_end = std::max(T->a_end, T->b_beg);
+  };
+  if (inst->kind == KIND_DENSE6) {
+    dense_taps(inst->C.sw_k >= 0, &inst->rows);
+    o_nat = mtab.size();
+    dense_taps(false, &inst->rows_nat);
+    o_dl = mtab.size();
+    for (const Point& p : pts) mtab.push_back(p.dl);
+  }
   // Tables of the group inverter: the points in whole chunks; the taps by row
   // (dense: over all points; banded: over the row's 16 points) and, banded,
   // as matrix operands: lane l of chunk ch feeds row 16 ch - 3 + l % 16 with
@@ -674,18 +671,6 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
     e = hipMalloc(&inst->d_pts, bytes);
     if (e == hipSuccess && !pts.empty())
       e = hipMemcpy(inst->d_pts, pts.data(), sizeof(Point) * pts.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !pts5.empty()) {
-      e = hipMalloc(&inst->d_pts5, sizeof(Point) * pts5.size());
-      if (e == hipSuccess)
-        e = hipMemcpy(inst->d_pts5, pts5.data(), sizeof(Point) * pts5.size(),
-                      hipMemcpyHostToDevice);
-    }
-    if (e == hipSuccess && !ptsv.empty()) {
-      e = hipMalloc(&inst->d_ptsv, sizeof(Point) * ptsv.size());
-      if (e == hipSuccess)
-        e = hipMemcpy(inst->d_ptsv, ptsv.data(), sizeof(Point) * ptsv.size(),
-                      hipMemcpyHostToDevice);
-    }
   } else {
     e = hipMalloc(&inst->d_blocks, sizeof(Block) * blocks.size());
     if (e == hipSuccess) e = hipMalloc(&inst->d_row_sums, sizeof(float) * (size_t)no);
@@ -695,6 +680,14 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
     if (e == hipSuccess)
       e = hipMemcpy(inst->d_row_sums, row_sum.data(), sizeof(float) * (size_t)no,
                     hipMemcpyHostToDevice);
+  }
+  if (e == hipSuccess && !mtab.empty()) {
+    e = hipMalloc(&inst->d_rows, sizeof(float) * mtab.size());
+    if (e == hipSuccess)
+      e = hipMemcpy(inst->d_rows, mtab.data(), sizeof(float) * mtab.size(), hipMemcpyHostToDevice);
+    inst->rows.t = (const float2*)inst->d_rows;
+    inst->rows_nat.t = (const float2*)(inst->d_rows + o_nat);
+    inst->rows.dl = inst->rows_nat.dl = inst->d_rows + o_dl;
   }
   if (e == hipSuccess && (inst->kind == KIND_BAND || inst->group.n_chunk == 1)) {
     std::vector<float> host(gdl);
@@ -712,8 +705,7 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
   if (e != hipSuccess) {
     if (inst->d_group) hipFree(inst->d_group);
     if (inst->d_pts) hipFree(inst->d_pts);
-    if (inst->d_pts5) hipFree(inst->d_pts5);
-    if (inst->d_ptsv) hipFree(inst->d_ptsv);
+    if (inst->d_rows) hipFree(inst->d_rows);
     if (inst->d_blocks) hipFree(inst->d_blocks);
     if (inst->d_row_sums) hipFree(inst->d_row_sums);
     hipFree(inst->d_obs_x);
@@ -735,8 +727,7 @@ int vfisv_instrument_destroy(vfisv_instrument* inst) {
   hipSetDevice(inst->device);
   hipDeviceSynchronize();
   if (inst->d_pts) hipFree(inst->d_pts);
-  if (inst->d_pts5) hipFree(inst->d_pts5);
-  if (inst->d_ptsv) hipFree(inst->d_ptsv);
+  if (inst->d_rows) hipFree(inst->d_rows);
   if (inst->d_blocks) hipFree(inst->d_blocks);
   if (inst->d_row_sums) hipFree(inst->d_row_sums);
   if (inst->d_obs_x) hipFree(inst->d_obs_x);

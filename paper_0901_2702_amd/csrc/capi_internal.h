@@ -67,8 +67,8 @@ struct vfisv_instrument {
                    // instrument never reads the context
   int kind = vfisv::KIND_DENSE6;
   vfisv::Point* d_pts = nullptr;       // KIND_DENSE6
-  vfisv::Point* d_pts5 = nullptr;      // KIND_DENSE6, windowed records (C.sw_k >= 0)
-  vfisv::Point* d_ptsv = nullptr;      // KIND_DENSE6, rows in the windowed slot order
+  float* d_rows = nullptr;             // KIND_DENSE6: matrix-core tap tables of lm_kernel
+  vfisv::DenseTaps rows{}, rows_nat{};  // in d_rows
   vfisv::Block* d_blocks = nullptr;    // KIND_BAND
   float* d_row_sums = nullptr;         // KIND_BAND
   float* d_obs_x = nullptr;            // [n_obs] observed wavelength of each sample

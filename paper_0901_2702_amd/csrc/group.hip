@@ -38,21 +38,12 @@ namespace vfisv {
 
 namespace {
 
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-
 // Orders this wave's LDS accesses (a workgroup is one wave, whose LDS
 // operations complete in order: the compiler alone must not move them).
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// A value whose last operation is not contracted with what follows:
-// lm_kernel rounds here, at the end of a basic block.
-__device__ __forceinline__ double rounded(double x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 
 constexpr int NEQ = 64;               // chains of the normal equations

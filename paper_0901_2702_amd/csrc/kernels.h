@@ -27,10 +27,8 @@ constexpr int HIST_MAX = 4096;  // iteration-histogram bins (kept after the work
 
 struct LMArgs {
   Consts C;
-  const Point* pts;        // KIND_DENSE6
-  const Point* pts5;       // KIND_DENSE6, windowed records (C.sw_k >= 0)
-  const Point* ptsv;       // KIND_DENSE6, the rows in the windowed pass's slot
-                           // order (values-only pass; = pts when C.sw_k < 0)
+  DenseTaps rows;          // KIND_DENSE6, rows in the order of C.sw_k
+  DenseTaps rows_nat;      // the same in the filter's own order (lane pairs)
   const Block* blocks;     // KIND_BAND: C.n_obs + BAND_R - 1 blocks
   const float* row_sums;   // KIND_BAND: [n_obs] sums of the kept taps
   const float* stokes;

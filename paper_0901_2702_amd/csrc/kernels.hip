@@ -31,15 +31,6 @@ __device__ __forceinline__ unsigned long long bcast_lane0(unsigned long long v) 
   return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
-  for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned lo = __shfl_xor((unsigned)(v & 0xffffffffull), off);
-    const unsigned hi = __shfl_xor((unsigned)(v >> 32), off);
-    v += ((unsigned long long)hi << 32) | lo;
-  }
-  return v;
-}
-
 // SplitMix64 (Steele, Lea and Flood 2014) as a counter-based generator:
 // output number c of the stream seeded with seed.  Restart k of a pixel draws
 // parameter q from output (pixel << 16 | k << 4 | q), top 53 bits.
@@ -60,188 +51,141 @@ __device__ __forceinline__ double restart_half(int q) {
   return h[q];
 }
 
+// Work of a wave.  A lane notes what it did in a turn as bits (EV_*), which
+// the wave counts at the top of the next turn, where all its lanes are
+// together: one register per lane instead of a counter each.
+enum : unsigned {
+  EV_PIX = 1, EV_TRIAL = 2, EV_ACC = 4, EV_PASS = 8, EV_FB = 16, EV_HESS = 32, EV_JPASS = 64,
+  EV_JNEED = 128
+};
 struct WaveCounters {
-  unsigned long long pix = 0, trial = 0, acc = 0, pass = 0, fb = 0, hess = 0, jpass = 0,
-                     jneed = 0;
+  unsigned long long pix = 0, trial = 0, acc = 0, pass = 0, fb = 0, hess = 0, jpass = 0, jneed = 0;
+  __device__ __forceinline__ void count(unsigned ev) {
+    auto n = [&](unsigned bit) __attribute__((always_inline)) {
+      return (unsigned long long)__popcll(__ballot((ev & bit) != 0u));
+    };
+    pix += n(EV_PIX);
+    trial += n(EV_TRIAL);
+    acc += n(EV_ACC);
+    pass += n(EV_PASS);
+    fb += n(EV_FB);
+    hess += n(EV_HESS);
+    jpass += n(EV_JPASS);
+    jneed += n(EV_JNEED);
+  }
 };
 
-// One synthesis pass with derivatives at Mc for the pixel's observations:
-// returns the reduced chi^2 (Eq. 1) in float64 and, when the trial is
-// accepted (fresh start, or finite and below chib), leaves the float32
-// normal equations H (55, packed) and g (10) of Mc in this lane's LDS
-// column.  NOBS = 6: dense HMI-shaped filter, all 174 row accumulators held
-// until chi^2 decides whether H and g are built.  NOBS = 0: banded filter,
-// rows folded into chi^2, H and g as they complete (H and g are built for
-// every trial, since the rows are gone once chi^2 is known).
-// keep_h: the step starts from a model near the minimum (Sect. 4.4): only g
-// is rebuilt and stored, H stays as it is in LDS.
-// One pass of the dense layout over windowed records: the same chi^2 and
-// normal equations as lm_pass, from five register slots and the row parked
-// in LDS.  After the pass every row is folded into chi^2, g (registers) and
-// H (the lane's LDS slots, 14 float4, read and written once per row), for
-// every lane: some lane of the wave accepts in practically every pass, so
-// the wave would run the fold anyway, and with H out of the registers the
-// fold needs no more of them than the point loop.  Accepted lanes then copy
-// H and g to the parking area.
-template <int NOBS, int V>
-__device__ __forceinline__ double lm_pass_win(const LMArgs& A, const Pix& px, const RowFactors& rf,
-                                              int64_t pix, bool fresh, double chib, bool keep_h,
-                                              float* sHG, float4* sHa, int lane, bool& accept) {
-  constexpr int ROWS = 4 * NOBS;
-  const float* obs = A.stokes + pix * ROWS;
-  const float* Wp = A.W_pp ? A.W + pix * ROWS : A.W;
-  float4* park = sHa + H4 * 64;
-  float acc[5][NACC];
-  synth_accumulate_win<V>(A.pts5, px, A.C, acc, park, lane);
-  double chi = 0.0;
-  float g[NPAR];
+// A lane's column in LDS: the normal equations H (55, packed) and g (10) of
+// its best model, the model itself, the pass's model and, in the fixed-
+// iteration scheme of dense pixels, the best model seen: what is not read
+// inside a pass takes no registers through it.
+constexpr int HG_MB = 65, HG_MC = HG_MB + NPAR, HG_MG = HG_MC + NPAR;
+constexpr int HG_CHI = HG_MG + NPAR + 1;  // (float64 rows) its chi^2 and the first chi^2
+constexpr int HG_ROWS = HG_MG, HG_ROWS_PAPER = HG_CHI + 4;
+static_assert(HG_CHI % 2 == 0, "float64 rows");
+
+// The lane's model of a pass, read again wherever it is asked for.
+__device__ __forceinline__ void load_model(const float* Mc, float* M) {
+  asm volatile("" ::: "memory");
 #pragma unroll
-  for (int e = 0; e < NPAR; ++e) g[e] = 0.f;
-  if (!keep_h) {
-#pragma unroll
-    for (int c = 0; c < H4; ++c) sHa[c * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  auto fold = [&](const float* a, int q) {
-    const int i = A.C.slot_row[q];
-    float S[4], J[4][NPAR], WJ[4][NPAR];
-    assemble_sample<true>(a, A.C.slot_rs[q], rf, S, J);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const float w = Wp[s * NOBS + i];
-      const float r = obs[s * NOBS + i] - S[s];
-      chi = fma((double)w * (double)r, (double)r, chi);
-#pragma unroll
-      for (int p = 0; p < NPAR; ++p) {
-        WJ[s][p] = w * J[s][p];
-        if (!jzero(s, p)) g[p] = fmaf(WJ[s][p], r, g[p]);
-      }
-    }
-    if (!keep_h) {
-      lds_rmw4<0, H4>(sHa, lane, [&](auto cc, float4& h) __attribute__((always_inline)) {
-        float* hv = &h.x;
-        static_for<4>([&](auto kk) __attribute__((always_inline)) {
-          constexpr int k = decltype(kk)::value, e = 4 * decltype(cc)::value + k;
-          if constexpr (e < 55) {
-            constexpr int p = pk_row(e), q2 = pk_col(e);
-            static_for<4>([&](auto ss) __attribute__((always_inline)) {
-              constexpr int s = decltype(ss)::value;
-              if constexpr (!hzero(s, e)) hv[k] = fmaf(WJ[s][p], J[s][q2], hv[k]);
-            });
-          }
-        });
-      });
-    }
-  };
-#pragma unroll
-  for (int q = 0; q < 5; ++q) fold(acc[q], q);
-  {
-    float a[NACC];
-    unpark(park, lane, a);
-    fold(a, 5);
-  }
-  chi *= A.inv_dof;
-  accept = fresh || (isfinite(chi) && chi < chib);
-  if (accept) {
-    if (!keep_h) {
-#pragma unroll
-      for (int c = 0; c < H4; ++c) {
-        const float4 h = sHa[c * 64 + lane];
-        const float hv[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (4 * c + k < 55) sHG[(4 * c + k) * 64 + lane] = hv[k];
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < NPAR; ++e) sHG[(55 + e) * 64 + lane] = g[e];
-  }
-  return chi;
+  for (int q = 0; q < NPAR; ++q) M[q] = Mc[64 * q];
 }
 
-template <int NOBS, int LPP, int V>
-__device__ __forceinline__ double lm_pass(const LMArgs& A, const float* Mc, int64_t pix,
+// One synthesis pass with derivatives at Mc for the pixel's observations:
+// returns the reduced chi^2 (Eq. 1) in float64 and, when the lane takes part
+// and its trial is accepted (fresh start, or finite and below chib), leaves
+// the float32 normal equations H (55, packed) and g (10) of Mc in this lane's
+// LDS column.  Every lane of the wave runs it (rows4), those that take no part
+// with the model they have.  H and g are built for every trial: some lane of a
+// wave accepts in practically every pass.
+// NOBS = 6: dense HMI-shaped filter, all row sums in accumulation registers;
+// the rows are then folded one by one into chi^2, g (registers) and H (the
+// lane's LDS slots: registers for it would have to come from the rest of the
+// fold).  NOBS = 0: banded filter, rows folded into chi^2, H and g (LDS) as
+// they complete.
+// keep_h: the step starts from a model near the minimum (Sect. 4.4): only g
+// is rebuilt and stored, H stays as it is in LDS.
+template <int NOBS, int LPP, int V, bool APART>
+__device__ __forceinline__ double lm_pass(const LMArgs& A, const float* Mc, int64_t pix, bool part,
                                           bool fresh, double chib, bool keep_h, float* sHG,
                                           float4* sHa, int lane, bool& accept) {
   Pix px;
-  pix_setup(Mc, A.C, px);
+  float M[NPAR];
+  load_model(Mc, M);
+  pix_setup(M, A.C, px);
   RowFactors rf;
-  row_factors(Mc, px, A.C, rf);
   double chi = 0.0;
-  if constexpr (NOBS > 0 && LPP == 1) {
-    if (A.C.sw_k >= 0) return lm_pass_win<NOBS, V>(A, px, rf, pix, fresh, chib, keep_h, sHG, sHa,
-                                                   lane, accept);
-  }
   if constexpr (NOBS > 0) {
     constexpr int ROWS = 4 * NOBS;
     const float* obs = A.stokes + pix * ROWS;
     const float* Wp = A.W_pp ? A.W + pix * ROWS : A.W;
-    float acc[NOBS][NACC];
-    if constexpr (LPP == 2)
-      synth_accumulate_pair<NOBS, V>(A.pts, px, A.C, acc, lane & 1);
-    else
-      synth_accumulate<NOBS, true, V>(A.pts, px, A.C, acc);
+    const bool slots = LPP == 1 && A.C.sw_k >= 0;
+    f32x4 ra[NACC], rb[NACC];
+    dense_rows<LPP, V, true, APART>(LPP == 1 ? A.rows : A.rows_nat, px, A.C, lane, ra, rb);
+    load_model(Mc, M);
+    row_factors(M, px, A.C, rf);
+    float g[NPAR];
 #pragma unroll
-    for (int i = 0; i < NOBS; ++i) {
-      float S[4], J[4][NPAR];
-      assemble_sample<false>(acc[i], A.C.row_sum[i], rf, S, J);
+    for (int e = 0; e < NPAR; ++e) g[e] = 0.f;
+    if (!keep_h) {
+#pragma unroll
+      for (int c = 0; c < H4; ++c) sHa[c * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    static_for<NOBS>([&](auto qq) __attribute__((always_inline)) {
+      constexpr int q = decltype(qq)::value;
+      // one row at a time in registers
+      __builtin_amdgcn_sched_barrier(0);
+      const int i = slots ? A.C.slot_row[q] : q;
+      float a[NACC];
+#pragma unroll
+      for (int m = 0; m < NACC; ++m) a[m] = SLOT_GROUP[q] == 0 ? ra[m][SLOT_ROW[q]] : rb[m][SLOT_ROW[q]];
+      float S[4], J[4][NPAR], WJ[4][NPAR];
+      assemble_sample<true>(a, slots ? A.C.slot_rs[q] : A.C.row_sum[q], rf, S, J);
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
+        const float w = Wp[s * NOBS + i];
         const float r = obs[s * NOBS + i] - S[s];
-        chi = fma((double)Wp[s * NOBS + i] * (double)r, (double)r, chi);
-      }
-    }
-    chi *= A.inv_dof;
-    accept = fresh || (isfinite(chi) && chi < chib);
-    if (accept && !keep_h) {
-      float H[55], g[NPAR];
+        chi = fma((double)w * (double)r, (double)r, chi);
 #pragma unroll
-      for (int e = 0; e < 55; ++e) H[e] = 0.f;
-#pragma unroll
-      for (int e = 0; e < NPAR; ++e) g[e] = 0.f;
-#pragma unroll
-      for (int i = 0; i < NOBS; ++i) {
-        float S[4], J[4][NPAR];
-        assemble_sample<true>(acc[i], A.C.row_sum[i], rf, S, J);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const float w = Wp[s * NOBS + i];
-          const float r = obs[s * NOBS + i] - S[s];
-#pragma unroll
-          for (int p = 0; p < NPAR; ++p) {
-            const float wj = w * J[s][p];
-            if (jzero(s, p)) continue;
-            g[p] = fmaf(wj, r, g[p]);
-#pragma unroll
-            for (int q = 0; q <= p; ++q)
-              if (!jzero(s, q)) H[pk(p, q)] = fmaf(wj, J[s][q], H[pk(p, q)]);
-          }
+        for (int p = 0; p < NPAR; ++p) {
+          WJ[s][p] = w * J[s][p];
+          if (!jzero(s, p)) g[p] = fmaf(WJ[s][p], r, g[p]);
         }
       }
+      if (!keep_h) {
+        lds_rmw4<0, H4>(sHa, lane, [&](auto cc, float4& h) __attribute__((always_inline)) {
+          float* hv = &h.x;
+          static_for<4>([&](auto kk) __attribute__((always_inline)) {
+            constexpr int k = decltype(kk)::value, e = 4 * decltype(cc)::value + k;
+            if constexpr (e < 55) {
+              constexpr int p = pk_row(e), q2 = pk_col(e);
+              static_for<4>([&](auto ss) __attribute__((always_inline)) {
+                constexpr int s = decltype(ss)::value;
+                if constexpr (!hzero(s, e)) hv[k] = fmaf(WJ[s][p], J[s][q2], hv[k]);
+              });
+            }
+          });
+        });
+      }
+    });
+    chi = rounded(chi * A.inv_dof);
+    accept = part && (fresh || (isfinite(chi) && chi < chib));
+    if (accept) {
+      if (!keep_h) {
 #pragma unroll
-      for (int e = 0; e < 55; ++e) sHG[e * 64 + lane] = H[e];
+        for (int c = 0; c < H4; ++c) {
+          const float4 h = sHa[c * 64 + lane];
+          const float hv[4] = {h.x, h.y, h.z, h.w};
 #pragma unroll
-      for (int e = 0; e < NPAR; ++e) sHG[(55 + e) * 64 + lane] = g[e];
-    } else if (accept) {  // H kept: the gradient alone
-      float g[NPAR];
-#pragma unroll
-      for (int e = 0; e < NPAR; ++e) g[e] = 0.f;
-#pragma unroll
-      for (int i = 0; i < NOBS; ++i) {
-        float S[4], J[4][NPAR];
-        assemble_sample<true>(acc[i], A.C.row_sum[i], rf, S, J);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const float w = Wp[s * NOBS + i];
-          const float r = obs[s * NOBS + i] - S[s];
-#pragma unroll
-          for (int p = 0; p < NPAR; ++p)
-            if (!jzero(s, p)) g[p] = fmaf(w * J[s][p], r, g[p]);
+          for (int k = 0; k < 4; ++k)
+            if (4 * c + k < 55) sHG[(4 * c + k) * 64 + lane] = hv[k];
         }
       }
 #pragma unroll
       for (int e = 0; e < NPAR; ++e) sHG[(55 + e) * 64 + lane] = g[e];
     }
   } else {
+    row_factors(M, px, A.C, rf);
     const int no = A.C.n_obs;
     const float* obs = A.stokes + pix * (int64_t)(4 * no);
     const float* Wp = A.W_pp ? A.W + pix * (int64_t)(4 * no) : A.W;
@@ -309,8 +253,8 @@ __device__ __forceinline__ double lm_pass(const LMArgs& A, const float* Mc, int6
               upd(cc, h, std::false_type{});
             });
         });
-    chi *= A.inv_dof;
-    accept = fresh || (isfinite(chi) && chi < chib);
+    chi = rounded(chi * A.inv_dof);
+    accept = part && (fresh || (isfinite(chi) && chi < chib));
     if (accept) {
 #pragma unroll
       for (int c = 0; c < HG4; ++c) {
@@ -330,40 +274,42 @@ __device__ __forceinline__ double lm_pass(const LMArgs& A, const float* Mc, int6
 
 // One synthesis pass without derivatives at Mc: the reduced chi^2 (Eq. 1)
 // in float64 of a trial.  Every row receives the same products in the same
-// order as in lm_pass, and the rows enter chi^2 in lm_pass's order (the
-// windowed pass folds its register slots first and the parked row last;
-// ptsv holds the rows in that order), so a model gets the same chi^2 from
-// either pass.
-template <int NOBS, int LPP, int V>
+// order as in lm_pass, and the rows enter chi^2 in lm_pass's order, so a model
+// gets the same chi^2 from either pass.  Every lane runs it, as lm_pass.
+template <int NOBS, int LPP, int V, bool APART>
 __device__ __forceinline__ double lm_pass_values(const LMArgs& A, const float* Mc, int64_t pix,
                                                  int lane) {
   Pix px;
-  pix_setup(Mc, A.C, px);
+  float M[NPAR];
+  load_model(Mc, M);
+  pix_setup(M, A.C, px);
   RowFactors rf;
-  row_factors(Mc, px, A.C, rf);
   double chi = 0.0;
   if constexpr (NOBS > 0) {
     constexpr int ROWS = 4 * NOBS;
     const float* obs = A.stokes + pix * ROWS;
     const float* Wp = A.W_pp ? A.W + pix * ROWS : A.W;
-    const bool win = LPP == 1 && A.C.sw_k >= 0;
-    float acc[NOBS][NACC];
-    if constexpr (LPP == 2)
-      synth_accumulate_pair<NOBS, V, false>(A.pts, px, A.C, acc, lane & 1);
-    else
-      synth_accumulate<NOBS, false, V>(win ? A.ptsv : A.pts, px, A.C, acc);
+    const bool slots = LPP == 1 && A.C.sw_k >= 0;
+    f32x4 ra[5], rb[5];
+    dense_rows<LPP, V, false, APART>(LPP == 1 ? A.rows : A.rows_nat, px, A.C, lane, ra, rb);
+    load_model(Mc, M);
+    row_factors(M, px, A.C, rf);
+    static_for<NOBS>([&](auto qq) __attribute__((always_inline)) {
+      constexpr int q = decltype(qq)::value;
+      const int i = slots ? A.C.slot_row[q] : q;
+      float a[5];
 #pragma unroll
-    for (int q = 0; q < NOBS; ++q) {
-      const int i = win ? A.C.slot_row[q] : q;
+      for (int m = 0; m < 5; ++m) a[m] = SLOT_GROUP[q] == 0 ? ra[m][SLOT_ROW[q]] : rb[m][SLOT_ROW[q]];
       float S[4], J[4][NPAR];
-      assemble_sample<false>(acc[q], win ? A.C.slot_rs[q] : A.C.row_sum[q], rf, S, J);
+      assemble_sample<false>(a, slots ? A.C.slot_rs[q] : A.C.row_sum[q], rf, S, J);
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const float r = obs[s * NOBS + i] - S[s];
         chi = fma((double)Wp[s * NOBS + i] * (double)r, (double)r, chi);
       }
-    }
+    });
   } else {
+    row_factors(M, px, A.C, rf);
     const int no = A.C.n_obs;
     const float* obs = A.stokes + pix * (int64_t)(4 * no);
     const float* Wp = A.W_pp ? A.W + pix * (int64_t)(4 * no) : A.W;
@@ -395,27 +341,28 @@ __device__ __forceinline__ double lm_pass_values(const LMArgs& A, const float* M
           }
         });
   }
-  return chi * A.inv_dof;
+  return rounded(chi * A.inv_dof);
 }
 
 // The persistent LM loop of one wave over one batch: lanes take pixels
 // from the batch's queues, fit them, and return when the queues are empty
 // and every lane has finished.
-// LPP = 2 (dense only): a pair of lanes carries one pixel; the even lane is
-// the pair's leader (it takes queue positions, writes the results and counts
-// the work), the odd lane mirrors its state: both see the same inputs and
-// the same pair sums, so they take the same decisions.
+// LPP = 2 (dense only): a pair of lanes (lane and lane ^ 4) carries one pixel;
+// the lower one is the pair's leader (it takes queue positions, writes the
+// results and counts the work), the other mirrors its state: both see the
+// same inputs and the same pair sums, so they take the same decisions.
 // PAPER: the fixed-iteration scheme of Sect. 4.2 (A.fixed_iters trials per
 // pixel, restarts from a perturbed best model, the best model seen is the
 // result); otherwise exits on convergence, stall or A.max_iter.
-template <int NOBS, int LPP, int V = 0, bool PAPER = false, bool SPLIT = false>
+template <int NOBS, int LPP, int V = 0, bool PAPER = false, bool SPLIT = false,
+          bool APART = false>
 __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa, double* sws,
                                         int lane,
                                         int64_t glane,
                                         WaveCounters& wc) {
   static_assert(LPP == 1 || (LPP == 2 && NOBS > 0), "lane pairs serve the dense layout");
-  const bool leader = LPP == 1 || (lane & 1) == 0;
-  const int mate = lane & ~(LPP - 1);
+  const bool leader = LPP == 1 || (lane & 4) == 0;
+  const int mate = LPP == 1 ? lane : lane & ~4;
   const unsigned long long n_total = A.n_dev ? *A.n_dev : (unsigned long long)A.n;
   const int rows = NOBS > 0 ? 4 * NOBS : 4 * A.C.n_obs;
   // Pixel queues: queue q owns the blocks b of 2^chunk_log2 consecutive
@@ -431,13 +378,23 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
   unsigned dry = 0u;  // queues this wave has seen empty (wave-uniform)
   bool live = false, fresh = false, exhausted = false;
   int64_t pix = 0;
-  float Mb[NPAR], Mc[NPAR];
+  // best model and model of the next pass, element q at [64 q]
+  float* Mb = sHG + HG_MB * 64 + lane;
+  float* Mc = sHG + HG_MC * 64 + lane;
+#pragma unroll
+  for (int q = 0; q < NPAR; ++q) Mb[64 * q] = Mc[64 * q] = 0.f;
   double chib = 0.0, eps = 0.0;
   int it = 0;
-  // fixed-iteration scheme: best model seen, first chi^2, failed trials in
+  // fixed-iteration scheme: best model seen (banded pixels have no LDS left
+  // for it) and its chi^2, first chi^2, failed trials in
   // a row, restarts used, restart due / being evaluated
-  float Mg[NPAR];
-  double chig = 0.0, chi_first = 0.0;
+  float mg[NOBS > 0 ? 1 : NPAR];
+  constexpr int MG = NOBS > 0 ? 64 : 1;
+  float* Mg = NOBS > 0 ? sHG + HG_MG * 64 + lane : mg;
+  double cg[NOBS > 0 && PAPER ? 1 : 2];
+  double* const cgs = NOBS > 0 && PAPER ? reinterpret_cast<double*>(sHG + HG_CHI * 64) + lane : cg;
+  double &chig = cgs[0], &chi_first = cgs[NOBS > 0 && PAPER ? 64 : 1];
+  chig = chi_first = 0.0;
   int bad = 0, kr = 0;
   bool pending = false, restart_eval = false;
   // the damped solve needs the eigen fallback: done with the whole wave at
@@ -452,7 +409,10 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
   // in the fixed-iteration scheme, whose restarts are fresh starts)
   static_assert(!(SPLIT && PAPER), "the fixed-iteration scheme fuses its passes");
 
+  unsigned ev = 0u;
   for (;;) {
+    wc.count(ev);
+    ev = 0u;
     // ---- refill lanes whose pixel finished --------------------------------
     unsigned long long nm = __ballot(!live && !exhausted && leader);
     for (int j = 0; j < NQ && nm != 0ull; ++j) {
@@ -472,7 +432,7 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
       const bool take = need && rank < got;
       unsigned long long k = k0 + rank;
       bool mine = take;
-      if constexpr (LPP == 2) {  // the odd lane follows its leader
+      if constexpr (LPP == 2) {  // the mate follows its leader
         mine = __shfl(take ? 1 : 0, mate) != 0;
         const unsigned lo = __shfl((unsigned)(k & 0xffffffffull), mate);
         const unsigned hi = __shfl((unsigned)(k >> 32), mate);
@@ -497,7 +457,7 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
           }
           project(M0);
 #pragma unroll
-          for (int q2 = 0; q2 < NPAR; ++q2) Mc[q2] = (float)M0[q2];
+          for (int q2 = 0; q2 < NPAR; ++q2) Mc[64 * q2] = (float)M0[q2];
           live = true;
           fresh = true;
           eps = A.eps0;
@@ -519,13 +479,13 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
       solve_eigen_wave(&sHG[L], 64, &sHG[55 * 64 + L], 64, __shfl(eps, L), A.free_mask, sws,
                        lane);
       if (lane == L) {
-        if (leader) ++wc.fb;
+        if (leader) ev |= EV_FB;
         double Mt[NPAR];
 #pragma unroll
-        for (int q = 0; q < NPAR; ++q) Mt[q] = (double)Mb[q] + sws[200 + q];
+        for (int q = 0; q < NPAR; ++q) Mt[q] = (double)Mb[64 * q] + sws[200 + q];
         project(Mt);
 #pragma unroll
-        for (int q = 0; q < NPAR; ++q) Mc[q] = (float)Mt[q];
+        for (int q = 0; q < NPAR; ++q) Mc[64 * q] = (float)Mt[q];
         need_fb = false;
       }
       __syncthreads();  // lane L has read the step before the record is reused
@@ -545,24 +505,23 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
       const int nw = __popcll(__ballot(live && wait)), nl = __popcll(live_m);
       jpass = nw == nl || nw * 64 >= A.deriv_split * nl;
     }
-    if (!live || (!jpass && wait)) continue;
-
-    if (leader) {
-      ++wc.pass;
-      if (jpass) ++wc.jpass;
-    }
+    // (the passes run on every lane of the wave: its row sums are matrix
+    // instructions, which take the taps from all lanes)
+    const bool part = live && (jpass || !wait);
     bool accept = false;
     // Sect. 4.4: a step from a model already near the minimum keeps H
     const bool keep_h = need_j ? kh_wait : (!fresh && chib < A.hess_reuse);
     double chi;
-    bool hess_counted = false;
     if (!SPLIT || jpass) {
-      chi = lm_pass<NOBS, LPP, V>(A, Mc, pix, wait, chib, keep_h, sHG, sHa, lane, accept);
-      hess_counted = leader && accept && !keep_h;
-      if (hess_counted) ++wc.hess;
+      chi = lm_pass<NOBS, LPP, V, APART>(A, Mc, pix, part, wait, chib, keep_h, sHG, sHa, lane, accept);
+      if (leader && accept && !keep_h) ev |= EV_HESS;
     } else {
-      chi = lm_pass_values<NOBS, LPP, V>(A, Mc, pix, lane);
-      accept = isfinite(chi) && chi < chib;
+      chi = lm_pass_values<NOBS, LPP, V, APART>(A, Mc, pix, lane);
+      accept = part && isfinite(chi) && chi < chib;
+    }
+    if (!part) continue;
+    if (leader) {
+      ev |= jpass ? EV_PASS | EV_JPASS : EV_PASS;
     }
 
     // ---- Levenberg-Marquardt bookkeeping (Sect. 4.2, Table 2) -------------
@@ -584,22 +543,18 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
         const float* obs = A.stokes + pix * rows;
         const float* Wp = A.W_pp ? A.W + pix * rows : A.W;
         for (int r = 0; r < rows; ++r) bad_input = bad_input || !isfinite(obs[r]) || !isfinite(Wp[r]);
-        if (bad_input && leader) {
-          --wc.pass;
-          if (jpass) --wc.jpass;
-          if (hess_counted) --wc.hess;
-        }
+        if (bad_input) ev &= ~(EV_PASS | EV_JPASS | EV_HESS);
       }
 #pragma unroll
-      for (int q = 0; q < NPAR; ++q) Mb[q] = Mc[q];
+      for (int q = 0; q < NPAR; ++q) Mb[64 * q] = Mc[64 * q];
       chib = chi;
       if constexpr (PAPER) {
         if (restart_eval) {  // the restart's evaluation is a trial
           ++it;
-          if (leader) ++wc.trial;
+          if (leader) ev |= EV_TRIAL;
           if (isfinite(chi) && chi < chig) {
 #pragma unroll
-            for (int q = 0; q < NPAR; ++q) Mg[q] = Mc[q];
+            for (int q = 0; q < NPAR; ++q) Mg[MG * q] = Mc[64 * q];
             chig = chi;
           }
           bad = 0;
@@ -608,12 +563,12 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
           chi_first = chi;
           chig = chi;
 #pragma unroll
-          for (int q = 0; q < NPAR; ++q) Mg[q] = Mc[q];
+          for (int q = 0; q < NPAR; ++q) Mg[MG * q] = Mc[64 * q];
         }
       }
     } else {
       ++it;
-      if (leader) ++wc.trial;
+      if (leader) ev |= EV_TRIAL;
       if (accept) {
         const double dec = chib - chi;
         // values-only pass: the derivatives of the new best model are due
@@ -621,15 +576,15 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
         need_j = !jpass;
         kh_wait = chib < A.hess_reuse;
 #pragma unroll
-        for (int q = 0; q < NPAR; ++q) Mb[q] = Mc[q];
+        for (int q = 0; q < NPAR; ++q) Mb[64 * q] = Mc[64 * q];
         chib = chi;
         eps = eps_down(eps);
-        if (leader) ++wc.acc;
+        if (leader) ev |= EV_ACC;
         if constexpr (PAPER) {
           bad = 0;
           if (chi < chig) {
 #pragma unroll
-            for (int q = 0; q < NPAR; ++q) Mg[q] = Mc[q];
+            for (int q = 0; q < NPAR; ++q) Mg[MG * q] = Mc[64 * q];
             chig = chi;
           }
         } else {
@@ -653,7 +608,7 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
     fresh = false;
     if (done < 0 && it >= limit) done = 1;
     if (done >= 0) need_j = false;
-    if (leader && new_best && done < 0) ++wc.jneed;
+    if (leader && new_best && done < 0) ev |= EV_JNEED;
 
     if (done >= 0) {
       if (leader) {
@@ -665,12 +620,12 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
           if (A.status) A.status[pix] = 3;
         } else {
 #pragma unroll
-          for (int q = 0; q < NPAR; ++q) A.params[pix * NPAR + q] = PAPER ? Mg[q] : Mb[q];
+          for (int q = 0; q < NPAR; ++q) A.params[pix * NPAR + q] = PAPER ? Mg[MG * q] : Mb[64 * q];
           A.chi2[pix] = PAPER ? chig : chib;
           A.iters[pix] = it;
           if (A.status) A.status[pix] = PAPER ? (done | (kr << 8)) : done;
         }
-        ++wc.pix;
+        ev |= EV_PIX;
       }
       live = false;
     } else if (PAPER && pending) {
@@ -681,12 +636,12 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
       for (int q = 0; q < NPAR; ++q) {
         const double u = restart_uniform(A.seed, pix, kr, q);
         Mt[q] = ((A.free_mask >> q) & 1u)
-                    ? (double)Mg[q] + (2.0 * u - 1.0) * 0.1 * kr * restart_half(q)
-                    : (double)Mg[q];
+                    ? (double)Mg[MG * q] + (2.0 * u - 1.0) * 0.1 * kr * restart_half(q)
+                    : (double)Mg[MG * q];
       }
       project(Mt);
 #pragma unroll
-      for (int q = 0; q < NPAR; ++q) Mc[q] = (float)Mt[q];
+      for (int q = 0; q < NPAR; ++q) Mc[64 * q] = (float)Mt[q];
       fresh = true;
       restart_eval = true;
       pending = false;
@@ -707,10 +662,10 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
       } else {
         double Mt[NPAR];
 #pragma unroll
-        for (int q = 0; q < NPAR; ++q) Mt[q] = (double)Mb[q] + delta[q];
+        for (int q = 0; q < NPAR; ++q) Mt[q] = (double)Mb[64 * q] + delta[q];
         project(Mt);
 #pragma unroll
-        for (int q = 0; q < NPAR; ++q) Mc[q] = (float)Mt[q];
+        for (int q = 0; q < NPAR; ++q) Mc[64 * q] = (float)Mt[q];
       }
     }
   }
@@ -719,44 +674,41 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
 // ---- work counters: one atomic per wave and counter ----------------------
 __device__ __forceinline__ void flush_counters(unsigned long long* work, WaveCounters wc,
                                                int lane) {
-  const unsigned long long p = wave_sum(wc.pix), t = wave_sum(wc.trial), a = wave_sum(wc.acc),
-                           s = wave_sum(wc.pass), f = wave_sum(wc.fb),
-                           h = wave_sum(wc.hess), j = wave_sum(wc.jpass),
-                           jn = wave_sum(wc.jneed);
   if (lane == 0) {
-    atomicAdd(&work[0], j);
-    atomicAdd(&work[8], jn);
-    atomicAdd(&work[1], p);
-    atomicAdd(&work[2], t);
-    atomicAdd(&work[3], a);
-    atomicAdd(&work[4], s);
-    atomicAdd(&work[5], f);
+    atomicAdd(&work[0], wc.jpass);
+    atomicAdd(&work[8], wc.jneed);
+    atomicAdd(&work[1], wc.pix);
+    atomicAdd(&work[2], wc.trial);
+    atomicAdd(&work[3], wc.acc);
+    atomicAdd(&work[4], wc.pass);
+    atomicAdd(&work[5], wc.fb);
     atomicAdd(&work[6], 1ull);
-    atomicAdd(&work[7], h);
+    atomicAdd(&work[7], wc.hess);
   }
 }
 
 // V: Voigt evaluation (0 Weideman's series, 1/2 Taylor table; dense only).
 // SPLIT: values-only trial passes with derivative passes on demand (a
 // separate kernel, so that the fused one keeps its own register allocation).
-template <int NOBS, int V, bool PAPER, bool SPLIT = false>
+// LPP: lanes per pixel.  A launch that may use pairs serves a batch of up to
+// pair_max pixels with two lanes each and a larger one with one lane; where
+// only the device knows the count, both kernels are launched and one of them
+// ends at once.
+template <int NOBS, int LPP, int V, bool PAPER, bool SPLIT = false>
 __global__ __launch_bounds__(64) void lm_kernel(const LMArgs A) {
-  __shared__ float sHG[65 * 64];  // H (55, packed) and g (10) per lane
-  __shared__ float4 sHa[PASS4 * 64];  // the pass's accumulators in LDS
-  double* sws = ws_record(sHa);       // the wave's eigen-fallback record
+  __shared__ __align__(16) float sHG[(PAPER && NOBS > 0 ? HG_ROWS_PAPER : HG_ROWS) * 64];
+  // the pass's H (banded: and g), and the wave's eigen-fallback record
+  __shared__ float4 sHa[(NOBS > 0 ? H4 : HG4) * 64];
+  double* sws = ws_record(sHa);
   const int lane = threadIdx.x;
   const int64_t glane = (int64_t)blockIdx.x * 64 + lane;
-  WaveCounters wc;
   if constexpr (NOBS > 0) {
     const unsigned long long n_total = A.n_dev ? *A.n_dev : (unsigned long long)A.n;
-    // pairs only for batches small enough (host's choice, pair_max)
-    if (A.lpp_max >= 2 && n_total <= (unsigned long long)A.pair_max)
-      lm_loop<NOBS, 2, V, PAPER, SPLIT>(A, sHG, sHa, sws, lane, glane, wc);
-    else
-      lm_loop<NOBS, 1, V, PAPER, SPLIT>(A, sHG, sHa, sws, lane, glane, wc);
-  } else {
-    lm_loop<NOBS, 1, V, PAPER, SPLIT>(A, sHG, sHa, sws, lane, glane, wc);
+    const bool pairs = A.lpp_max >= 2 && n_total <= (unsigned long long)A.pair_max;
+    if (pairs != (LPP == 2)) return;
   }
+  WaveCounters wc;
+  lm_loop<NOBS, LPP, V, PAPER, SPLIT, V == 0 && !PAPER>(A, sHG, sHa, sws, lane, glane, wc);
   flush_counters(A.work, wc, lane);
 }
 
@@ -766,8 +718,8 @@ __global__ __launch_bounds__(64) void lm_kernel(const LMArgs A) {
 // the earlier ones.
 template <bool SPLIT>
 __global__ __launch_bounds__(64) void lm_batches_kernel(const BatchArgs B) {
-  __shared__ float sHG[65 * 64];
-  __shared__ float4 sHa[PASS4 * 64];
+  __shared__ float sHG[HG_ROWS * 64];
+  __shared__ float4 sHa[HG4 * 64];
   double* sws = ws_record(sHa);
   const int lane = threadIdx.x;
   const int64_t glane = (int64_t)blockIdx.x * 64 + lane;
@@ -920,21 +872,30 @@ hipError_t launch_reset(unsigned long long* work, bool all, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int LPP, bool PAPER>
+static void launch_lm_dense(const LMArgs& a, int voigt, bool split, int grid, hipStream_t s) {
+  if (voigt == 1) {
+    lm_kernel<NOBS_HMI, LPP, 1, PAPER><<<grid, 64, 0, s>>>(a);
+  } else if (voigt == 2) {
+    lm_kernel<NOBS_HMI, LPP, 2, PAPER><<<grid, 64, 0, s>>>(a);
+  } else {
+    if (split) lm_kernel<NOBS_HMI, LPP, 0, false, true><<<grid, 64, 0, s>>>(a);
+    else lm_kernel<NOBS_HMI, LPP, 0, PAPER><<<grid, 64, 0, s>>>(a);
+  }
+}
+
 template <bool PAPER>
 static void launch_lm_mode(const LMArgs& a, int kind, int voigt, int grid, hipStream_t s) {
   // the split pass serves Weideman's series outside the fixed-iteration scheme
   const bool split = !PAPER && voigt == 0 && a.deriv_split > 0;
   if (kind != KIND_DENSE6) {
-    if (split) lm_kernel<0, 0, false, true><<<grid, 64, 0, s>>>(a);
-    else lm_kernel<0, 0, PAPER><<<grid, 64, 0, s>>>(a);
-  } else if (voigt == 1) {
-    lm_kernel<NOBS_HMI, 1, PAPER><<<grid, 64, 0, s>>>(a);
-  } else if (voigt == 2) {
-    lm_kernel<NOBS_HMI, 2, PAPER><<<grid, 64, 0, s>>>(a);
-  } else {
-    if (split) lm_kernel<NOBS_HMI, 0, false, true><<<grid, 64, 0, s>>>(a);
-    else lm_kernel<NOBS_HMI, 0, PAPER><<<grid, 64, 0, s>>>(a);
+    if (split) lm_kernel<0, 1, 0, false, true><<<grid, 64, 0, s>>>(a);
+    else lm_kernel<0, 1, 0, PAPER><<<grid, 64, 0, s>>>(a);
+    return;
   }
+  const bool may = a.lpp_max >= 2;
+  if (may && (a.n_dev || a.n <= a.pair_max)) launch_lm_dense<2, PAPER>(a, voigt, split, grid, s);
+  if (!may || a.n_dev || a.n > a.pair_max) launch_lm_dense<1, PAPER>(a, voigt, split, grid, s);
 }
 
 hipError_t launch_lm(const LMArgs& a, int kind, int voigt, int grid, hipStream_t s) {
@@ -1003,7 +964,7 @@ hipError_t launch_interleave(const float* in, float4* out, int64_t n, int n_obs,
 }
 
 hipError_t lm_blocks_per_cu(int* out) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(out, lm_kernel<NOBS_HMI, 0, false>, 64, 0);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(out, lm_kernel<NOBS_HMI, 1, 0, false>, 64, 0);
 }
 
 hipError_t band_blocks_per_cu(int* out) {

@@ -50,7 +50,7 @@ constexpr double DEG_D = 0.017453292519943295769;
 constexpr double C_KMS = 299792.458;
 
 // Wave-uniform constants of one launch (kernel argument -> SGPRs).
-constexpr int OV_MAX = 4;  // records shared by the two rows of the register slot 4
+constexpr int OV_MAX = 4;  // most records shared by the first row to end and the last to start
 
 struct Consts {
   float wc[NW + 1];      // 2 * a_n, n = 1..NW (index 0 unused)
@@ -60,11 +60,10 @@ struct Consts {
   int n_pts;             // synthesis points with a non-zero tap
   int n_obs;
   float row_sum[8];      // sum of the kept taps of each filter row
-  // Dense layout, windowed records (slot order): from record sw_k on, the
-  // register slot 4 takes a row that starts there, and the row it held
-  // (one that ends within OV_MAX records) is parked in LDS; -1 when the
-  // filter has no such pair of rows.  slot_row / slot_rs: filter row and row
-  // sum of each slot (slot 5: the parked row).
+  // Dense layout, order of the rows in chi^2 and the normal equations: with
+  // sw_k >= 0 the rows in slot order (slot_row and slot_rs: filter row and row
+  // sum of each slot; slot 5 the first row to end, slot 4 the last to start),
+  // else the filter's own order.
   int sw_k;
   int slot_row[6];
   float slot_rs[6];
@@ -72,13 +71,18 @@ struct Consts {
 };
 
 // One synthesis point: offset and the taps of the (up to 6) filter rows;
-// w[6] carries the bit mask of rows with a non-zero tap.  32 bytes.  In the
-// windowed records w[0..4] are the taps of the five register slots and w[5]
-// the tap of the parked row.
+// w[6] carries the bit mask of rows with a non-zero tap.  32 bytes.
 struct __attribute__((aligned(32))) Point {
   float dl;
   float w[7];
 };
+
+// A value rounded where it stands: its last operation is not contracted with
+// what follows.
+__device__ __forceinline__ double rounded(double x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
@@ -443,123 +447,100 @@ __device__ __forceinline__ void lds_rmw4(float4* __restrict__ base, int lane, F&
   lds_rmw4_from<C0, C1>(base, lane, a, b, f);
 }
 
-// The dense accumulation over windowed records (Consts::sw_k >= 0, so
-// 1 <= sw_k <= n_pts - 1): five register slots instead of six rows.  At
-// record sw_k the row held by slot 4 is parked in the lane's LDS slots
-// (8 float4, lane-interleaved) and slot 4 takes the row that starts there;
-// the parked row's taps on the records it still shares with that row (mask
-// bit 5) are added in LDS.  Every row receives the same sequence of
-// products as in synth_accumulate.
-constexpr int PARK4 = (NACC + 3) / 4;  // float4 slots of a parked row
-
-__device__ __forceinline__ float4 pack4(const float* a, int c) {
-  return make_float4(a[4 * c], 4 * c + 1 < NACC ? a[4 * c + 1] : 0.f,
-                     4 * c + 2 < NACC ? a[4 * c + 2] : 0.f, 4 * c + 3 < NACC ? a[4 * c + 3] : 0.f);
+// ---- row sums on the matrix cores --------------------------------------------
+// v_mfma_f32_4x4x1_16b_f32: in each block of four lanes, D[r](lane) = A[r] *
+// B(lane) + C[r](lane), where lane l of the block supplies A[l] and its own B.
+// With the taps of four filter rows as A and a quantity of every lane's pixel
+// as B, one instruction adds the point to four row sums of that quantity in
+// every lane, with the single rounding of fmaf.  It issues like one VALU
+// instruction (four fmaf take four) and runs beside the vector ALUs, and its
+// accumulators live in the accumulation registers without moves.  It does not
+// look at the execution mask: every lane of the wave must run it, with its
+// share of A.  (HMI: 186 taps x 29 quantities, 5,400 fmaf of a pass, become
+// 2,500 instructions, and no row has to be parked in LDS: 1M pixels, plain
+// LM 44.5 -> 40.6 ms, short fits from the network's start 13.5 -> 12.6 ms.)
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+__device__ __forceinline__ f32x4 rows4(float tap, float c, f32x4 acc) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(tap, c, acc, 0, 0, 0);
 }
 
-template <int V = 0>
-__device__ __forceinline__ void synth_accumulate_win(const Point* __restrict__ pts, const Pix& p,
-                                                     const Consts& C, float (&acc)[5][NACC],
-                                                     float4* __restrict__ park, int lane) {
+// The dense layout's six rows in two groups of MFMA rows: rows 5, 0, 1, 2 and
+// rows 3, 4 of the order the launch folds them in (Consts::sw_k).
+struct DenseTaps {
+  const float2* t;   // [n_pts][4]: MFMA row r's taps in the two groups
+  const float* dl;   // [n_pts]
+  int n, a_end, b_beg;  // the first group's taps end before a_end, the second's
+                        // begin at b_beg <= a_end
+};
+constexpr int SLOT_GROUP[6] = {0, 0, 0, 1, 1, 0};
+constexpr int SLOT_ROW[6] = {1, 2, 3, 0, 1, 0};
+
+// Row sums of every quantity at the lane's model.  LPP = 2: the lanes of a
+// pair (lane and lane ^ 4, so that the lanes of a block take the same record)
+// take every other synthesis point each and then add their sums.
+// The matrix instructions of a point stand together at its end: among vector
+// instructions each cost about nine cycles more (1M HMI pixels 51 ms with
+// the point before's sums spread over the next point's arithmetic, 44.6 ms
+// like this).
+// APART: the points after the first group's last tap have a loop of their own
+// (0.8% of a pass with derivatives), where the kernel has the registers for it.
+template <int LPP, int V, bool DERIV, bool APART>
+__device__ __forceinline__ void dense_rows(const DenseTaps& T, const Pix& p, const Consts& C,
+                                           int lane, f32x4 (&ra)[DERIV ? NACC : 5],
+                                           f32x4 (&rb)[DERIV ? NACC : 5]) {
+  constexpr int NC = DERIV ? NACC : 5;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int m = 0; m < NACC; ++m) acc[i][m] = 0.f;
-  const int last = C.n_pts - 1, sw = C.sw_k;
-  // two loops, before and after the switch, so that no accumulator is
-  // redefined inside a loop
-  auto point = [&](const Point& P, bool parked) {
+  for (int m = 0; m < NC; ++m) ra[m] = rb[m] = zero;
+  const float2* t = T.t + (lane & 3);
+  auto point = [&](float dl, float2 w, auto first, auto second) __attribute__((always_inline)) {
     float c[NACC];
-    point_contrib<true, V>(P.dl, p, C, c);
-    const uint32_t mask = __float_as_uint(P.w[6]);
+    point_contrib<DERIV, V>(dl, p, C, c);
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      if (mask & (1u << i)) {
-        const float w = P.w[i];
-#pragma unroll
-        for (int m = 0; m < NACC; ++m) acc[i][m] = fmaf(w, c[m], acc[i][m]);
-      }
-    }
-    if (parked && (mask & 32u)) {
-      const float w = P.w[5];
-      lds_rmw4<0, PARK4>(park, lane, [&](auto qq, float4& t) __attribute__((always_inline)) {
-        constexpr int q = decltype(qq)::value;
-        t.x = fmaf(w, c[4 * q], t.x);
-        if constexpr (4 * q + 1 < NACC) t.y = fmaf(w, c[4 * q + 1], t.y);
-        if constexpr (4 * q + 2 < NACC) t.z = fmaf(w, c[4 * q + 2], t.z);
-        if constexpr (4 * q + 3 < NACC) t.w = fmaf(w, c[4 * q + 3], t.w);
-      });
+    for (int m = 0; m < NC; ++m) {
+      if constexpr (decltype(first)::value) ra[m] = rows4(w.x, c[m], ra[m]);
+      if constexpr (decltype(second)::value) rb[m] = rows4(w.y, c[m], rb[m]);
     }
   };
-  Point P = load_uniform(pts, 0);
-  for (int k = 0; k < sw; ++k) {
-    const Point Pn = load_uniform(pts, k + 1);  // k + 1 <= sw <= last
-    point(P, false);
-    P = Pn;
-  }
-#pragma unroll
-  for (int c = 0; c < PARK4; ++c) park[c * 64 + lane] = pack4(acc[4], c);
-#pragma unroll
-  for (int m = 0; m < NACC; ++m) acc[4][m] = 0.f;
-  for (int k = sw; k <= last; ++k) {
-    const Point Pn = load_uniform(pts, k < last ? k + 1 : last);
-    point(P, true);
-    P = Pn;
-  }
-}
-
-// The parked row back in registers.
-__device__ __forceinline__ void unpark(const float4* __restrict__ park, int lane, float* a) {
-#pragma unroll
-  for (int q = 0; q < PARK4; ++q) {
-    const float4 t = park[q * 64 + lane];
-    a[4 * q] = t.x;
-    if (4 * q + 1 < NACC) a[4 * q + 1] = t.y;
-    if (4 * q + 2 < NACC) a[4 * q + 2] = t.z;
-    if (4 * q + 3 < NACC) a[4 * q + 3] = t.w;
-  }
-}
-
-// The same accumulation shared by a pair of lanes (lane & 1 = odd): each
-// lane takes every other synthesis point (two wave-uniform records per
-// step, each lane selecting its own), then the pair adds its partial sums,
-// so both lanes hold the full sums.  Used when a launch has at least two
-// lanes per pixel: a pass then takes about half the time.
-template <int NOBS, int V = 0, bool DERIV = true>
-__device__ __forceinline__ void synth_accumulate_pair(const Point* __restrict__ pts,
-                                                      const Pix& p, const Consts& C,
-                                                      float (&acc)[NOBS][NACC], bool odd) {
-  constexpr int NC = DERIV ? NACC : 5;
-#pragma unroll
-  for (int i = 0; i < NOBS; ++i)
-#pragma unroll
-    for (int m = 0; m < NACC; ++m) acc[i][m] = 0.f;
-  for (int k = 0; k < C.n_pts; k += 2) {
-    const Point P0 = load_uniform(pts, k);
-    Point P1;
-    if (k + 1 < C.n_pts) {
-      P1 = load_uniform(pts, k + 1);
-    } else {
-      P1.dl = 0.f;
-#pragma unroll
-      for (int i = 0; i < 7; ++i) P1.w[i] = 0.f;  // taps and mask zero: contributes nothing
-    }
-    float c[NACC];
-    point_contrib<DERIV, V>(odd ? P1.dl : P0.dl, p, C, c);
-    const uint32_t mask = __float_as_uint(P0.w[6]) | __float_as_uint(P1.w[6]);
-#pragma unroll
-    for (int i = 0; i < NOBS; ++i) {
-      if (mask & (1u << i)) {  // a record's taps are zero outside its own mask
-        const float w = odd ? P1.w[i] : P0.w[i];
-#pragma unroll
-        for (int m = 0; m < NC; ++m) acc[i][m] = fmaf(w, c[m], acc[i][m]);
+  const std::true_type yes;
+  const std::false_type no;
+  if (T.n == 0) return;
+  if constexpr (LPP == 1) {
+    // the taps of a point are loaded a whole point ahead of their use
+    const int last = T.n - 1;
+    float2 w = t[0];
+    float dl = load_uniform(T.dl, 0);
+    int k = 0;
+    auto run = [&](int end, auto first, auto second) __attribute__((always_inline)) {
+      for (; k < end; ++k) {
+        const int nk = k < last ? k + 1 : last;
+        const float2 wn = t[4 * nk];
+        const float dn = load_uniform(T.dl, nk);
+        point(dl, w, first, second);
+        w = wn;
+        dl = dn;
       }
+    };
+    run(T.b_beg, yes, no);
+    run(APART ? T.a_end : T.n, yes, yes);
+    if constexpr (APART) run(T.n, no, yes);
+  } else {
+    const int odd = (lane >> 2) & 1;
+    for (int k = 0; k < T.n; k += 2) {
+      const int k1 = k + 1 < T.n ? k + 1 : k;
+      const float d0 = load_uniform(T.dl, k), d1 = load_uniform(T.dl, k1);
+      float2 w = t[4 * (odd ? k1 : k)];
+      if (odd && k + 1 >= T.n) w = make_float2(0.f, 0.f);  // no point for this lane
+      point(odd ? (k + 1 < T.n ? d1 : 0.f) : d0, w, yes, yes);
     }
+#pragma unroll
+    for (int m = 0; m < NC; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        ra[m][r] += __shfl_xor(ra[m][r], 4);
+        if (r < 2) rb[m][r] += __shfl_xor(rb[m][r], 4);
+      }
   }
-#pragma unroll
-  for (int i = 0; i < NOBS; ++i)
-#pragma unroll
-    for (int m = 0; m < NC; ++m) acc[i][m] += __shfl_xor(acc[i][m], 1);
 }
 
 // Banded instruments (many observed samples, each seeing a short window of
@@ -804,15 +785,14 @@ __device__ __forceinline__ int solve_cholesky(const float* H, const float* g, do
 // always for its 60 sweeps, it took milliseconds per call.)
 constexpr int WS_DOUBLES = 210;
 
-// LDS of a pass, per wave, in float4 slots of 64 lanes: the banded pass's H
-// and g (HG4), or the windowed dense pass's H (H4) and parked row (PARK4).
-// The eigen-fallback record lies in the parked row's slots: it is used
+// LDS of a pass, per wave, in float4 slots of 64 lanes: the dense pass's H
+// (H4) or the banded pass's H and g (HG4).  The eigen-fallback record lies in the same slots: it is used
 // between passes only.
-constexpr int PASS4 = (HG4 > H4 + PARK4) ? HG4 : H4 + PARK4;
-static_assert(PARK4 * 64 * 16 >= WS_DOUBLES * 8, "the fallback record fits the parked row");
+constexpr int WS4 = (WS_DOUBLES * 8 + 1023) / 1024;  // slots that hold the record
 __device__ __forceinline__ double* ws_record(float4* sHa) {
-  return reinterpret_cast<double*>(sHa + H4 * 64);
+  return reinterpret_cast<double*>(sHa);
 }
+static_assert(H4 >= WS4, "the fallback record fits the pass's slots");
 
 // Called by all 64 lanes of a one-wave workgroup for the system of lane
 // L: H (packed, element stride hs) and g (stride gs) are read through
