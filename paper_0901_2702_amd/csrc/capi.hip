@@ -608,32 +608,22 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
     for (const Point& p : pts) mtab.push_back(p.dl);
   }
   // Tables of the group inverter: the points in whole chunks; the taps by row
-  // (dense: over all points; banded: over the row's 16 points) and, banded,
-  // as matrix operands: lane l of chunk ch feeds row 16 ch - 3 + l % 16 with
-  // point 4 i + l / 16 of the chunk's window in step i.  Dense instruments of
-  // more than one chunk are left to lm_kernel.
-  std::vector<float> gdl, gtaps, gop;
+  // (dense: over all points; banded: over the row's 16 points).  Dense
+  // instruments of more than one chunk are left to lm_kernel.
+  std::vector<float> gdl, gtaps;
   {
     const int n_pts = inst->kind == KIND_BAND ? BAND_S * (int)blocks.size() : (int)pts.size();
     const int n_chunk = (n_pts + GROUP_PTS - 1) / GROUP_PTS;
     inst->group.n_chunk = n_chunk;
     gdl.assign((size_t)n_chunk * GROUP_PTS, 0.f);
     if (inst->kind == KIND_BAND) {
-      constexpr int RT = BAND_S * BAND_R, RC = GROUP_PTS / BAND_S, OPS = GROUP_WIN + 1;
+      constexpr int RT = BAND_S * BAND_R;
       gtaps.assign((size_t)no * RT, 0.f);
       for (int k = 0; k < n_pts; ++k) gdl[(size_t)k] = blocks[(size_t)(k / BAND_S)].dl[k % BAND_S];
       for (int j = 0; j < no; ++j)
         for (int i = 0; i < BAND_R; ++i)
           for (int q = 0; q < BAND_S; ++q)
             gtaps[(size_t)(j * RT + i * BAND_S + q)] = blocks[(size_t)(j + i)].w[q][BAND_R - 1 - i];
-      gop.assign((size_t)n_chunk * 64 * OPS, 0.f);
-      for (int ch = 0; ch < n_chunk; ++ch)
-        for (int l = 0; l < 64; ++l)
-          for (int i = 0; i < GROUP_WIN; ++i) {
-            const int r = l % 16, j = RC * ch - (BAND_R - 1) + r, t = 4 * (i - r) + l / 16;
-            if (j >= 0 && j < no && t >= 0 && t < RT)
-              gop[(size_t)((ch * 64 + l) * OPS + i)] = gtaps[(size_t)(j * RT + t)];
-          }
     } else if (n_chunk == 1) {
       gtaps.assign((size_t)no * GROUP_PTS, 0.f);
       for (int k = 0; k < n_pts; ++k) {
@@ -692,15 +682,11 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
   if (e == hipSuccess && (inst->kind == KIND_BAND || inst->group.n_chunk == 1)) {
     std::vector<float> host(gdl);
     host.insert(host.end(), gtaps.begin(), gtaps.end());
-    while (host.size() % 4 != 0) host.push_back(0.f);
-    const size_t o_op = host.size();
-    host.insert(host.end(), gop.begin(), gop.end());
     e = hipMalloc(&inst->d_group, sizeof(float) * host.size());
     if (e == hipSuccess)
       e = hipMemcpy(inst->d_group, host.data(), sizeof(float) * host.size(), hipMemcpyHostToDevice);
     inst->group.dl = inst->d_group;
     inst->group.taps = inst->d_group + gdl.size();
-    inst->group.taps_a = inst->d_group + o_op;
   }
   if (e != hipSuccess) {
     if (inst->d_group) hipFree(inst->d_group);

@@ -13,12 +13,10 @@ namespace vfisv {
 // (the tables end with a whole chunk; padding points have offset 0 and no
 // taps), and their taps.
 constexpr int GROUP_PTS = 64;
-constexpr int GROUP_WIN = 19;  // banded: float4s of points that a chunk's 16 rows see
 struct GroupTables {
-  const float* dl = nullptr;     // [n_chunk * GROUP_PTS] offsets, in record order (dense: 1 chunk)
-  const float* taps = nullptr;   // dense: [6][GROUP_PTS], natural row order; banded: [n_obs][16]
-                                 // over the row's 4 blocks
-  const float* taps_a = nullptr; // banded: the same as MFMA operands, [n_chunk][64 lanes][20]
+  const float* dl = nullptr;    // [n_chunk * GROUP_PTS] offsets, in record order (dense: 1 chunk)
+  const float* taps = nullptr;  // dense: [6][GROUP_PTS], natural row order; banded: [n_obs][16]
+                                // over the row's 4 blocks
   int n_chunk = 0;
 };
 
@@ -35,7 +33,7 @@ static_assert(GROUP_LEFT_SLOT >= COUNTER_SLOTS, "a slot of its own");
 
 // Most pixels a wave works on at a time, per layout (KIND_*): as many as leave
 // room for eight waves' LDS on a CU, two per SIMD.
-constexpr int GROUP_SLOTS[2] = {8, 6};
+constexpr int GROUP_SLOTS[2] = {8, 8};
 
 hipError_t launch_lm_group(const GroupArgs& a, int kind, int grid, hipStream_t s);
 hipError_t lm_group_blocks_per_cu(int kind, int* out);

@@ -9,11 +9,15 @@
 // follow one another with a point per lane, and the sums over the points are
 // formed in the order in which lm_kernel forms them: every row sum adds the
 // points in record order, chi^2 the rows in slot order, H and g the residuals
-// in the same order.  The row sums with derivatives run on the matrix cores:
-// v_mfma_f32_16x16x4_f32 adds its four products one after the other, each
-// with one float32 rounding, as a chain of fmaf does, so rows x quantities
-// over 4 points are one instruction and the same bits.  All products, sums
-// and decisions being those of lm_kernel, so are the results, bit for bit.
+// in the same order.  The dense row sums (59 points, every row sees nearly all
+// of them) run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four
+// products one after the other, each with one float32 rounding, as a chain of
+// fmaf does, so rows x quantities over 4 points are one instruction and the
+// same bits.  The banded rows see 16 points each and are summed on the vector
+// ALUs: 38 matrix instructions per chunk, three quarters of them on zero
+// taps, hold a wave up for longer (100,003 fine spectra 38.3 ms, now 30.5).
+// All products, sums and decisions being those of lm_kernel, so are the
+// results, bit for bit.
 //
 // Trials run without derivatives; only a start and an accepted model that
 // does not end its fit get their Jacobian (Fig. 6), with no wave-mates to
@@ -27,8 +31,8 @@
 // the decisions and the set-up of a turn, which one lane each would otherwise
 // run alone (two pixels per wave, 32 lanes each: 1,750 instructions per
 // trial, 131,072 pixels in 18.2 ms instead of 7.6).  Measured, default
-// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.40 ms, 4,096 3.95 -> 0.65,
-// 65,536 4.7 -> 4.0; 1,000 fine spectra 29.5 -> 1.66 ms, 100,003 63.7 -> 38.1.
+// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.37 ms, 4,096 3.95 -> 0.67,
+// 65,536 4.7 -> 3.95; 1,000 fine spectra 29.5 -> 1.46 ms, 100,003 63.7 -> 30.5.
 #include <hip/hip_runtime.h>
 
 #include "group.h"
@@ -53,11 +57,12 @@ constexpr int ASTR = 33;              // row sums of a row
 // dense: J [10], r, W J [10] over the 24 residuals (padded), JB pixels at a time
 constexpr int DJ = 28, JB = 3, JPIX = (2 * NPAR + 1) * DJ;
 static_assert(JB * JPIX <= CN, "J and W J fit the contributions' space");
-// banded: the same over a chunk's 16 rows
-constexpr int BROWS = 16, BJ = 4 * BROWS + 4, BPREV = 4 * (BAND_R - 1);
-constexpr int WSTR = BPREV + GROUP_PTS + 8;  // values-only window of a quantity
-static_assert((2 * NPAR + 1) * BJ <= CN, "J and W J fit the contributions' space");
-static_assert(BPREV + GROUP_PTS == 4 * GROUP_WIN, "window");
+// banded: a chunk's window is its 64 points behind the last 12 of the chunk
+// before; J, r and W J over its 16 rows; VB slots' values summed together
+constexpr int BROWS = 16, BJ = 4 * BROWS + 4, BPREV = BAND_S * (BAND_R - 1);
+constexpr int WSTR = BPREV + GROUP_PTS + 8, WN = NACC * WSTR, VB = 4;
+constexpr int BASTR = 36;  // row sums of a row: 16-byte rows on distinct banks
+static_assert((2 * NPAR + 1) * BJ <= WN, "J and W J fit the window's space");
 
 // Equilibrated normal equations of a slot's best model.
 struct EqLds {
@@ -66,7 +71,7 @@ struct EqLds {
   double sc[NPAR];  // 1 / sqrt(H_pp), 0 for a frozen parameter
   float hg[66];     // H (packed) and g
 };
-struct SlotLds {
+struct alignas(16) SlotLds {
   EqLds eq;
   float px[18];  // the fields of Pix that Weideman's series needs
   float rf[10];  // RowFactors
@@ -83,20 +88,20 @@ struct Lds<false> {
 };
 template <>
 struct Lds<true> {
-  double2 c2[(CN + 3) / 4];
-  float a[BROWS * ASTR];
-  float prev[NACC * BPREV];  // the last 12 points of the chunk before
+  double2 c2[WN / 4];  // the window; values only: VB windows, or chi^2 terms, and the tails
+  float a[BROWS * BASTR];  // row sums
   SlotLds slot[GROUP_SLOTS[KIND_BAND]];
 };
 constexpr int TSTR_D = 4 * NOBS_HMI + 1, TSTR_B = 4 * BROWS + 1;  // chi^2 terms of a slot
-constexpr int T_B = (4 * WSTR + 3) / 4;  // first chi^2 term behind the banded window
+constexpr int TAIL_B = VB * 4 * WSTR;  // first tail: a slot's last 12 points, four quantities
 static_assert(GROUP_SLOTS[KIND_DENSE6] * TSTR_D <= CN / 4, "chi^2 terms");
-static_assert(T_B + GROUP_SLOTS[KIND_BAND] * TSTR_B <= CN / 4, "window and chi^2 terms");
+static_assert(4 * VB * TSTR_B <= TAIL_B && VB * BROWS * 4 <= BROWS * BASTR, "chi^2 terms");
+static_assert(TAIL_B + GROUP_SLOTS[KIND_BAND] * 4 * BPREV <= WN, "values-only tails");
 static_assert(GROUP_SLOTS[KIND_DENSE6] * NOBS_HMI <= 64 &&
                   GROUP_SLOTS[KIND_DENSE6] * NOBS_HMI * 8 <= JB * NOBS_HMI * ASTR,
               "values-only row sums of every slot");
-static_assert(GROUP_SLOTS[KIND_BAND] * 4 * BPREV <= NACC * BPREV, "values-only tails");
 static_assert(4 * CN >= (int)sizeof(double) * WS_DOUBLES, "the eigen fallback's record fits");
+static_assert(sizeof(Lds<false>) <= 20480 && sizeof(Lds<true>) <= 20480, "eight waves on a CU");
 
 // The normal equations as 64 independent chains of sums over the residuals:
 // chain e < 55 is H's packed entry e = (p, q), chain 55 + p is g[p]; H's
@@ -125,6 +130,57 @@ __device__ __forceinline__ float fma4(float4 w, float4 c, float s) {
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ void st4(float* p, float a, float b, float c, float d) {
   *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
+}
+// Nothing is scheduled across: the LDS loads of a block are all issued before
+// their first use.  (Left to itself the compiler loads one value, waits out
+// the LDS and uses it: 62 cycles per term of chi^2.)
+__device__ __forceinline__ void issued() { __builtin_amdgcn_sched_barrier(0); }
+
+// chi += the N terms term(0 ..), one after the other; the next LB are loaded meanwhile
+template <int N, class F>
+__device__ __forceinline__ double chi_chain(double chi, F term) {
+  constexpr int LB = 8;
+  static_assert(N % LB == 0, "whole blocks");
+  double2 t[2][LB];
+#pragma unroll
+  for (int i = 0; i < LB; ++i) t[0][i] = term(i);
+#pragma unroll
+  for (int b = 0; b < N / LB; ++b) {
+    if (b + 1 < N / LB) {
+#pragma unroll
+      for (int i = 0; i < LB; ++i) t[(b + 1) & 1][i] = term((b + 1) * LB + i);
+    }
+    issued();
+#pragma unroll
+    for (int i = 0; i < LB; ++i) chi = fma(t[b & 1][i].x, t[b & 1][i].y, chi);
+    issued();
+  }
+  return chi;
+}
+// The same for an entry of H or g: N residuals, four of J and W J per load.
+template <int N>
+__device__ __forceinline__ float eq_chain(float h, const float* WJ, const float* J) {
+  constexpr int LB = 4;
+  float4 w[2][LB], j[2][LB];
+  const auto load = [&](int b) {
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      if (b * LB + i >= N / 4) continue;
+      w[b & 1][i] = ld4(WJ + 4 * (b * LB + i));
+      j[b & 1][i] = ld4(J + 4 * (b * LB + i));
+    }
+  };
+  load(0);
+#pragma unroll
+  for (int b = 0; b * LB < N / 4; ++b) {
+    if ((b + 1) * LB < N / 4) load(b + 1);
+    issued();
+#pragma unroll
+    for (int i = 0; i < LB; ++i)
+      if (b * LB + i < N / 4) h = fma4(w[b & 1][i], j[b & 1][i], h);
+    issued();
+  }
+  return h;
 }
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -235,9 +291,84 @@ __device__ __forceinline__ int solve_equilibrated(const EqLds& E, double eps, do
   return 0;
 }
 
-// Slots of a mask, lowest first (wave-uniform).
+// Slots of a mask, lowest first (wave-uniform), and its b-th slot per lane
+// (b < 4; -1 if there is none).
 __device__ __forceinline__ int first_slot(unsigned m) {
   return __builtin_amdgcn_readfirstlane(__ffs((int)m) - 1);
+}
+__device__ __forceinline__ int nth_slot(unsigned m, int b) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (b > i) m &= m - 1u;
+  return __ffs((int)m) - 1;
+}
+
+// Residual and Jacobian row of Stokes parameter s (lane-dependent) of one
+// observed sample from its row sums a: assemble_sample's operations for it.
+__device__ __forceinline__ float assemble_one(const float* a, float rs, const RowFactors& f, int s,
+                                              float ob, float* J) {
+  const bool lin = s == 1 || s == 2;
+  const float a2 = a[2], a3 = a[3], as = a[s == 0 ? 0 : 4];
+  const float Q0 = f.S1a * a2, U0 = f.S1a * a3;
+  const float SQ = fmaf(f.c2p, Q0, -f.s2p * U0), SU = fmaf(f.s2p, Q0, f.c2p * U0);
+  const float cx = s == 1 ? f.c2p : f.s2p, cy = s == 1 ? -f.s2p : f.c2p;
+  const float fx = s == 0 ? f.S1 : f.S1a;
+  const float* d = a + 5 + (lin ? 1 : s);
+  const float qf[6] = {f.fB, f.fg, f.fv, f.fD, 2.f, 1.f};
+  const int qidx[6] = {0, 1, 3, 4, 5, 6};
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    const float x = d[4 * q] * fx * qf[q];
+    const float y = a[5 + 4 * q + 2] * f.S1a * qf[q];
+    const float xy = fmaf(cx, x, cy * y);
+    J[qidx[q]] = lin ? xy : x;
+  }
+  const float dpsi = s == 1 ? -2.f * DEG * SU : 2.f * DEG * SQ;
+  J[2] = lin ? dpsi : 0.f;
+  J[7] = s == 0 ? rs : 0.f;
+  const float j8 = fmaf(cx, f.alpha * a2, cy * (f.alpha * a3));
+  J[8] = lin ? j8 : s == 0 ? as : f.alpha * as;
+  const float j9 = fmaf(cx, f.S1 * a2, cy * (f.S1 * a3));
+  J[9] = lin ? j9 : f.S1 * a[s == 0 ? 1 : 4];
+  const float SI = fmaf(f.S0, rs, f.S1 * as);
+  const float r = ob - (lin ? (s == 1 ? SQ : SU) : SI);
+  return s == 3 ? fmaf(-f.S1a, as, ob) : r;
+}
+
+// This lane's entry of H or g (keep: H stays).
+__device__ __forceinline__ void store_entry(EqLds& E, float h, bool keep, int e, int p, int q) {
+  if (q == NPAR) E.hg[55 + p] = h;
+  else if (!keep) E.hg[e] = h;
+  if (e == 0) E.hg[30] = 0.f;
+}
+
+// Equilibrates the slots of a mask, six at a time.
+__device__ __forceinline__ void equilibrate(SlotLds* slot, unsigned jm, uint32_t free_mask,
+                                            int lane, int ep, int eq) {
+  wave_fence();
+  for (unsigned m = jm; m != 0u;) {
+    unsigned mk = m;
+    const int i = lane / NPAR, p = lane - i * NPAR;
+    for (int b = 0; b < i; ++b) mk &= mk - 1u;
+    if (mk != 0u && i < 6) {
+      EqLds& E = slot[__ffs((int)mk) - 1].eq;
+      E.sc[p] = scale_of(E, free_mask, p);
+    }
+    wave_fence();
+    for (int b = 0; b < 6 && m != 0u; ++b, m &= m - 1u) {
+      EqLds& E = slot[first_slot(m)].eq;
+      scale_entry(E, lane, ep, eq);
+      if (lane == 0) E.c[30] = 0.0;
+    }
+  }
+  wave_fence();
+}
+
+// The lane's number, recomputed from here on: what a pass derives from it (LDS
+// addresses, rows) is not carried through the other passes in registers.
+__device__ __forceinline__ int afresh(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
 }
 
 template <bool BAND>
@@ -254,7 +385,7 @@ template <>
 struct Layout<false> {
   Lds<false>& S;
   const GroupArgs& ga;
-  const int lane, col, kq;
+  int lane, col, kq;
   float* const c;
   bool pair;
   float dl, tap[16], rs;
@@ -310,6 +441,9 @@ struct Layout<false> {
 
   // chi^2 (without 1/dof) of the slots in lm, each in its owner's lane
   __device__ __forceinline__ double values(unsigned lm, bool, int64_t, double) {
+    lane = afresh(lane);
+    col = lane & 15;
+    kq = lane >> 4;
     for (unsigned m = lm; m != 0u;) {
       // up to three slots share the 16 columns of the MFMA
       const unsigned m0 = m;
@@ -356,11 +490,8 @@ struct Layout<false> {
     wave_fence();
     double chi = 0.0;
     if (lane < 32 && ((lm >> lane) & 1u)) {
-#pragma unroll
-      for (int i = 0; i < 4 * NOBS_HMI; ++i) {
-        const double2 t = T[lane * TSTR_D + i];
-        chi = fma(t.x, t.y, chi);
-      }
+      const double2* t = T + lane * TSTR_D;
+      chi = chi_chain<4 * NOBS_HMI>(0.0, [&](int i) { return t[i]; });
     }
     wave_fence();
     return chi;
@@ -369,6 +500,9 @@ struct Layout<false> {
   // Jacobian and equilibrated normal equations of the slots in jm; those in
   // keep leave H as it is (Sect. 4.4) and take the new gradient
   __device__ __forceinline__ void normal(unsigned jm, unsigned keep, int64_t, int cp, int cq) {
+    lane = afresh(lane);
+    col = lane & 15;
+    kq = lane >> 4;
     for (unsigned m = jm; m != 0u;) {
       const unsigned m0 = m;
       int nb = 0;
@@ -427,9 +561,7 @@ struct Layout<false> {
       for (int i = 0; i < nb; ++i, mb &= mb - 1u) {
         const float* Jt = c + i * JPIX + cq * DJ;
         const float* WJt = c + i * JPIX + (NPAR + 1 + cp) * DJ;
-        float h = 0.f;
-#pragma unroll
-        for (int k = 0; k < 4 * NOBS_HMI; k += 4) h = fma4(ld4(WJt + k), ld4(Jt + k), h);
+        const float h = eq_chain<4 * NOBS_HMI>(0.f, WJt, Jt);
         const int k0 = first_slot(mb);
         EqLds& E = S.slot[k0].eq;
         if (cq == NPAR || !((keep >> k0) & 1u)) E.hg[cq < NPAR ? lane : 55 + cp] = h;
@@ -459,15 +591,15 @@ struct Layout<false> {
 };
 
 // ---- banded layout ---------------------------------------------------------
-// A chunk of 64 points is 16 blocks and completes 16 rows, whose points lie
-// in the chunk and in the last three blocks (12 points) of the one before.
-// Lane (jr, s) = (lane % 16, lane / 16) carries row jr of the chunk and its
-// Stokes parameter s.
+// A chunk of 64 points is 16 blocks and completes 16 rows, whose 16 points
+// each lie in the chunk's window.  Lane (jr, s) = (lane % 16, lane / 16) sums
+// row jr over its points, a share s of the quantities, on the vector ALUs (a
+// matrix product would spend its time on the zero taps of 76 points).
 template <>
 struct Layout<true> {
   Lds<true>& S;
   const GroupArgs& ga;
-  const int lane, jr, s;
+  int lane, jr, s;
   float* const c;
 
   __device__ __forceinline__ Layout(Lds<true>& S_, const GroupArgs& g, int lane_, bool)
@@ -484,30 +616,30 @@ struct Layout<true> {
     return __ballot(!ok) == 0ull;
   }
 
-  struct Row {
-    float ob[4], wb[4], rs;
-    int j;
-    bool valid;
-  };
-  __device__ __forceinline__ Row load_row(int64_t pix, int ch) const {
-    const int no = ga.A.C.n_obs;
-    Row r;
-    r.j = ch * BROWS - (BAND_R - 1) + jr;
-    r.valid = r.j >= 0 && r.j < no;
-    if (!r.valid) r.j = 0;
-    const float* o = ga.A.stokes + pix * (int64_t)(4 * no) + r.j;
-    const float* W = (ga.A.W_pp ? ga.A.W + pix * (int64_t)(4 * no) : ga.A.W) + r.j;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      r.ob[k] = o[k * no];
-      r.wb[k] = W[k * no];
-    }
-    r.rs = ga.A.row_sums[r.j];
-    return r;
+  // Observed row that row jr of chunk ch completes, -1 if there is none.
+  __device__ __forceinline__ int row_of(int ch) const {
+    const int j = ch * BROWS - (BAND_R - 1) + jr;
+    return j >= 0 && j < ga.A.C.n_obs ? j : -1;
   }
-  __device__ __forceinline__ static int64_t pix_of(int64_t pix, int k) {
-    const unsigned lo = __builtin_amdgcn_readlane((unsigned)(pix & 0xffffffffll), k);
-    const unsigned hi = __builtin_amdgcn_readlane((unsigned)(pix >> 32), k);
+  struct Taps {
+    float4 w[4];
+  };
+  __device__ __forceinline__ Taps load_taps(int j) const {
+    Taps T;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) T.w[i] = ld4(ga.T.taps + (j >= 0 ? j : 0) * 16 + 4 * i);
+    return T;
+  }
+  // this lane's row summed over the window of one quantity
+  __device__ __forceinline__ float row_sum(const Taps& T, const float* window) const {
+    float a = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a = fma4(T.w[i], ld4(window + 4 * (jr + i)), a);
+    return a;
+  }
+  __device__ __forceinline__ int64_t pix_of(int64_t pix, int k) const {
+    const unsigned lo = __shfl((unsigned)(pix & 0xffffffffll), k);
+    const unsigned hi = __shfl((unsigned)(pix >> 32), k);
     return (int64_t)(((unsigned long long)hi << 32) | lo);
   }
 
@@ -515,150 +647,160 @@ struct Layout<true> {
   // slot whose running sum has reached its bound (chi^2 of its best model) is
   // left there: with weights >= 0 the rest cannot bring it back below.
   __device__ __forceinline__ double values(unsigned lm, bool monotone, int64_t pix, double bound) {
-    double2* T = S.c2 + T_B;
+    lane = afresh(lane);
+    jr = lane & 15;
+    s = lane >> 4;
+    const int no = ga.A.C.n_obs;
+    double2* T = S.c2;
     double chi = 0.0;
-    for (int i = lane; i < GROUP_SLOTS[KIND_BAND] * 4 * BPREV; i += 64) S.prev[i] = 0.f;
+    float* const tail = c + TAIL_B;
+    for (int i = lane; i < GROUP_SLOTS[KIND_BAND] * 4 * BPREV; i += 64) tail[i] = 0.f;
+    const int pq = lane / BPREV, pp = lane - pq * BPREV;  // lanes < 48: a point of a tail
 #pragma unroll 1
     for (int ch = 0; ch < ga.T.n_chunk && lm != 0u; ++ch) {
       const float dl = ga.T.dl[ch * GROUP_PTS + lane];
+      const int j = row_of(ch);
+      const Taps taps = load_taps(j);
+      const float rs = j >= 0 ? ga.A.row_sums[j] : 0.f;
 #pragma unroll 1
-      for (unsigned m = lm; m != 0u; m &= m - 1u) {
-        const int k = first_slot(m);
-        const Row r = load_row(pix_of(pix, k), ch);
-        float4 w[4];
+      for (unsigned m = lm; m != 0u;) {
+        const unsigned m0 = m;
+        // lane (jr, s) assembles row jr of the batch's slot s
+        const int kb = nth_slot(m0, s);
+        const int64_t pb = pix_of(pix, kb >= 0 ? kb : 0);
+        float ob[4] = {}, wb[4] = {};
+        if (kb >= 0 && j >= 0) {
+          const float* o = ga.A.stokes + pb * (int64_t)(4 * no) + j;
+          const float* W = (ga.A.W_pp ? ga.A.W + pb * (int64_t)(4 * no) : ga.A.W) + j;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = ld4(ga.T.taps + r.j * 16 + 4 * i);
-        const Pix px = get_pix(S.slot[k]);
-        float v[NACC];
-        point_contrib<false>(dl, px, ga.A.C, v);
-        // the quantities that the Stokes values need
-        const float u[4] = {v[0], v[2], v[3], v[4]};
-        float* prev = S.prev + k * (4 * BPREV);
-        if (lane < 4 * BPREV) c[(lane / BPREV) * WSTR + lane % BPREV] = prev[lane];
+          for (int i = 0; i < 4; ++i) {
+            ob[i] = o[i * no];
+            wb[i] = W[i * no];
+          }
+        }
+        int nb = 0;
+#pragma unroll 1
+        for (; nb < VB && m != 0u; ++nb, m &= m - 1u) {
+          const int k = first_slot(m);
+          const Pix px = get_pix(S.slot[k]);
+          float v[NACC];
+          point_contrib<false>(dl, px, ga.A.C, v);
+          // the quantities that the Stokes values need
+          const float u[4] = {v[0], v[2], v[3], v[4]};
+          float* const win = c + 4 * nb * WSTR;
+          float* const last = tail + k * (4 * BPREV);
+          if (lane < 4 * BPREV) win[pq * WSTR + pp] = last[lane];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          c[i * WSTR + BPREV + lane] = u[i];
-          if (lane >= GROUP_PTS - BPREV) prev[i * BPREV + lane - (GROUP_PTS - BPREV)] = u[i];
+          for (int i = 0; i < 4; ++i) {
+            win[i * WSTR + BPREV + lane] = u[i];
+            if (lane >= GROUP_PTS - BPREV) last[i * BPREV + lane - (GROUP_PTS - BPREV)] = u[i];
+          }
         }
         wave_fence();
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sum = fma4(w[i], ld4(&c[s * WSTR + 4 * (jr + i)]), sum);
-        S.a[jr * 5 + s] = sum;
+#pragma unroll 1
+        for (int b = 0; b < nb; ++b)
+          S.a[(b * BROWS + jr) * 4 + s] = row_sum(taps, c + (4 * b + s) * WSTR);
         wave_fence();
-        const float a[5] = {S.a[jr * 5], 0.f, S.a[jr * 5 + 1], S.a[jr * 5 + 2], S.a[jr * 5 + 3]};
-        const RowFactors rf = get_rf(S.slot[k]);
-        float Sv[4], J[4][NPAR], rr[4];
-        assemble_sample<false>(a, r.rs, rf, Sv, J);
+        if (kb >= 0) {
+          const float4 h = ld4(S.a + lane * 4);
+          const float a[5] = {h.x, 0.f, h.y, h.z, h.w};
+          const RowFactors rf = get_rf(S.slot[kb]);
+          float Sv[4], J[4][NPAR];
+          assemble_sample<false>(a, rs, rf, Sv, J);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rr[i] = r.ob[i] - Sv[i];
-        const float res = s == 0 ? rr[0] : s == 1 ? rr[1] : s == 2 ? rr[2] : rr[3];
-        const float wt = s == 0 ? r.wb[0] : s == 1 ? r.wb[1] : s == 2 ? r.wb[2] : r.wb[3];
-        T[k * TSTR_B + 4 * jr + s] = r.valid ? make_double2((double)wt * (double)res, (double)res)
-                                             : make_double2(0.0, 0.0);
-        wave_fence();
-      }
-      const bool mine = lane < 32 && ((lm >> lane) & 1u);
-      if (mine) {
-#pragma unroll 8
-        for (int i = 0; i < 4 * BROWS; ++i) {
-          const double2 t = T[lane * TSTR_B + i];
-          chi = fma(t.x, t.y, chi);
+          for (int i = 0; i < 4; ++i) {
+            const float r = ob[i] - Sv[i];
+            T[s * TSTR_B + BROWS * i + jr] = j >= 0 ? make_double2((double)wb[i] * (double)r, (double)r)
+                                                : make_double2(0.0, 0.0);
+          }
         }
+        wave_fence();
+        const bool mine = lane < 32 && (((m0 & ~m) >> lane) & 1u);
+        if (mine) {
+          const double2* t = T + __popc(m0 & ((1u << lane) - 1u)) * TSTR_B;
+#pragma unroll 1
+          for (int b = 0; b < BROWS; b += 2)
+            chi = chi_chain<8>(chi, [&](int i) { return t[BROWS * (i & 3) + (i >> 2) + b]; });
+        }
+        wave_fence();
+        lm &= ~(unsigned)__ballot(mine && monotone && rounded(chi * ga.A.inv_dof) >= bound);
       }
-      wave_fence();
-      lm &= ~(unsigned)__ballot(mine && monotone && rounded(chi * ga.A.inv_dof) >= bound);
     }
     return chi;
   }
 
-  __device__ __forceinline__ void normal(unsigned jm, unsigned keep, int64_t pix, int cp, int cq) {
-    const float* Jt = c + cq * BJ;
-    const float* WJt = c + (NPAR + 1 + cp) * BJ;
+  __device__ __forceinline__ void normal(unsigned jm, unsigned keep, int64_t pix, int ep, int eq) {
+    lane = afresh(lane);
+    jr = lane & 15;
+    s = lane >> 4;
+    const int no = ga.A.C.n_obs;
+    const float* Jc = c + eq * BJ;
+    const float* WJ = c + (NPAR + 1 + ep) * BJ;
     for (unsigned m = jm; m != 0u; m &= m - 1u) {
       const int k = first_slot(m);
       const int64_t pk_ = pix_of(pix, k);
+      const float* o = ga.A.stokes + pk_ * (int64_t)(4 * no) + s * no;
+      const float* W = (ga.A.W_pp ? ga.A.W + pk_ * (int64_t)(4 * no) : ga.A.W) + s * no;
       float h = 0.f;
-      for (int i = lane; i < NACC * BPREV; i += 64) S.prev[i] = 0.f;
+      // the last 12 points of the chunk before, two float4 per lane
+      const int i1 = lane + 64 < NACC * (BPREV / 4) ? lane + 64 : lane;
+      float* const p0 = c + (lane / 3) * WSTR + 4 * (lane % 3);
+      float* const p1 = c + (i1 / 3) * WSTR + 4 * (i1 % 3);
+      float4 t0 = make_float4(0.f, 0.f, 0.f, 0.f), t1 = t0;
 #pragma unroll 1
       for (int ch = 0; ch < ga.T.n_chunk; ++ch) {
-        const Row r = load_row(pk_, ch);
-        float tap[GROUP_WIN + 1];
-#pragma unroll
-        for (int i = 0; i < GROUP_WIN + 1; i += 4) {
-          const float4 t = ld4(ga.T.taps_a + (ch * 64 + lane) * (GROUP_WIN + 1) + i);
-          tap[i] = t.x;
-          tap[i + 1] = t.y;
-          tap[i + 2] = t.z;
-          tap[i + 3] = t.w;
+        // lane (jr, s) assembles residual s of row jr
+        const int j = row_of(ch);
+        const Taps taps = load_taps(j);
+        float ob = 0.f, w = 0.f, rs = 0.f;
+        if (j >= 0) {
+          ob = o[j];
+          w = W[j];
+          rs = ga.A.row_sums[j];
         }
+        *reinterpret_cast<float4*>(p0) = t0;
+        *reinterpret_cast<float4*>(p1) = t1;
         {
           const Pix px = get_pix(S.slot[k]);
           float v[NACC];
           point_contrib<true>(ga.T.dl[ch * GROUP_PTS + lane], px, ga.A.C, v);
 #pragma unroll
-          for (int i = 0; i < NACC; ++i) c[i * CSTR + lane] = v[i];
-        }
-        wave_fence();
-        // row sums: rows jr, quantities jr and 16 + jr of this lane's column
-        {
-          const int m1 = jr + 16 < NACC ? jr + 16 : jr;
-          f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int i = 0; i < GROUP_WIN; ++i) {
-            constexpr int PW = BAND_R - 1;
-            const float b0 = i < PW ? S.prev[jr * BPREV + 4 * i + s] : c[jr * CSTR + 4 * (i - PW) + s];
-            const float b1 = i < PW ? S.prev[m1 * BPREV + 4 * i + s] : c[m1 * CSTR + 4 * (i - PW) + s];
-            a0 = mfma4(tap[i], b0, a0);
-            a1 = mfma4(tap[i], b1, a1);
-          }
-          wave_fence();
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            S.a[(4 * s + i) * ASTR + jr] = a0[i];
-            if (jr + 16 < NACC) S.a[(4 * s + i) * ASTR + jr + 16] = a1[i];
-          }
-          for (int i = lane; i < NACC * (BPREV / 4); i += 64) {
-            const int q = i / (BPREV / 4), p = 4 * (i % (BPREV / 4));
-            const float4 v = ld4(&c[q * CSTR + GROUP_PTS - BPREV + p]);
-            st4(&S.prev[q * BPREV + p], v.x, v.y, v.z, v.w);
-          }
+          for (int i = 0; i < NACC; ++i) c[i * WSTR + BPREV + lane] = v[i];
         }
         wave_fence();
         {
-          float a[NACC];
+          float v[8];
 #pragma unroll
-          for (int i = 0; i < NACC; ++i) a[i] = S.a[jr * ASTR + i];
+          for (int i = 0; i < 8; ++i) {
+            const int q = 8 * s + i < NACC ? 8 * s + i : NACC - 1;
+            v[i] = row_sum(taps, c + q * WSTR);
+          }
+          float* const a = S.a + jr * BASTR + 8 * s;
+          st4(a, v[0], v[1], v[2], v[3]);
+          st4(a + 4, v[4], v[5], v[6], v[7]);
+        }
+        t0 = ld4(p0 + GROUP_PTS);
+        t1 = ld4(p1 + GROUP_PTS);
+        wave_fence();
+        {
           const RowFactors rf = get_rf(S.slot[k]);
-          float Sv[4], J[4][NPAR], rr[4];
-          assemble_sample<true>(a, r.rs, rf, Sv, J);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) rr[i] = r.ob[i] - Sv[i];
-          const float w = s == 0 ? r.wb[0] : s == 1 ? r.wb[1] : s == 2 ? r.wb[2] : r.wb[3];
-          const float res = s == 0 ? rr[0] : s == 1 ? rr[1] : s == 2 ? rr[2] : rr[3];
+          float J[NPAR];
+          const float r = assemble_one(S.a + jr * BASTR, rs, rf, s, ob, J);
+          float* Jt = c + 4 * jr + s;
 #pragma unroll
           for (int p = 0; p < NPAR; ++p) {
-            const float d = s == 0 ? J[0][p] : s == 1 ? J[1][p] : s == 2 ? J[2][p] : J[3][p];
-            c[p * BJ + 4 * jr + s] = r.valid ? d : 0.f;
-            c[(NPAR + 1 + p) * BJ + 4 * jr + s] = r.valid ? w * d : 0.f;
+            Jt[p * BJ] = j >= 0 ? J[p] : 0.f;
+            Jt[(NPAR + 1 + p) * BJ] = j >= 0 ? w * J[p] : 0.f;
           }
-          c[NPAR * BJ + 4 * jr + s] = r.valid ? res : 0.f;
+          Jt[NPAR * BJ] = j >= 0 ? r : 0.f;
         }
         wave_fence();
-#pragma unroll 4
-        for (int i = 0; i < 4 * BROWS; i += 4) h = fma4(ld4(WJt + i), ld4(Jt + i), h);
+        h = eq_chain<4 * BROWS>(h, WJ, Jc);
         wave_fence();
       }
-      EqLds& E = S.slot[k].eq;
-      if (cq == NPAR || !((keep >> k) & 1u)) E.hg[cq < NPAR ? lane : 55 + cp] = h;
-      if (lane == 0) E.hg[30] = 0.f;
-      wave_fence();
-      if (lane < NPAR) E.sc[lane] = scale_of(E, ga.A.free_mask, lane);
-      wave_fence();
-      scale_entry(E, lane, cp, cq);
-      if (lane == 0) E.c[30] = 0.0;
-      wave_fence();
+      store_entry(S.slot[k].eq, h, (keep >> k) & 1u, lane, ep, eq);
     }
+    equilibrate(S.slot, jm, ga.A.free_mask, lane, ep, eq);
   }
 };
 
