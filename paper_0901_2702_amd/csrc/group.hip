@@ -31,8 +31,8 @@
 // the decisions and the set-up of a turn, which one lane each would otherwise
 // run alone (two pixels per wave, 32 lanes each: 1,750 instructions per
 // trial, 131,072 pixels in 18.2 ms instead of 7.6).  Measured, default
-// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.37 ms, 4,096 3.95 -> 0.67,
-// 65,536 4.7 -> 3.95; 1,000 fine spectra 29.5 -> 1.46 ms, 100,003 63.7 -> 30.5.
+// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.35 ms, 4,096 3.95 -> 0.62,
+// 65,536 4.7 -> 3.7; 1,000 fine spectra 29.5 -> 1.43 ms, 100,003 63.7 -> 30.2.
 #include <hip/hip_runtime.h>
 
 #include "group.h"
@@ -229,7 +229,7 @@ __device__ __forceinline__ double scale_of(const EqLds& E, uint32_t free_mask, i
     if ((free_mask >> k) & 1u) maxd = fmax(maxd, (double)E.hg[pk(k, k)]);
   const double d = (double)E.hg[p * (p + 3) / 2];
   const bool act = ((free_mask >> p) & 1u) && maxd > 0.0 && d > 1e-30 * maxd;
-  return act ? 1.0 / sqrt(d) : 0.0;
+  return act ? root_of(d).rl : 0.0;
 }
 // This lane's chain (p, q) of the equilibrated system.
 __device__ __forceinline__ void scale_entry(EqLds& E, int e, int p, int q) {
@@ -237,57 +237,25 @@ __device__ __forceinline__ void scale_entry(EqLds& E, int e, int p, int q) {
   else E.b[p] = E.sc[p] * (double)E.hg[55 + p];
 }
 
-// The factorisation and substitutions of solve_cholesky on an equilibrated
-// system.  Returns 0, 1 (broken down) or 2 (nothing free).
+// The step of solve_cholesky from an equilibrated system.  Returns 0, 1 (left
+// to solve_wave) or 2 (nothing free).
 __device__ __forceinline__ int solve_equilibrated(const EqLds& E, double eps, double* delta) {
-  double sc[NPAR], L[55];
+  double L[55], y[NPAR];
   bool any = false;
 #pragma unroll
   for (int p = 0; p < NPAR; ++p) {
-    sc[p] = E.sc[p];
-    any = any || sc[p] != 0.0;
+    const double sc = E.sc[p];
+    any = any || sc != 0.0;
     delta[p] = 0.0;
+    y[p] = E.b[p];
 #pragma unroll
     for (int q = 0; q < p; ++q) L[pk(p, q)] = E.c[pk(p, q)];
-    L[pk(p, p)] = (sc[p] != 0.0) ? 1.0 + eps : 1.0;
+    L[pk(p, p)] = (sc != 0.0) ? 1.0 + eps : 1.0;
   }
   if (!any) return 2;
-  bool ok = true;
+  if (factor_solve(L, y) != 0) return 1;
 #pragma unroll
-  for (int j = 0; j < NPAR; ++j) {
-    double d = L[pk(j, j)];
-#pragma unroll
-    for (int k = 0; k < j; ++k) d = fma(-L[pk(j, k)], L[pk(j, k)], d);
-    ok = ok && (d > 0.0) && (d < 1.0e300);
-    const double ljj = sqrt(fmax(d, 1e-300));
-    const double rl = 1.0 / ljj;
-    L[pk(j, j)] = ljj;
-#pragma unroll
-    for (int i = j + 1; i < NPAR; ++i) {
-      double s = L[pk(i, j)];
-#pragma unroll
-      for (int k = 0; k < j; ++k) s = fma(-L[pk(i, k)], L[pk(j, k)], s);
-      L[pk(i, j)] = s * rl;
-    }
-  }
-  if (!ok) return 1;
-  double y[NPAR];
-#pragma unroll
-  for (int i = 0; i < NPAR; ++i) {
-    double s = E.b[i];
-#pragma unroll
-    for (int k = 0; k < i; ++k) s = fma(-L[pk(i, k)], y[k], s);
-    y[i] = s / L[pk(i, i)];
-  }
-#pragma unroll
-  for (int i = NPAR - 1; i >= 0; --i) {
-    double s = y[i];
-#pragma unroll
-    for (int k = i + 1; k < NPAR; ++k) s = fma(-L[pk(k, i)], y[k], s);
-    y[i] = s / L[pk(i, i)];
-  }
-#pragma unroll
-  for (int p = 0; p < NPAR; ++p) delta[p] = rounded(sc[p] * y[p]);
+  for (int p = 0; p < NPAR; ++p) delta[p] = rounded(E.sc[p] * y[p]);
   return 0;
 }
 
@@ -880,14 +848,14 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
         if (lane == k) monotone = f;
       }
     }
-    // ---- eigen/SVD fallbacks of the last steps, one slot at a time ----------
+    // ---- steps left by the solve, one slot at a time ------------------------
     for (unsigned fbm = (unsigned)__ballot(need_fb); fbm != 0u; fbm &= fbm - 1u) {
       const int L = first_slot(fbm);
       double* sws = reinterpret_cast<double*>(S.c2);
       const float* hg = S.slot[L].eq.hg;
-      solve_eigen_wave(hg, 1, hg + 55, 1, __shfl(eps, L), A.free_mask, sws, lane);
+      const bool eigen = solve_wave(hg, 1, hg + 55, 1, __shfl(eps, L), A.free_mask, sws, lane);
       if (lane == L) {
-        ++n_fb;
+        if (eigen) ++n_fb;
         double Mt[NPAR];
 #pragma unroll
         for (int k = 0; k < NPAR; ++k) Mt[k] = (double)Mb[k] + sws[200 + k];

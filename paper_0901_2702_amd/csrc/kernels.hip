@@ -397,8 +397,8 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
   chig = chi_first = 0.0;
   int bad = 0, kr = 0;
   bool pending = false, restart_eval = false;
-  // the damped solve needs the eigen fallback: done with the whole wave at
-  // the top of the next turn, where every lane is active
+  // the damped step is left to solve_wave (the eigen fallback): done with the
+  // whole wave at the top of the next turn, where every lane is active
   bool need_fb = false;
   // derivative pass due (Fig. 6: derivatives only at accepted models): an
   // accepted trial of a values-only pass waits for the next derivative pass
@@ -473,13 +473,13 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
     if (nm != 0ull && dry == (1u << NQ) - 1u) exhausted = exhausted || ((nm >> lane) & 1ull);
     if constexpr (LPP == 2) exhausted = __shfl(exhausted ? 1 : 0, mate) != 0;
 
-    // ---- eigen/SVD fallbacks of the last steps, one lane at a time --------
+    // ---- steps left by solve_cholesky, one lane at a time -----------------
     for (unsigned long long fbm = __ballot(need_fb); fbm != 0ull; fbm &= fbm - 1ull) {
       const int L = __ffsll((unsigned long long)fbm) - 1;
-      solve_eigen_wave(&sHG[L], 64, &sHG[55 * 64 + L], 64, __shfl(eps, L), A.free_mask, sws,
-                       lane);
+      const bool eigen = solve_wave(&sHG[L], 64, &sHG[55 * 64 + L], 64, __shfl(eps, L),
+                                    A.free_mask, sws, lane);
       if (lane == L) {
-        if (leader) ev |= EV_FB;
+        if (leader && eigen) ev |= EV_FB;
         double Mt[NPAR];
 #pragma unroll
         for (int q = 0; q < NPAR; ++q) Mt[q] = (double)Mb[64 * q] + sws[200 + q];
@@ -655,8 +655,8 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
       for (int e = 0; e < 55; ++e) H[e] = sHG[e * 64 + lane];
 #pragma unroll
       for (int e = 0; e < NPAR; ++e) g[e] = sHG[(55 + e) * 64 + lane];
-      double delta[NPAR], sc[NPAR], b[NPAR];
-      const int code = solve_cholesky(H, g, eps, A.free_mask, delta, sc, b);
+      double delta[NPAR];
+      const int code = solve_cholesky(H, g, eps, A.free_mask, delta);
       if (code == 1) {
         need_fb = true;  // the step is taken at the top of the next turn
       } else {
@@ -809,16 +809,16 @@ __global__ __launch_bounds__(64) void solve_kernel(const SolveArgs A) {
       for (int e = 0; e < 55; ++e) H[e] = A.H[i * 55 + e];
 #pragma unroll
       for (int e = 0; e < NPAR; ++e) g[e] = A.g[i * NPAR + e];
-      double sc[NPAR], b[NPAR];
       eps = A.eps[i];
-      code = solve_cholesky(H, g, eps, A.free_mask, delta, sc, b);
+      code = solve_cholesky(H, g, eps, A.free_mask, delta);
     }
     for (unsigned long long fbm = __ballot(valid && code == 1); fbm != 0ull; fbm &= fbm - 1ull) {
       const int L = __ffsll((unsigned long long)fbm) - 1;
       const int64_t iL = base + L;
-      solve_eigen_wave(A.H + iL * 55, 1, A.g + iL * NPAR, 1, __shfl(eps, L), A.free_mask, sws,
-                       lane);
+      const bool eigen = solve_wave(A.H + iL * 55, 1, A.g + iL * NPAR, 1, __shfl(eps, L),
+                                    A.free_mask, sws, lane);
       if (lane == L) {
+        if (!eigen) code = 0;
 #pragma unroll
         for (int q = 0; q < NPAR; ++q) delta[q] = sws[200 + q];
       }
