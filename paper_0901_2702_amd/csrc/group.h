@@ -10,8 +10,8 @@
 namespace vfisv {
 
 // The synthesis points of an instrument in chunks of GROUP_PTS, one per lane
-// (the tables end with a whole chunk; padding points have offset 0 and no
-// taps), and their taps.
+// (the tables end with a whole chunk; padding points repeat the last one and
+// have no taps), and their taps.
 constexpr int GROUP_PTS = 64;
 struct GroupTables {
   const float* dl = nullptr;    // [n_chunk * GROUP_PTS] offsets, in record order (dense: 1 chunk)
@@ -35,6 +35,9 @@ static_assert(GROUP_LEFT_SLOT >= COUNTER_SLOTS, "a slot of its own");
 // room for eight waves' LDS on a CU, two per SIMD.
 constexpr int GROUP_SLOTS[2] = {8, 8};
 
+// Synthesis by waves of a few models; num_cus sizes the grid.
+hipError_t launch_synth_group(const SynthArgs& a, const GroupTables& t, int kind, bool deriv,
+                              int num_cus, hipStream_t s);
 hipError_t launch_lm_group(const GroupArgs& a, int kind, int grid, hipStream_t s);
 hipError_t lm_group_blocks_per_cu(int kind, int* out);
 

@@ -71,10 +71,12 @@ struct EqLds {
   double sc[NPAR];  // 1 / sqrt(H_pp), 0 for a frozen parameter
   float hg[66];     // H (packed) and g
 };
-struct alignas(16) SlotLds {
-  EqLds eq;
+struct alignas(16) ModelLds {
   float px[18];  // the fields of Pix that Weideman's series needs
   float rf[10];  // RowFactors
+};
+struct SlotLds : ModelLds {
+  EqLds eq;
 };
 
 template <bool BAND>
@@ -186,7 +188,7 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ void put_model(SlotLds& S, const Pix& p, const RowFactors& f) {
+__device__ __forceinline__ void put_model(ModelLds& S, const Pix& p, const RowFactors& f) {
   const float px[18] = {p.vsi, p.invD, p.zs, p.a,      p.denr, p.denr2, p.c0,  p.hs2,  p.hc,
                         p.hI,  p.hq,   p.hsin2g, p.hsg, p.s2h,  p.cgh,   p.eta0, p.alpha, p.oma};
   const float rf[10] = {f.S0, f.S1, f.alpha, f.S1a, f.c2p, f.s2p, f.fB, f.fg, f.fv, f.fD};
@@ -195,7 +197,7 @@ __device__ __forceinline__ void put_model(SlotLds& S, const Pix& p, const RowFac
 #pragma unroll
   for (int k = 0; k < 10; ++k) S.rf[k] = rf[k];
 }
-__device__ __forceinline__ Pix get_pix(const SlotLds& S) {
+__device__ __forceinline__ Pix get_pix(const ModelLds& S) {
   Pix p;
   float* const f[18] = {&p.vsi, &p.invD, &p.zs,     &p.a,   &p.denr, &p.denr2, &p.c0,   &p.hs2,
                         &p.hc,  &p.hI,   &p.hq,     &p.hsin2g, &p.hsg, &p.s2h, &p.cgh,  &p.eta0,
@@ -206,7 +208,7 @@ __device__ __forceinline__ Pix get_pix(const SlotLds& S) {
   p.a0 = p.da = 0.f;
   return p;
 }
-__device__ __forceinline__ RowFactors get_rf(const SlotLds& S) {
+__device__ __forceinline__ RowFactors get_rf(const ModelLds& S) {
   RowFactors r;
   r.S0 = S.rf[0];
   r.S1 = S.rf[1];
@@ -975,6 +977,330 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
     atomicAdd(&A.work[7], th);
     atomicAdd(&A.work[8], tj);
   }
+}
+
+// ---- synthesis -------------------------------------------------------------
+// The filtered Stokes vectors (and Jacobians) of given models by the same
+// split: a point per lane, `per` models per wave, whose set-up the lanes share
+// out.  A model per lane (synth_kernel) takes one lane's pass over all points
+// however few models there are, one wave per SIMD that waits out its own
+// latencies up to 65,536 models.  Bound by VALU issue from there on (620 wave
+// instructions per HMI model with its Jacobian, 2,100 per fine spectrum).
+// Measured, a model per lane -> here: 1,000 HMI models with Jacobian 66 -> 11
+// us, 65,537 172 -> 100; 30,011 fine spectra 406 -> 99, with Jacobian 937 ->
+// 380.  (Jacobian rows through LDS, to store whole lines, take as long.)
+namespace {
+
+constexpr int SYNTH_PER[2] = {32, 16};  // most models of a wave, per layout
+constexpr int DV = 8;                   // dense, values only: models assembled together
+static_assert(DV * NOBS_HMI <= 64 && DV % 4 == 0, "lanes of the assembly");
+
+// Row sums over the points with taps alone, for models whose contributions
+// are not all finite (a zero tap is no tap); columns m < n of c, rows of a.
+__device__ __noinline__ void sums_of_taps(const float* taps, const float* c, int n, float* a,
+                                          int astr, int cols, int lane) {
+  const int m = lane & 31;
+  if (m < n) {
+#pragma unroll 1
+    for (int r = lane >> 5; r < NOBS_HMI; r += 2) {
+      float s = 0.f;
+#pragma unroll 1
+      for (int k = 0; k < GROUP_PTS; ++k) {
+        const float w = taps[r * GROUP_PTS + k];
+        if (w != 0.f) s = fmaf(w, c[m * CSTR + k], s);
+      }
+      a[(m / cols) * (NOBS_HMI * astr) + r * astr + m % cols] = s;
+    }
+  }
+}
+__device__ __forceinline__ bool all_finite(f32x4 v) {
+  return __ballot(!isfinite((v[0] + v[1]) + (v[2] + v[3]))) == 0ull;
+}
+
+__device__ __forceinline__ void setup_models(const SynthArgs& A, ModelLds* rec, int64_t first,
+                                             int n, int lane) {
+  if (lane < n) {
+    float M[NPAR];
+#pragma unroll
+    for (int q = 0; q < NPAR; ++q) M[q] = A.params[(first + lane) * NPAR + q];
+    Pix px;
+    RowFactors rf;
+    pix_setup(M, A.C, px);
+    row_factors(M, px, A.C, rf);
+    put_model(rec[lane], px, rf);
+  }
+  wave_fence();
+}
+
+// A Stokes value (rounded, as stored without noise) and its noise.
+__device__ __forceinline__ float plus_noise(float S, float noise) {
+#pragma clang fp contract(off)
+  return S + noise;
+}
+__device__ __forceinline__ void store_jac(float* J, const float* v) {
+#pragma unroll
+  for (int p = 0; p < NPAR; ++p) J[p] = v[p];
+}
+
+}  // namespace
+
+// Dense: the rows of four models' values, or of one model's 29 quantities,
+// are one or two chains of 16 MFMAs (Layout<false>).
+template <bool DERIV>
+__global__ __launch_bounds__(64, DERIV ? 3 : 4) void synth_group_kernel(const SynthArgs A,
+                                                                        const GroupTables T,
+                                                                        int per) {
+  constexpr int NB = DERIV ? 2 : DV, NC = DERIV ? NACC : 16, AS = DERIV ? ASTR : 4;
+  __shared__ __align__(16) float c[NC * CSTR];
+  __shared__ __align__(16) float a[NB * NOBS_HMI * AS];
+  __shared__ ModelLds rec[SYNTH_PER[KIND_DENSE6]];
+  const int lane = threadIdx.x, col = lane & 15, kq = lane >> 4;
+  const int64_t first = (int64_t)blockIdx.x * per;
+  const int n = (int)(A.n - first < per ? A.n - first : per);
+  const float dl = T.dl[lane];
+  float tap[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float w = T.taps[(col < NOBS_HMI ? col : 0) * GROUP_PTS + 4 * i + kq];
+    tap[i] = col < NOBS_HMI ? w : 0.f;
+  }
+  // assembly: lane (model, Stokes parameter, row), the order of the outputs,
+  // or (model, row) without derivatives
+  constexpr int LM = DERIV ? 4 * NOBS_HMI : NOBS_HMI;
+  const int b = lane / LM, t = lane - b * LM, st = t / NOBS_HMI, row = t - st * NOBS_HMI;
+  float rs = A.C.row_sum[0];
+#pragma unroll
+  for (int k = 1; k < NOBS_HMI; ++k)
+    if (row == k) rs = A.C.row_sum[k];
+  setup_models(A, rec, first, n, lane);
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += NB) {
+    const bool mine = b < NB && k0 + b < n;
+    const int64_t out = (first + k0 + b) * (4 * NOBS_HMI) + t;
+    float noise[DERIV ? 1 : 4] = {};
+    if (A.noise && mine) {
+#pragma unroll
+      for (int i = 0; i < (DERIV ? 1 : 4); ++i) noise[i] = A.noise[out + i * NOBS_HMI];
+    }
+    if constexpr (DERIV) {
+#pragma unroll 1
+      for (int i = 0; i < NB && k0 + i < n; ++i) {
+        {
+          const Pix px = get_pix(rec[k0 + i]);
+          float v[NACC];
+          point_contrib<true>(dl, px, A.C, v);
+#pragma unroll
+          for (int q = 0; q < NACC; ++q) c[q * CSTR + lane] = v[q];
+        }
+        wave_fence();
+        const float* s0 = c + col * CSTR + kq;
+        const float* s1 = c + (col + 16 < NACC ? col + 16 : col) * CSTR + kq;
+        f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+#pragma unroll
+        for (int h = 0; h < 16; h += 8) {
+          float x[8], y[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            x[j] = s0[4 * (h + j)];
+            y[j] = s1[4 * (h + j)];
+          }
+          issued();
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            a0 = mfma4(tap[h + j], x[j], a0);
+            a1 = mfma4(tap[h + j], y[j], a1);
+          }
+        }
+        float* const ai = a + i * (NOBS_HMI * AS);
+        if (kq < 2) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (4 * kq + r >= NOBS_HMI) continue;
+            ai[(4 * kq + r) * AS + col] = a0[r];
+            if (col + 16 < NACC) ai[(4 * kq + r) * AS + col + 16] = a1[r];
+          }
+        }
+        if (!all_finite(a0) || !all_finite(a1))
+          sums_of_taps(T.taps, c, NACC, ai, AS, NACC, lane);
+        wave_fence();
+      }
+      if (mine) {
+        const RowFactors rf = get_rf(rec[k0 + b]);
+        float J[NPAR];
+        const float r = assemble_one(a + (b * NOBS_HMI + row) * AS, rs, rf, st, 0.f, J);
+        A.stokes[out] = A.noise ? plus_noise(-r, noise[0]) : -r;
+        store_jac(A.jac + out * NPAR, J);
+      }
+    } else {
+#pragma unroll 1
+      for (int h = 0; h < NB && k0 + h < n; h += 4) {
+#pragma unroll 1
+        for (int i = 0; i < 4 && k0 + h + i < n; ++i) {
+          const Pix px = get_pix(rec[k0 + h + i]);
+          float v[NACC];
+          point_contrib<false>(dl, px, A.C, v);
+          const float u[4] = {v[0], v[2], v[3], v[4]};  // what the Stokes values need
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c[(4 * i + q) * CSTR + lane] = u[q];
+        }
+        wave_fence();
+        const int cols = 4 * (n - k0 - h < 4 ? n - k0 - h : 4);
+        const float* src = c + (col < cols ? col : 0) * CSTR + kq;
+        float x[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = src[4 * j];
+        issued();
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s = mfma4(tap[j], x[j], s);
+        float* const ah = a + h * (NOBS_HMI * AS);
+        if (kq < 2 && col < cols) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (4 * kq + r < NOBS_HMI)
+              ah[((col >> 2) * NOBS_HMI + 4 * kq + r) * AS + (col & 3)] = s[r];
+        }
+        if (!all_finite(s)) sums_of_taps(T.taps, c, cols, ah, AS, 4, lane);
+        wave_fence();
+      }
+      if (mine) {
+        const float4 h = ld4(a + lane * AS);
+        const float av[5] = {h.x, 0.f, h.y, h.z, h.w};
+        const RowFactors rf = get_rf(rec[k0 + b]);
+        float Sv[4], J[4][NPAR];
+        assemble_sample<false>(av, rs, rf, Sv, J);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          A.stokes[out + i * NOBS_HMI] = A.noise ? plus_noise(Sv[i], noise[i]) : Sv[i];
+      }
+    }
+    wave_fence();
+  }
+}
+
+// Banded: a chunk's 16 rows over its window (Layout<true>), the values of VB
+// models at a time.
+template <bool DERIV>
+__global__ __launch_bounds__(64, DERIV ? 3 : 4) void synth_group_band_kernel(const SynthArgs A,
+                                                                             const GroupTables T,
+                                                                             int per) {
+  constexpr int NB = DERIV ? 1 : VB, NW = DERIV ? NACC : 4 * VB;
+  __shared__ __align__(16) float c[NW * WSTR];
+  __shared__ __align__(16) float tail[NW * BPREV];
+  __shared__ __align__(16) float a[BROWS * (DERIV ? BASTR : 4 * VB)];
+  __shared__ ModelLds rec[SYNTH_PER[KIND_BAND]];
+  const int lane = threadIdx.x, jr = lane & 15, s = lane >> 4, no = A.C.n_obs;
+  const int64_t first = (int64_t)blockIdx.x * per;
+  const int n = (int)(A.n - first < per ? A.n - first : per);
+  setup_models(A, rec, first, n, lane);
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += NB) {
+    for (int i = lane; i < NW * BPREV; i += 64) tail[i] = 0.f;
+    wave_fence();
+    const int nb = n - k0 < NB ? n - k0 : NB;
+    // values: lane (jr, s) assembles row jr of model s; derivatives: row jr of
+    // Stokes parameter s
+    const int kb = DERIV ? k0 : k0 + (s < nb ? s : 0);
+    const int64_t base = (first + kb) * (int64_t)(4 * no) + (DERIV ? s * no : 0);
+#pragma unroll 1
+    for (int ch = 0; ch < T.n_chunk; ++ch) {
+      const float dl = T.dl[ch * GROUP_PTS + lane];
+      const int j0 = ch * BROWS - (BAND_R - 1) + jr;
+      const bool valid = j0 >= 0 && j0 < no, mine = valid && (DERIV || s < nb);
+      const int j = valid ? j0 : 0;
+      float4 w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = ld4(T.taps + j * 16 + 4 * i);
+      const float rs = A.row_sums[j];
+      float noise[DERIV ? 1 : 4] = {};
+      if (A.noise && mine) {
+#pragma unroll
+        for (int i = 0; i < (DERIV ? 1 : 4); ++i) noise[i] = A.noise[base + i * no + j];
+      }
+      for (int i = lane; i < NW * (BPREV / 4); i += 64)
+        *reinterpret_cast<float4*>(c + (i / (BPREV / 4)) * WSTR + 4 * (i % (BPREV / 4))) =
+            ld4(tail + 4 * i);
+      wave_fence();
+      const auto row_sum = [&](const float* window) {
+        float4 x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = ld4(window + 4 * (jr + i));
+        float r = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r = fma4(w[i], x[i], r);
+        return r;
+      };
+#pragma unroll 1
+      for (int b = 0; b < nb; ++b) {
+        const Pix px = get_pix(rec[k0 + b]);
+        float v[NACC];
+        point_contrib<DERIV>(dl, px, A.C, v);
+        if constexpr (!DERIV) {  // what the Stokes values need
+          v[1] = v[2];
+          v[2] = v[3];
+          v[3] = v[4];
+        }
+        constexpr int NQ = DERIV ? NACC : 4;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) c[(NQ * b + i) * WSTR + BPREV + lane] = v[i];
+        if (lane >= GROUP_PTS - BPREV) {
+#pragma unroll
+          for (int i = 0; i < NQ; ++i)
+            tail[(NQ * b + i) * BPREV + lane - (GROUP_PTS - BPREV)] = v[i];
+        }
+      }
+      wave_fence();
+      if constexpr (DERIV) {
+        float r[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] = row_sum(c + (8 * s + i < NACC ? 8 * s + i : NACC - 1) * WSTR);
+        st4(a + jr * BASTR + 8 * s, r[0], r[1], r[2], r[3]);
+        st4(a + jr * BASTR + 8 * s + 4, r[4], r[5], r[6], r[7]);
+        wave_fence();
+        if (mine) {
+          const RowFactors rf = get_rf(rec[k0]);
+          float J[NPAR];
+          const float x = assemble_one(a + jr * BASTR, rs, rf, s, 0.f, J);
+          A.stokes[base + j] = A.noise ? plus_noise(-x, noise[0]) : -x;
+          store_jac(A.jac + (base + j) * NPAR, J);
+        }
+      } else {
+#pragma unroll 1
+        for (int b = 0; b < nb; ++b)
+          a[(b * BROWS + jr) * 4 + s] = row_sum(c + (4 * b + s) * WSTR);
+        wave_fence();
+        if (mine) {
+          const float4 h = ld4(a + lane * 4);
+          const float av[5] = {h.x, 0.f, h.y, h.z, h.w};
+          const RowFactors rf = get_rf(rec[kb]);
+          float Sv[4], J[4][NPAR];
+          assemble_sample<false>(av, rs, rf, Sv, J);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            A.stokes[base + i * no + j] = A.noise ? plus_noise(Sv[i], noise[i]) : Sv[i];
+        }
+      }
+      wave_fence();
+    }
+  }
+}
+
+hipError_t launch_synth_group(const SynthArgs& a, const GroupTables& t, int kind, bool deriv,
+                              int num_cus, hipStream_t s) {
+  // as many models per wave as leave the chip its waves (12 or 16 with
+  // Jacobian: 65,537 HMI models 106 or 119 us instead of 100)
+  const int64_t waves = (int64_t)num_cus * (deriv ? 8 : 16);
+  int64_t per = (a.n + waves - 1) / waves;
+  if (per > SYNTH_PER[kind]) per = SYNTH_PER[kind];
+  const int grid = (int)((a.n + per - 1) / per);
+  if (kind == KIND_BAND) {
+    if (deriv) synth_group_band_kernel<true><<<grid, 64, 0, s>>>(a, t, (int)per);
+    else synth_group_band_kernel<false><<<grid, 64, 0, s>>>(a, t, (int)per);
+  } else {
+    if (deriv) synth_group_kernel<true><<<grid, 64, 0, s>>>(a, t, (int)per);
+    else synth_group_kernel<false><<<grid, 64, 0, s>>>(a, t, (int)per);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_lm_group(const GroupArgs& a, int kind, int grid, hipStream_t s) {
