@@ -56,26 +56,21 @@ struct MlpDev {
   float* out_std;     // [7]
 };
 
-// Work buffers for a batch of M rows.
+// Work buffers of a training step of up to cap rows (a multiple of 32).
 struct MlpWork {
-  int64_t cap;        // rows
-  bf16* X0;           // [cap][K0]
-  bf16* X0t;          // [K0][cap]        (training)
-  bf16* Y[3];         // [cap][H]
-  bf16* Yt[3];        // [H][cap]         (training)
-  float* Z[3];        // [cap][H] pre-activations (training)
-  float* Y4;          // [cap][32]
-  bf16* dZ[4];        // [cap][H or 32]   (training)
-  bf16* dZt[4];       // [H or 32][cap]   (training)
-  float* dW;          // [SPLITK][max layer size] partial weight gradients
+  int64_t cap;
+  bf16* X0t;          // [K0][cap]  inputs, transposed
+  bf16* Yt[3];        // [H][cap]   activations
+  bf16* dZt[4];       // [H or 32][cap]  gradients of the pre-activations
+  float* dW;          // [SPLITK][layer size] partial weight gradients
   float* grad;        // [total] assembled gradient
   double* loss;       // [1]
 };
 
-hipError_t mlp_forward(const MlpDev& net, MlpWork& w, int64_t M, const float* stokes,
-                       const int32_t* rows, bool train, hipStream_t s);
-hipError_t mlp_decode(const MlpDev& net, const float* Y4, int64_t M, float* codes,
-                      float* params, hipStream_t s);
+// Forward and backward pass of a batch: adds the loss to *w.loss, leaves the
+// partial weight gradients in w.dW and the bias gradients in w.grad.
+hipError_t mlp_pass(const MlpDev& net, MlpWork& w, int64_t M, const float* stokes,
+                    const float* targets, const int32_t* rows, hipStream_t s);
 // Fused inference (inputs -> decoded codes/params in one kernel); LDS bytes
 // it needs for an input width K0.  The widest input it serves keeps its
 // 64-row tile within the 160 KB of LDS of a workgroup.
@@ -84,8 +79,6 @@ constexpr int MLP_MAX_IN = 1248;  // K0 + 8 padded columns, 64 rows, bf16
 hipError_t mlp_infer(const MlpDev& net, int64_t M, const float* stokes, float* codes,
                      float* params, hipStream_t s);
 size_t mlp_infer_lds_bytes(int K0);
-hipError_t mlp_backward(const MlpDev& net, MlpWork& w, int64_t M, const float* targets,
-                        const int32_t* rows, hipStream_t s);
 hipError_t mlp_adam(const MlpDev& net, const MlpWork& w, float lr, float beta1, float beta2,
                     float eps, int step, hipStream_t s);
 hipError_t mlp_refresh_bf16(const MlpDev& net, hipStream_t s);

@@ -9,13 +9,21 @@
 // parameters, trained on profiles synthesised by the library's own forward
 // model.
 //
-// Every GEMM is C = A . Bt^T with A [M][Kd] and Bt [N][Kd] both contiguous
+// Every product is C = A . Bt^T with A [M][Kd] and Bt [N][Kd] both contiguous
 // along Kd, so each lane fetches its 8-element MFMA fragments with one
 // 16-byte load:  forward  X [B][K] . Wt [N][K]^T;  input gradient
 // dZ [B][N] . W [K][N]^T;  weight gradient X^T [K][B] . dZ^T [N][B]^T (in the
 // [in][out] order of the master weights, so that the Adam kernel reads it
 // coalesced), split along the batch into MLP_SPLITK partial sums that the
 // Adam kernel adds.
+//
+// A training step is three launches.  Everything that concerns one row of the
+// batch (inputs, four layers, loss, the gradient down to the first layer's
+// pre-activation) runs in one workgroup per few rows, which leaves only the
+// transposed activations and gradients behind (train_rows_kernel); all weight
+// and bias gradients follow in one launch, and Adam.  One launch per product
+// and element-wise pass, 15 per step, spent 99 us of a step of 4,096 rows in
+// kernels of 3 to 10 us that mostly waited for their first loads.
 #include <hip/hip_runtime.h>
 
 #include "me_device.h"
@@ -60,84 +68,11 @@ __device__ __forceinline__ float gelu_grad(float z) {
   return fmaf(z * 0.39894228040143268f, f.e, f.Phi);
 }
 
-// ---- GEMM ------------------------------------------------------------------
-// One wave computes a 32 x 32 tile of C (2 x 2 MFMA tiles of 16 x 16) over
-// the Kd range [z * k_chunk, min((z + 1) * k_chunk, Kd)); Kd and k_chunk are
-// multiples of 32.  The fragments of KC k-steps are loaded before the first
-// MFMA of the group, so that one memory latency serves KC k-steps (the
-// 256-deep products of the hidden layers take one group).  MFMA 16x16x32
-// lane layout: lane l feeds A row (l & 15) and B column (l & 15) with
-// k = 8 (l >> 4) .. +7, and receives C rows 4 (l >> 4) .. +3 of column
-// (l & 15); the epilogue gets those four rows at once.
-constexpr int GT = 2;   // 16 x 16 MFMA tiles per wave along each of M and N
-constexpr int GKC = 8;  // k-steps loaded per group
-template <class Epi>
-__global__ __launch_bounds__(64) void gemm_abt(const bf16* __restrict__ A, int64_t lda,
-                                               const bf16* __restrict__ Bt, int64_t ldb,
-                                               int64_t M, int N, int64_t Kd, int64_t k_chunk,
-                                               Epi epi) {
-  const int l = threadIdx.x;
-  const int64_t m0 = (int64_t)blockIdx.x * 16 * GT;
-  const int n0 = blockIdx.y * 16 * GT;
-  const int64_t kbeg = (int64_t)blockIdx.z * k_chunk;
-  const int64_t kend = kbeg + k_chunk < Kd ? kbeg + k_chunk : Kd;
-  const int lr = l & 15, lk = (l >> 4) * 8;
-  f32x4 acc[GT][GT];
-#pragma unroll
-  for (int rb = 0; rb < GT; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < GT; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 zero;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) zero[i] = (bf16)0.f;
-  const bf16* arow[GT];
-  const bf16* bcol[GT];
-  bool aok[GT], bok[GT];
-#pragma unroll
-  for (int t = 0; t < GT; ++t) {
-    const int64_t row = m0 + t * 16 + lr;
-    const int col = n0 + t * 16 + lr;
-    aok[t] = row < M;
-    bok[t] = col < N;
-    arow[t] = A + (aok[t] ? row : 0) * lda + lk;
-    bcol[t] = Bt + (int64_t)(bok[t] ? col : 0) * ldb + lk;
-  }
-  for (int64_t k0 = kbeg; k0 < kend; k0 += 32 * GKC) {
-    bf16x8 a[GKC][GT], b[GKC][GT];
-#pragma unroll
-    for (int kc = 0; kc < GKC; ++kc) {
-      const int64_t k = k0 + 32 * kc;
-      const bool kin = k < kend;
-#pragma unroll
-      for (int t = 0; t < GT; ++t) {
-        a[kc][t] = kin && aok[t] ? *(const bf16x8*)(arow[t] + k) : zero;
-        b[kc][t] = kin && bok[t] ? *(const bf16x8*)(bcol[t] + k) : zero;
-      }
-    }
-#pragma unroll
-    for (int kc = 0; kc < GKC; ++kc) {
-      if (k0 + 32 * kc >= kend) break;  // wave-uniform
-#pragma unroll
-      for (int rb = 0; rb < GT; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < GT; ++cb)
-          acc[rb][cb] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kc][rb], b[kc][cb], acc[rb][cb], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int rb = 0; rb < GT; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < GT; ++cb) {
-      const int64_t row0 = m0 + rb * 16 + (l >> 4) * 4;
-      const int col = n0 + cb * 16 + lr;
-      if (row0 < M && col < N) epi(row0, col, acc[rb][cb], blockIdx.z);
-    }
-}
-
-// Epilogues receive the four rows row0 .. row0 + 3 (M is a multiple of 32,
-// so all four exist) of one column.  Transposed copies store the four
-// consecutive values with one 8-byte write.
+// ---- training: rows ----------------------------------------------------------
+// MFMA 16x16x32 lane layout: lane l feeds A row (l & 15) and B column (l & 15)
+// with k = 8 (l >> 4) .. +7, and receives C rows 4 (l >> 4) .. +3 of column
+// (l & 15).  Each element is one chain of MFMAs over ascending k.
+// Transposed copies store four consecutive rows with one 8-byte write.
 __device__ __forceinline__ void store4_bf16(bf16* p, float v0, float v1, float v2, float v3) {
   typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
   bf16x4 v;
@@ -148,144 +83,355 @@ __device__ __forceinline__ void store4_bf16(bf16* p, float v0, float v1, float v
   *(bf16x4*)p = v;
 }
 
-struct EpiHidden {  // z = acc + b; y = gelu(z)
-  const float* bias;
-  bf16* Y;
-  bf16* Yt;
-  float* Z;
-  int64_t ld, ldt;
-  __device__ void operator()(int64_t row0, int col, f32x4 acc, int) const {
-    float y[4];
+constexpr int LDH = MLP_H + 8;  // row of 256 activations in LDS
+constexpr int TW = 8;           // waves of a workgroup; wave w owns columns [32 w, 32 w + 32)
+constexpr int TCB = MLP_H / (16 * TW);
+constexpr int LDZ = MLP_OUT + 8;
+
+struct TrainRowsArgs {
+  const float* stokes;
+  const int32_t* rows;  // batch row -> sample (nullptr: the same)
+  const float* targets;
+  int64_t M, cap;
+  int n_in, K0;
+  const float* mean;
+  const float* istd;
+  const bf16* Wt[4];
+  const bf16* Wk[4];
+  const float* bias[4];
+  bf16* X0t;
+  bf16* Yt[3];
+  bf16* dZt[4];
+  double* loss;
+};
+
+// This wave's fragments of NK k-steps of a weight matrix (rows of ld).
+template <int NK>
+struct TrainW {
+  bf16x8 f[NK][TCB];
+  __device__ __forceinline__ void fetch(const bf16* W, int ld, int wave, int l) {
+    const bf16* p = W + (int64_t)(wave * 16 * TCB + (l & 15)) * ld + (l >> 4) * 8;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float z = acc[j] + bias[col];
-      if (Z) Z[(row0 + j) * ld + col] = z;
-      y[j] = gelu(z);
-      Y[(row0 + j) * ld + col] = (bf16)y[j];
-    }
-    if (Yt) store4_bf16(Yt + (int64_t)col * ldt + row0, y[0], y[1], y[2], y[3]);
+    for (int s = 0; s < NK; ++s)
+#pragma unroll
+      for (int cb = 0; cb < TCB; ++cb) f[s][cb] = *(const bf16x8*)(p + (int64_t)cb * 16 * ld + 32 * s);
   }
 };
 
-struct EpiOut {  // linear output layer
-  const float* bias;
-  float* Y4;
-  __device__ void operator()(int64_t row0, int col, f32x4 acc, int) const {
+template <int RB, int NK>
+__device__ __forceinline__ void train_product(const bf16* in, int ldin, const TrainW<NK>& w,
+                                              f32x4 (&acc)[RB][TCB], int l) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) Y4[(row0 + j) * MLP_OUT + col] = acc[j] + bias[col];
-  }
-};
-
-struct EpiBwdX {  // dz_prev = (dZ . W^T) * gelu'(z_prev)
-  const float* Zp;
-  bf16* dZ;
-  bf16* dZt;
-  int64_t ld, ldt;
-  __device__ void operator()(int64_t row0, int col, f32x4 acc, int) const {
-    float d[4];
+  for (int s = 0; s < NK; ++s) {
+    bf16x8 a[RB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      d[j] = acc[j] * gelu_grad(Zp[(row0 + j) * ld + col]);
-      dZ[(row0 + j) * ld + col] = (bf16)d[j];
-    }
-    store4_bf16(dZt + (int64_t)col * ldt + row0, d[0], d[1], d[2], d[3]);
-  }
-};
-
-struct EpiDW {  // partial weight gradient, [split][in][out]
-  float* part;
-  int64_t split_stride;
-  int ldo;
-  __device__ void operator()(int64_t row0, int col, f32x4 acc, int z) const {
+    for (int rb = 0; rb < RB; ++rb)
+      a[rb] = *(const bf16x8*)(in + (rb * 16 + (l & 15)) * ldin + 32 * s + (l >> 4) * 8);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) part[(int64_t)z * split_stride + (row0 + j) * ldo + col] = acc[j];
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < TCB; ++cb)
+        acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb], w.f[s][cb], acc[rb][cb], 0, 0, 0);
   }
-};
-
-template <class Epi>
-static hipError_t gemm(const bf16* A, int64_t lda, const bf16* Bt, int64_t ldb, int64_t M, int N,
-                       int64_t Kd, int splits, const Epi& e, hipStream_t s) {
-  const int64_t chunk = ((Kd + splits - 1) / splits + 31) / 32 * 32;
-  dim3 grid((unsigned)((M + 16 * GT - 1) / (16 * GT)), (unsigned)((N + 16 * GT - 1) / (16 * GT)),
-            (unsigned)splits);
-  gemm_abt<Epi><<<grid, 64, 0, s>>>(A, lda, Bt, ldb, M, N, Kd, chunk, e);
-  return hipGetLastError();
 }
 
-// ---- element-wise kernels --------------------------------------------------
-
-__global__ void encode_kernel(const float* __restrict__ stokes, const int32_t* __restrict__ rows,
-                              int64_t M, int n_in, int K0, const float* __restrict__ mean,
-                              const float* __restrict__ istd, bf16* X0, bf16* X0t, int64_t cap) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= M * K0) return;
-  const int64_t m = t / K0;
-  const int k = (int)(t - m * K0);
-  const int64_t src = rows ? (int64_t)rows[m] : m;
-  const float x = k < n_in ? (stokes[src * n_in + k] - mean[k]) * istd[k] : 0.f;
-  const bf16 xb = (bf16)x;
-  X0[m * K0 + k] = xb;
-  if (X0t) X0t[(int64_t)k * cap + m] = xb;
+// out[rb][cb] = f(acc, index) as bfloat16, to the tile h and transposed to t
+template <int RB, class F>
+__device__ __forceinline__ void train_epilogue(const f32x4 (&acc)[RB][TCB], bf16* h, bf16* t,
+                                               int64_t cap, int64_t m0, int wave, int l, F f) {
+#pragma unroll
+  for (int cb = 0; cb < TCB; ++cb) {
+    const int col = wave * 16 * TCB + cb * 16 + (l & 15);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int row = rb * 16 + (l >> 4) * 4;
+      float v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[j] = f(acc[rb][cb][j], rb, cb, j);
+        if (h) h[(row + j) * LDH + col] = (bf16)v[j];
+      }
+      store4_bf16(t + (int64_t)col * cap + m0 + row, v[0], v[1], v[2], v[3]);
+    }
+  }
 }
 
-__global__ void loss_grad_kernel(const float* __restrict__ Y4, const float* __restrict__ T,
-                                 const int32_t* __restrict__ rows, int64_t M, int64_t cap,
-                                 bf16* dZ, bf16* dZt, double* loss) {
-  __shared__ float red[256];
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  float d2 = 0.f;
-  if (t < M * MLP_OUT) {
-    const int64_t m = t / MLP_OUT;
-    const int c = (int)(t - m * MLP_OUT);
-    float d = 0.f;
-    if (c < MLP_NCODE) {
-      const int64_t src = rows ? (int64_t)rows[m] : m;
-      d = Y4[m * MLP_OUT + c] - T[src * MLP_NCODE + c];
-    }
-    d2 = d * d;
-    const bf16 g = (bf16)(2.f * d / (float)(M * MLP_NCODE));
-    dZ[m * MLP_OUT + c] = g;
-    dZt[(int64_t)c * cap + m] = g;
+constexpr int64_t TRAIN_RB2_ROWS = 131072;
+template <int RB>
+constexpr size_t train_lds_bytes(int K0) {
+  const size_t R = 16 * RB;
+  return R * (sizeof(bf16) * (K0 + 8 + 2 * LDH + LDZ) + sizeof(float) * (MLP_OUT + 1 + MLP_OUT));
+}
+
+// 16 RB rows per workgroup.  Bound by its own chain of seven dependent
+// products and by the weights' way from L2 (560 KB per workgroup): a layer's
+// weights are fetched two products ahead into registers, pre-activations stay
+// there (in float32) for the way back.  256 workgroups for a batch of 4,096
+// (RB = 1); RB = 2 halves the weights' reads, which tells only where they are
+// the larger part of the traffic: 524,288 rows 4.3 ms with RB = 1, 4.05 with
+// RB = 2, 65,536 equal, 16,384 138 us against 142.
+template <int RB>
+__global__ __launch_bounds__(TW * 64, 2) void train_rows_kernel(const TrainRowsArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int R = 16 * RB, NT = TW * 64;
+  const int ldx = a.K0 + 8;
+  bf16* const xs = (bf16*)smem;   // [R][K0 + 8]
+  bf16* const h0 = xs + R * ldx;  // [R][LDH]
+  bf16* const h1 = h0 + R * LDH;
+  bf16* const dz = h1 + R * LDH;  // [R][LDZ]
+  float* const y4 = (float*)(dz + R * LDZ);  // [R][MLP_OUT + 1]
+  float* const red = y4 + R * (MLP_OUT + 1); // [R * MLP_OUT]
+  const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63;
+  // neighbouring rows on one XCD: they share the transposed outputs' lines
+  const unsigned nb = gridDim.x, b = blockIdx.x;
+  const int64_t m0 = (int64_t)(nb % 8 == 0 ? (b % 8) * (nb / 8) + b / 8 : b) * R;
+  constexpr int NH = MLP_H / 32;
+  TrainW<1> w1;
+  TrainW<NH> wa, wb;
+  const bool one_step = a.K0 == 32;
+  // inputs, and the targets of this thread's outputs
+  for (int i = tid; i < R * a.K0; i += NT) {
+    const int r = i / a.K0, k = i - r * a.K0;
+    const int64_t src = a.rows ? (int64_t)a.rows[m0 + r] : m0 + r;
+    const float x = k < a.n_in ? (a.stokes[src * a.n_in + k] - a.mean[k]) * a.istd[k] : 0.f;
+    xs[r * ldx + k] = (bf16)x;
   }
-  red[threadIdx.x] = d2;
+  float target[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int e = tid + NT * i, r = e / MLP_OUT, c = e % MLP_OUT;
+    const int64_t src = a.rows ? (int64_t)a.rows[m0 + r] : m0 + r;
+    target[i] = c < MLP_NCODE ? a.targets[src * MLP_NCODE + c] : 0.f;
+  }
+  if (one_step) w1.fetch(a.Wt[0], 32, wave, l);
+  float bias[3][TCB];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int cb = 0; cb < TCB; ++cb) bias[i][cb] = a.bias[i][wave * 16 * TCB + cb * 16 + (l & 15)];
+  wa.fetch(a.Wt[1], MLP_H, wave, l);
   __syncthreads();
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
+  wb.fetch(a.Wt[2], MLP_H, wave, l);
+  for (int i = tid; i < a.K0 * (R / 8); i += NT) {
+    const int k = i / (R / 8), g = 8 * (i % (R / 8));
+    bf16x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = xs[(g + j) * ldx + k];
+    *(bf16x8*)(a.X0t + (int64_t)k * a.cap + m0 + g) = v;
   }
-  if (threadIdx.x == 0) atomicAdd(loss, (double)red[0]);
+  float z[3][RB][TCB][4];
+  const auto zero = [](f32x4 (&acc)[RB][TCB]) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < TCB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  f32x4 acc[RB][TCB];
+  // first layer: xs -> h0
+  zero(acc);
+  if (one_step) {
+    train_product<RB, 1>(xs, ldx, w1, acc, l);
+  } else {
+    for (int k = 0; k < a.K0; k += 32) {
+      w1.fetch(a.Wt[0] + k, a.K0, wave, l);
+      train_product<RB, 1>(xs + k, ldx, w1, acc, l);
+    }
+  }
+  const auto hidden = [&](int layer, bf16* h) {
+    train_epilogue<RB>(acc, h, a.Yt[layer], a.cap, m0, wave, l, [&](float c, int rb, int cb, int j) {
+      z[layer][rb][cb][j] = c + bias[layer][cb];
+      return gelu(z[layer][rb][cb][j]);
+    });
+  };
+  const auto back = [&](int layer, bf16* h) {
+    train_epilogue<RB>(acc, h, a.dZt[layer], a.cap, m0, wave, l, [&](float c, int rb, int cb, int j) {
+      return c * gelu_grad(z[layer][rb][cb][j]);
+    });
+  };
+  hidden(0, h0);
+  __syncthreads();
+  // second layer: h0 -> h1
+  zero(acc);
+  train_product<RB, NH>(h0, LDH, wa, acc, l);
+  wa.fetch(a.Wk[2], MLP_H, wave, l);
+  hidden(1, h1);
+  __syncthreads();
+  // third layer: h1 -> h0
+  zero(acc);
+  train_product<RB, NH>(h1, LDH, wb, acc, l);
+  // the output layer's products: waves 0 .. 2 RB - 1, a tile each
+  const bool out_wave = wave < 2 * RB;
+  const int out_col = (wave & 1) * 16 + (l & 15);
+  bf16x8 wo[NH];
+  if (out_wave) {
+#pragma unroll
+    for (int s = 0; s < NH; ++s)
+      wo[s] = *(const bf16x8*)(a.Wt[3] + (int64_t)out_col * MLP_H + 32 * s + (l >> 4) * 8);
+  }
+  w1.fetch(a.Wk[3], MLP_OUT, wave, l);
+  hidden(2, h0);
+  __syncthreads();
+  if (out_wave) {
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    const int r0 = (wave >> 1) * 16;
+#pragma unroll
+    for (int s = 0; s < NH; ++s)
+      o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          *(const bf16x8*)(h0 + (r0 + (l & 15)) * LDH + 32 * s + (l >> 4) * 8), wo[s], o, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      y4[(r0 + (l >> 4) * 4 + j) * (MLP_OUT + 1) + out_col] = o[j] + a.bias[3][out_col];
+  }
+  wb.fetch(a.Wk[1], MLP_H, wave, l);
+  __syncthreads();
+  // loss and its gradient
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int e = tid + NT * i, r = e / MLP_OUT, c = e % MLP_OUT;
+    const float d = c < MLP_NCODE ? y4[r * (MLP_OUT + 1) + c] - target[i] : 0.f;
+    red[e] = d * d;
+    dz[r * LDZ + c] = (bf16)(2.f * d / (float)(a.M * MLP_NCODE));
+  }
+  __syncthreads();
+  if (wave < R / 8) {  // 8 rows' squares, halved pairwise from 128 apart down to neighbours
+    const float* q = red + 256 * wave + l;
+    float s = (q[0] + q[128]) + (q[64] + q[192]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_down(s, off);
+    if (l == 0) atomicAdd(a.loss, (double)s);
+  }
+  for (int i = tid; i < MLP_OUT * (R / 8); i += NT) {
+    const int c = i / (R / 8), g = 8 * (i % (R / 8));
+    bf16x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = dz[(g + j) * LDZ + c];
+    *(bf16x8*)(a.dZt[3] + (int64_t)c * a.cap + m0 + g) = v;
+  }
+  // back through the output layer, dz -> h1, and the third and second, h1 -> h0 -> out
+  zero(acc);
+  train_product<RB, 1>(dz, LDZ, w1, acc, l);
+  back(2, h1);
+  __syncthreads();
+  zero(acc);
+  train_product<RB, NH>(h1, LDH, wa, acc, l);
+  back(1, h0);
+  __syncthreads();
+  zero(acc);
+  train_product<RB, NH>(h0, LDH, wb, acc, l);
+  back(0, nullptr);
 }
 
-// db[n] = sum over the batch of dZ^T[n][:].  One block of 256 threads per
-// column; the batch dimension is contiguous, so each thread reads 8 values
-// per load (M and cap are multiples of 32: 16-byte aligned rows), then a
-// wave reduction and one LDS step combine the 256 partial sums.
-// All four layers in one launch: block b takes column b - first[l] of the
-// layer l whose columns it falls in.
-struct BiasGradArgs {
+// ---- training: weight and bias gradients ------------------------------------
+// One launch for all four layers.  Weights: dW[in][out] = X^T[in][B] .
+// dZ^T[out][B]^T, a wave per 32 x 32 tile and batch chunk (2 x 2 MFMA tiles;
+// the fragments of KC k-steps are loaded before the first MFMA of the group,
+// so that one memory latency serves them all).  Biases: db[n] = sum of
+// dZ^T[n][:], a workgroup per column; the batch dimension is contiguous, so
+// each thread reads 8 values per load (M and cap are multiples of 32: 16-byte
+// aligned rows), then a wave reduction and one LDS step combine the 256
+// partial sums.  (A wave per column: 17.4 us instead of 15.2 for 4,096 rows.)
+constexpr int GT = 2;   // 16 x 16 MFMA tiles per wave along each of in and out
+constexpr int GKC = 8;  // k-steps loaded per group
+constexpr int GRAD_XCDS = 8;
+static_assert(MLP_SPLITK % GRAD_XCDS == 0, "chunks per XCD");
+// workgroups of four tiles per XCD
+__host__ __device__ constexpr int grad_blocks(int n_tiles) {
+  return (n_tiles * (MLP_SPLITK / GRAD_XCDS) + 3) / 4;
+}
+struct GradArgs {
+  const bf16* Xt[4];
   const bf16* dZt[4];
+  float* part[4];  // [split][in][out]
   float* grad_b[4];
-  int first[5];  // first block of each layer; first[4] = total columns
+  int in_dim[4], out_dim[4];
+  int first_tile[5];  // first tile of each layer (of one chunk); then the total
+  int first_col[5];   // first bias column of each layer; then the total
+  int64_t M, cap, chunk;
 };
 
-__global__ __launch_bounds__(256) void bias_grad_kernel(const BiasGradArgs a, int64_t M,
-                                                        int64_t cap) {
+__device__ __forceinline__ void weight_grad_tile(const GradArgs& a, int tile, int split,
+                                                 int l) {
+  int q = 0;
+#pragma unroll
+  for (int i = 1; i < 4; ++i) q = tile >= a.first_tile[i] ? i : q;
+  const int t = tile - a.first_tile[q], nn = a.out_dim[q] / (16 * GT);
+  const int n0 = t % nn * 16 * GT, m0 = t / nn * 16 * GT;
+  const int64_t kbeg = split * a.chunk;
+  const int64_t kend = kbeg + a.chunk < a.M ? kbeg + a.chunk : a.M;
+  const int lr = l & 15, lk = (l >> 4) * 8;
+  const bf16* arow = a.Xt[q] + (int64_t)(m0 + lr) * a.cap + lk;
+  const bf16* bcol = a.dZt[q] + (int64_t)(n0 + lr) * a.cap + lk;
+  f32x4 acc[GT][GT];
+#pragma unroll
+  for (int rb = 0; rb < GT; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < GT; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 zero;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) zero[i] = (bf16)0.f;
+  for (int64_t k0 = kbeg; k0 < kend; k0 += 32 * GKC) {
+    bf16x8 x[GKC][GT], y[GKC][GT];
+#pragma unroll
+    for (int kc = 0; kc < GKC; ++kc) {
+      const int64_t k = k0 + 32 * kc;
+#pragma unroll
+      for (int i = 0; i < GT; ++i) {
+        x[kc][i] = k < kend ? *(const bf16x8*)(arow + 16 * i * a.cap + k) : zero;
+        y[kc][i] = k < kend ? *(const bf16x8*)(bcol + 16 * i * a.cap + k) : zero;
+      }
+    }
+#pragma unroll
+    for (int kc = 0; kc < GKC; ++kc) {
+      if (k0 + 32 * kc >= kend) break;  // wave-uniform
+#pragma unroll
+      for (int rb = 0; rb < GT; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < GT; ++cb)
+          acc[rb][cb] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[kc][rb], y[kc][cb], acc[rb][cb], 0, 0, 0);
+    }
+  }
+  float* part = a.part[q] + (int64_t)split * a.in_dim[q] * a.out_dim[q];
+#pragma unroll
+  for (int rb = 0; rb < GT; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < GT; ++cb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        part[(int64_t)(m0 + rb * 16 + (l >> 4) * 4 + j) * a.out_dim[q] + n0 + cb * 16 + lr] =
+            acc[rb][cb][j];
+}
+
+__global__ __launch_bounds__(256) void grad_kernel(const GradArgs a) {
   __shared__ float red[4];
-  int l = 0;
-  while (l < 3 && (int)blockIdx.x >= a.first[l + 1]) ++l;
-  const int n = (int)blockIdx.x - a.first[l];
-  float* grad_b = a.grad_b[l];
-  const bf16* row = a.dZt[l] + (int64_t)n * cap;
+  // (the wave's number as a scalar: the layer's tables are read once, by it)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  // the batch chunks of an XCD's workgroups are its own (workgroups go to the
+  // XCDs in turn): an XCD reads an eighth of the batch, not all of it
+  const int n_tiles = a.first_tile[4], tile_blocks = GRAD_XCDS * grad_blocks(n_tiles);
+  if ((int)blockIdx.x < tile_blocks) {
+    const int t = 4 * ((int)blockIdx.x / GRAD_XCDS) + wave, i = t / n_tiles;
+    if (i < MLP_SPLITK / GRAD_XCDS)
+      weight_grad_tile(a, t - i * n_tiles,
+                       (int)blockIdx.x % GRAD_XCDS * (MLP_SPLITK / GRAD_XCDS) + i, l);
+    return;
+  }
+  const int c = (int)blockIdx.x - tile_blocks;
+  int q = 0;
+#pragma unroll
+  for (int i = 1; i < 4; ++i) q = c >= a.first_col[i] ? i : q;
+  const int n = c - a.first_col[q];
+  const bf16* row = a.dZt[q] + (int64_t)n * a.cap;
   float s = 0.f;
-  for (int64_t m = (int64_t)threadIdx.x * 8; m < M; m += 256 * 8) {
+  for (int64_t m = (int64_t)threadIdx.x * 8; m < a.M; m += 256 * 8) {
     const bf16x8 v = *reinterpret_cast<const bf16x8*>(row + m);
 #pragma unroll
     for (int k = 0; k < 8; ++k) s += (float)v[k];
   }
   for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  if (l == 0) red[wave] = s;
   __syncthreads();
-  if (threadIdx.x == 0) grad_b[n] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (threadIdx.x == 0) a.grad_b[q][n] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 struct AdamArgs {
@@ -298,42 +444,59 @@ struct AdamArgs {
   bf16* Wk[4];
   int64_t oW[4], ob[4];
   int in_dim[4], out_dim[4];
-  int64_t split_stride[4];
-  int64_t total;
+  int first_tile[5];  // first tile of each layer's weights; then the total
+  int first_col[5];   // first bias of each layer; then the total
   float lr, beta1, beta2, eps, bc1, bc2;
   int update;  // 0: only assemble the gradient
 };
 
-__global__ void adam_kernel(const AdamArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.total) return;
-  int l = 0;
-  while (l < 3 && i >= a.oW[l + 1]) ++l;
-  float g;
-  const bool is_w = i < a.ob[l];
-  int k = 0, n = 0;
-  if (is_w) {
-    const int64_t e = i - a.oW[l];
-    k = (int)(e / a.out_dim[l]);
-    n = (int)(e - (int64_t)k * a.out_dim[l]);
-    g = 0.f;
-    for (int s = 0; s < MLP_SPLITK; ++s)
-      g += a.part[l][(int64_t)s * a.split_stride[l] + e];
-    a.grad[i] = g;
-  } else {
-    g = a.grad[i];  // written by bias_grad_kernel
-  }
-  if (!a.update) return;
+__device__ __forceinline__ float adam_update(const AdamArgs& a, int64_t i, float g) {
   const float m = a.beta1 * a.m[i] + (1.f - a.beta1) * g;
   const float v = a.beta2 * a.v[i] + (1.f - a.beta2) * g * g;
   a.m[i] = m;
   a.v[i] = v;
   const float w = a.master[i] - a.lr * (m / a.bc1) / (sqrtf(v / a.bc2) + a.eps);
   a.master[i] = w;
-  if (is_w) {
-    a.Wt[l][(int64_t)n * a.in_dim[l] + k] = (bf16)w;
-    a.Wk[l][(int64_t)k * a.out_dim[l] + n] = (bf16)w;
+  return w;
+}
+
+// A workgroup per 8 x 32 tile of a layer's weights (ADAM_K inputs, ADAM_N
+// outputs, so that the transposed bfloat16 copy goes out in 16-byte pieces
+// instead of single values), then one per 256 biases.
+constexpr int ADAM_K = 8, ADAM_N = 32;
+__global__ __launch_bounds__(256) void adam_kernel(const AdamArgs a) {
+  __shared__ __align__(16) bf16 wt[ADAM_N * ADAM_K];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  if (b >= a.first_tile[4]) {
+    const int c = (b - a.first_tile[4]) * 256 + tid;
+    if (c >= a.first_col[4] || !a.update) return;
+    int64_t i = a.ob[0] + c;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) i = c >= a.first_col[q] ? a.ob[q] + (c - a.first_col[q]) : i;
+    adam_update(a, i, a.grad[i]);  // (written by grad_kernel)
+    return;
   }
+  int q = 0;
+#pragma unroll
+  for (int i = 1; i < 4; ++i) q = b >= a.first_tile[i] ? i : q;
+  const int t = b - a.first_tile[q], in = a.in_dim[q], out = a.out_dim[q], nn = out / ADAM_N;
+  const int k = t / nn * ADAM_K + tid / ADAM_N, n = t % nn * ADAM_N + tid % ADAM_N;
+  const int64_t e = (int64_t)k * out + n, i = a.oW[q] + e;
+  const float* part = a.part[q] + e;
+  float x[MLP_SPLITK], g = 0.f;
+#pragma unroll
+  for (int s = 0; s < MLP_SPLITK; ++s) x[s] = part[(int64_t)s * in * out];
+#pragma unroll
+  for (int s = 0; s < MLP_SPLITK; ++s) g += x[s];
+  a.grad[i] = g;
+  if (!a.update) return;
+  const float w = adam_update(a, i, g);
+  a.Wk[q][e] = (bf16)w;
+  wt[(tid % ADAM_N) * ADAM_K + tid / ADAM_N] = (bf16)w;
+  __syncthreads();
+  if (tid < ADAM_N)
+    *(bf16x8*)(a.Wt[q] + (int64_t)(t % nn * ADAM_N + tid) * in + t / nn * ADAM_K) =
+        *(const bf16x8*)(wt + tid * ADAM_K);
 }
 
 struct RefreshArgs {
@@ -379,15 +542,6 @@ __device__ __forceinline__ void decode_row(const float* y_in, const float* __res
   for (int c = 0; c < NPAR; ++c) params[c] = (float)P[c];
 }
 
-__global__ void decode_kernel(const float* __restrict__ Y4, int64_t M,
-                              const float* __restrict__ out_mean,
-                              const float* __restrict__ out_std, float* codes, float* params) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  decode_row(Y4 + m * MLP_OUT, out_mean, out_std, codes ? codes + m * MLP_NCODE : nullptr,
-             params ? params + m * NPAR : nullptr);
-}
-
 // ---- fused inference ---------------------------------------------------------
 // One workgroup of four waves carries FT rows through the whole network:
 // standardised inputs and hidden activations stay in one LDS tile
@@ -398,11 +552,9 @@ __global__ void decode_kernel(const float* __restrict__ Y4, int64_t M,
 // hidden columns [64 w, 64 w + 64) and output rows [16 w, 16 w + 16).
 // (128-row tiles would halve the weight reads but need 335 registers per
 // lane, one wave per SIMD: measured 1.5x slower.)  The MFMA sequence per
-// output element
-// (same instruction, same k order, same epilogue) is that of gemm_abt, so
-// the results equal those of the layer-by-layer path.
+// output element (same instruction, same k order, same epilogue) is that of
+// the training step's forward pass, so the results are equal.
 constexpr int FT = 64;
-constexpr int LDH = MLP_H + 8;
 // waves per inference workgroup; each owns IW_COLS of a hidden layer's 256
 // columns for the tile's 64 rows (eight waves keep the registers per wave
 // low enough for four waves per SIMD, which hide the weight loads' latency)
@@ -857,35 +1009,6 @@ __global__ void fallback_merge_kernel(const int32_t* __restrict__ list,
 
 static unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
-hipError_t mlp_forward(const MlpDev& net, MlpWork& w, int64_t M, const float* stokes,
-                       const int32_t* rows, bool train, hipStream_t s) {
-  const MlpLayout& L = net.L;
-  encode_kernel<<<blocks_for(M * L.K0, 256), 256, 0, s>>>(
-      stokes, rows, M, L.n_in, L.K0, net.in_mean, net.in_istd, w.X0, train ? w.X0t : nullptr,
-      w.cap);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const bf16* X = w.X0;
-  int64_t ldx = L.K0;
-  for (int l = 0; l < 3; ++l) {
-    EpiHidden ep{net.master + L.ob[l], w.Y[l], train ? w.Yt[l] : nullptr,
-                 train ? w.Z[l] : nullptr, MLP_H, w.cap};
-    e = gemm(X, ldx, net.Wt[l], L.in_dim[l], M, MLP_H, L.in_dim[l], 1, ep, s);
-    if (e != hipSuccess) return e;
-    X = w.Y[l];
-    ldx = MLP_H;
-  }
-  EpiOut eo{net.master + L.ob[3], w.Y4};
-  return gemm(X, ldx, net.Wt[3], MLP_H, M, MLP_OUT, MLP_H, 1, eo, s);
-}
-
-hipError_t mlp_decode(const MlpDev& net, const float* Y4, int64_t M, float* codes, float* params,
-                      hipStream_t s) {
-  decode_kernel<<<blocks_for(M, 256), 256, 0, s>>>(Y4, M, net.out_mean, net.out_std, codes,
-                                                   params);
-  return hipGetLastError();
-}
-
 __global__ void copy_u64_kernel(unsigned long long* dst, const unsigned long long* src, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
     dst[i] = src[i];
@@ -1011,40 +1134,63 @@ hipError_t sq_diff_sum(const float* A, const float* B, int64_t count, double* ou
   return hipGetLastError();
 }
 
-hipError_t mlp_backward(const MlpDev& net, MlpWork& w, int64_t M, const float* targets,
-                        const int32_t* rows, hipStream_t s) {
-  const MlpLayout& L = net.L;
-  loss_grad_kernel<<<blocks_for(M * MLP_OUT, 256), 256, 0, s>>>(
-      w.Y4, targets, rows, M, w.cap, w.dZ[3], w.dZt[3], w.loss);
-  hipError_t e = hipGetLastError();
+template <int RB>
+static hipError_t launch_train_rows(const TrainRowsArgs& a, hipStream_t s) {
+  const size_t lds = train_lds_bytes<RB>(a.K0);
+  hipError_t e = hipSuccess;
+  if (lds > 64 * 1024)
+    e = hipFuncSetAttribute((const void*)train_rows_kernel<RB>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, MLP_LDS_MAX);
   if (e != hipSuccess) return e;
-  for (int l = 3; l >= 0; --l) {
-    const int out = L.out_dim[l], in = L.in_dim[l];
-    const int64_t stride = (int64_t)out * in;
-    int64_t off = 0;
-    for (int q = 0; q < l; ++q) off += (int64_t)L.in_dim[q] * L.out_dim[q] * MLP_SPLITK;
-    // weight gradient: dW[in][out] = X^T[in][B] . dZ^T[out][B]^T
-    const bf16* Xt = l == 0 ? w.X0t : w.Yt[l - 1];
-    EpiDW ed{w.dW + off, stride, out};
-    e = gemm(Xt, w.cap, w.dZt[l], w.cap, in, out, M, MLP_SPLITK, ed, s);
-    if (e != hipSuccess) return e;
-    if (l > 0) {  // input gradient through W and the previous GELU
-      EpiBwdX eb{w.Z[l - 1], w.dZ[l - 1], w.dZt[l - 1], MLP_H, w.cap};
-      e = gemm(w.dZ[l], out, net.Wk[l], out, M, in, out, 1, eb, s);
-      if (e != hipSuccess) return e;
-    }
-  }
-  // bias gradients of every layer: column sums of dZ^T, one launch
-  BiasGradArgs bg;
-  int cols = 0;
+  train_rows_kernel<RB><<<blocks_for(a.M, 16 * RB), TW * 64, lds, s>>>(a);
+  return hipGetLastError();
+}
+static_assert(train_lds_bytes<2>((MLP_MAX_IN + 31) / 32 * 32) <= MLP_LDS_MAX, "the rows' LDS");
+
+hipError_t mlp_pass(const MlpDev& net, MlpWork& w, int64_t M, const float* stokes,
+                    const float* targets, const int32_t* rows, hipStream_t s) {
+  const MlpLayout& L = net.L;
+  TrainRowsArgs a;
+  a.stokes = stokes;
+  a.rows = rows;
+  a.targets = targets;
+  a.M = M;
+  a.cap = w.cap;
+  a.n_in = L.n_in;
+  a.K0 = L.K0;
+  a.mean = net.in_mean;
+  a.istd = net.in_istd;
+  a.X0t = w.X0t;
+  a.loss = w.loss;
+  GradArgs g;
+  g.M = M;
+  g.cap = w.cap;
+  g.chunk = ((M + MLP_SPLITK - 1) / MLP_SPLITK + 31) / 32 * 32;
+  int64_t off = 0;
+  int tiles = 0, cols = 0;
   for (int l = 0; l < 4; ++l) {
-    bg.dZt[l] = w.dZt[l];
-    bg.grad_b[l] = w.grad + L.ob[l];
-    bg.first[l] = cols;
+    a.Wt[l] = net.Wt[l];
+    a.Wk[l] = net.Wk[l];
+    a.bias[l] = net.master + L.ob[l];
+    a.dZt[l] = w.dZt[l];
+    if (l < 3) a.Yt[l] = w.Yt[l];
+    g.Xt[l] = l == 0 ? w.X0t : w.Yt[l - 1];
+    g.dZt[l] = w.dZt[l];
+    g.part[l] = w.dW + off;
+    g.grad_b[l] = w.grad + L.ob[l];
+    g.in_dim[l] = L.in_dim[l];
+    g.out_dim[l] = L.out_dim[l];
+    g.first_tile[l] = tiles;
+    g.first_col[l] = cols;
+    off += (int64_t)L.in_dim[l] * L.out_dim[l] * MLP_SPLITK;
+    tiles += L.in_dim[l] / (16 * GT) * (L.out_dim[l] / (16 * GT));
     cols += L.out_dim[l];
   }
-  bg.first[4] = cols;
-  bias_grad_kernel<<<cols, 256, 0, s>>>(bg, M, w.cap);
+  g.first_tile[4] = tiles;
+  g.first_col[4] = cols;
+  const hipError_t e = M >= TRAIN_RB2_ROWS ? launch_train_rows<2>(a, s) : launch_train_rows<1>(a, s);
+  if (e != hipSuccess) return e;
+  grad_kernel<<<GRAD_XCDS * grad_blocks(tiles) + cols, 256, 0, s>>>(g);
   return hipGetLastError();
 }
 
@@ -1057,6 +1203,7 @@ hipError_t mlp_adam(const MlpDev& net, const MlpWork& w, float lr, float beta1, 
   a.v = net.adam_v;
   a.grad = w.grad;
   int64_t off = 0;
+  int tiles = 0, cols = 0;
   for (int l = 0; l < 4; ++l) {
     a.part[l] = w.dW + off;
     off += (int64_t)L.in_dim[l] * L.out_dim[l] * MLP_SPLITK;
@@ -1066,9 +1213,13 @@ hipError_t mlp_adam(const MlpDev& net, const MlpWork& w, float lr, float beta1, 
     a.ob[l] = L.ob[l];
     a.in_dim[l] = L.in_dim[l];
     a.out_dim[l] = L.out_dim[l];
-    a.split_stride[l] = (int64_t)L.in_dim[l] * L.out_dim[l];
+    a.first_tile[l] = tiles;
+    a.first_col[l] = cols;
+    tiles += L.in_dim[l] / ADAM_K * (L.out_dim[l] / ADAM_N);
+    cols += L.out_dim[l];
   }
-  a.total = L.total;
+  a.first_tile[4] = tiles;
+  a.first_col[4] = cols;
   a.lr = lr;
   a.beta1 = beta1;
   a.beta2 = beta2;
@@ -1076,7 +1227,7 @@ hipError_t mlp_adam(const MlpDev& net, const MlpWork& w, float lr, float beta1, 
   a.update = step > 0 ? 1 : 0;
   a.bc1 = step > 0 ? 1.f - powf(beta1, (float)step) : 1.f;
   a.bc2 = step > 0 ? 1.f - powf(beta2, (float)step) : 1.f;
-  adam_kernel<<<blocks_for(L.total, 256), 256, 0, s>>>(a);
+  adam_kernel<<<tiles + blocks_for(cols, 256), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 

@@ -45,45 +45,27 @@ hipError_t dalloc(T** p, int64_t count) {
 }
 
 void free_work(MlpWork& w) {
-  hipFree(w.X0);
   hipFree(w.X0t);
-  for (int l = 0; l < 3; ++l) {
-    hipFree(w.Y[l]);
-    hipFree(w.Yt[l]);
-    hipFree(w.Z[l]);
-  }
-  hipFree(w.Y4);
-  for (int l = 0; l < 4; ++l) {
-    hipFree(w.dZ[l]);
-    hipFree(w.dZt[l]);
-  }
+  for (int l = 0; l < 3; ++l) hipFree(w.Yt[l]);
+  for (int l = 0; l < 4; ++l) hipFree(w.dZt[l]);
   hipFree(w.dW);
   hipFree(w.grad);
   hipFree(w.loss);
   std::memset(&w, 0, sizeof w);
 }
 
-hipError_t alloc_work(MlpWork& w, const MlpLayout& L, int64_t cap, bool training) {
+hipError_t alloc_work(MlpWork& w, const MlpLayout& L, int64_t cap) {
   free_work(w);
   w.cap = cap;
-  hipError_t e = dalloc(&w.X0, cap * L.K0);
-  for (int l = 0; l < 3 && e == hipSuccess; ++l) e = dalloc(&w.Y[l], cap * MLP_H);
-  if (e == hipSuccess) e = dalloc(&w.Y4, cap * MLP_OUT);
-  if (e == hipSuccess) e = dalloc(&w.loss, 1);
-  if (training) {
-    if (e == hipSuccess) e = dalloc(&w.X0t, cap * L.K0);
-    for (int l = 0; l < 3 && e == hipSuccess; ++l) e = dalloc(&w.Yt[l], cap * MLP_H);
-    for (int l = 0; l < 3 && e == hipSuccess; ++l) e = dalloc(&w.Z[l], cap * MLP_H);
-    for (int l = 0; l < 4 && e == hipSuccess; ++l) {
-      const int64_t width = l == 3 ? MLP_OUT : MLP_H;
-      e = dalloc(&w.dZ[l], cap * width);
-      if (e == hipSuccess) e = dalloc(&w.dZt[l], cap * width);
-    }
-    int64_t part = 0;
-    for (int l = 0; l < 4; ++l) part += (int64_t)L.in_dim[l] * L.out_dim[l] * MLP_SPLITK;
-    if (e == hipSuccess) e = dalloc(&w.dW, part);
-    if (e == hipSuccess) e = dalloc(&w.grad, L.total);
-  }
+  hipError_t e = dalloc(&w.loss, 1);
+  if (e == hipSuccess) e = dalloc(&w.X0t, cap * L.K0);
+  for (int l = 0; l < 3 && e == hipSuccess; ++l) e = dalloc(&w.Yt[l], cap * MLP_H);
+  for (int l = 0; l < 4 && e == hipSuccess; ++l)
+    e = dalloc(&w.dZt[l], cap * (l == 3 ? MLP_OUT : MLP_H));
+  int64_t part = 0;
+  for (int l = 0; l < 4; ++l) part += (int64_t)L.in_dim[l] * L.out_dim[l] * MLP_SPLITK;
+  if (e == hipSuccess) e = dalloc(&w.dW, part);
+  if (e == hipSuccess) e = dalloc(&w.grad, L.total);
   if (e != hipSuccess) free_work(w);
   return e;
 }
@@ -186,7 +168,7 @@ int build(vfisv_ctx* ctx, int n_in, const float* in_mean, const float* in_std,
 int ensure_train(vfisv_mlp* m, int64_t rows) {
   if (m->train.cap >= rows) return VFISV_OK;
   hipError_t e = hipDeviceSynchronize();
-  if (e == hipSuccess) e = alloc_work(m->train, m->dev.L, rows, true);
+  if (e == hipSuccess) e = alloc_work(m->train, m->dev.L, rows);
   if (e == hipSuccess) e = hipMemset(m->train.loss, 0, sizeof(double));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) return fail(m->ctx, VFISV_E_NOMEM, "mlp: training buffers");
@@ -359,8 +341,7 @@ int vfisv_mlp_gradient(vfisv_ctx* ctx, vfisv_mlp* m, int64_t n, const float* sto
   hipStream_t s = (hipStream_t)stream;
   MlpWork& w = m->train;
   e = zero_u64((unsigned long long*)w.loss, 1, s);
-  if (e == hipSuccess) e = mlp_forward(m->dev, w, n, stokes, nullptr, true, s);
-  if (e == hipSuccess) e = mlp_backward(m->dev, w, n, targets, nullptr, s);
+  if (e == hipSuccess) e = mlp_pass(m->dev, w, n, stokes, targets, nullptr, s);
   if (e == hipSuccess) e = mlp_adam(m->dev, w, 0.f, 0.f, 0.f, 0.f, 0, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(grad, w.grad, 4 * m->dev.L.total, hipMemcpyDeviceToDevice, s);
@@ -385,8 +366,7 @@ int vfisv_mlp_train_step(vfisv_ctx* ctx, vfisv_mlp* m, const float* stokes, cons
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
   MlpWork& w = m->train;
-  e = mlp_forward(m->dev, w, batch, stokes, rows, true, s);
-  if (e == hipSuccess) e = mlp_backward(m->dev, w, batch, targets, rows, s);
+  e = mlp_pass(m->dev, w, batch, stokes, targets, rows, s);
   if (e == hipSuccess) e = mlp_adam(m->dev, w, lr, 0.9f, 0.999f, 1e-8f, m->step + 1, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "mlp_train_step");
   m->step += 1;
@@ -554,8 +534,7 @@ int vfisv_mlp_train(vfisv_ctx* ctx, vfisv_mlp* m, const vfisv_train_spec* sp,
       const double frac = total > 1 ? (double)step / (double)(total - 1) : 0.0;
       const double f = sp->min_lr_frac + (1.0 - sp->min_lr_frac) * 0.5 * (1.0 + std::cos(pi * frac));
       const int32_t* rows = w.perm + b * sp->batch;
-      e = mlp_forward(m->dev, m->train, sp->batch, sp->stokes, rows, true, s);
-      if (e == hipSuccess) e = mlp_backward(m->dev, m->train, sp->batch, w.T, rows, s);
+      e = mlp_pass(m->dev, m->train, sp->batch, sp->stokes, w.T, rows, s);
       if (e == hipSuccess)
         e = mlp_adam(m->dev, m->train, (float)(sp->lr * f), 0.9f, 0.999f, 1e-8f, m->step + 1, s);
       if (e != hipSuccess) return hip_fail(ctx, e, "mlp_train: step");
