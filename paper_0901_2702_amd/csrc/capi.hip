@@ -166,24 +166,28 @@ static int grow_obs4(vfisv_ctx* ctx, size_t bytes) {
 
 // The pixels up to which the group inverter takes a launch, by layout and
 // use (FitUse), where it is faster than lm_kernel on 65,536 lanes.  Measured
-// (group / lm_kernel): plain HMI fits 4,096 pixels 0.65 / 3.95 ms, 50,000
-// 3.35 / 4.04, 65,536 4.11 / 4.05, 114,688 6.7 / 7.5, 131,072 7.6 / 7.0; fine
-// spectra 1,000 pixels 1.7 / 29, 100,003 38 / 64, 262,144 95.6 / 97.2, 400,000
-// 147 / 136.  From the network's start more trials are accepted and need
-// their Jacobian, which lm_kernel computes ahead: short fits of HMI pixels
-// 20,011 0.60 / 1.12 ms, 50,000 1.19 / 1.22, 65,536 1.49 / 1.29.  Re-fits,
-// which lm_kernel runs in lane pairs up to 36,044 pixels: 1,139 pixels 0.65 /
-// 2.36 ms, 34,776 2.77 / 2.80, 40,263 2.98 / 3.40, 51,000 3.9 / 3.4.
-constexpr int64_t GROUP_MAX[2][4] = {{0, 122880, 53248, 45056}, {0, 262144, 131072, 131072}};
+// (group / lm_kernel, ms): plain HMI fits 4,096 pixels 0.62 / 3.5, 65,536 3.7
+// / 4.0, 114,688 6.3 / 7.4, 131,072 7.1 / 6.9, 262,144 13.6 / 12.5; fine
+// spectra at any size, 1,000 pixels 1.43 / 27, 131,072 38 / 61, 262,144 74 /
+// 97, 1,000,000 277 / 306.  From the network's start more trials are accepted
+// and need their Jacobian, which lm_kernel computes ahead: short fits of HMI
+// pixels 20,011 0.58 / 1.09, 55,000 1.21 / 1.23, 60,000 1.34 / 1.27.  Re-fits,
+// which lm_kernel runs in lane pairs up to 36,044 pixels: 1,139 pixels 0.55 /
+// 2.33, 34,776 2.41 / 2.75, 46,630 2.79 / 3.34.
+constexpr int64_t GROUP_ANY = INT64_MAX;
+constexpr int64_t GROUP_MAX[2][4] = {{0, 122880, 57344, 57344}, {0, GROUP_ANY, 131072, 131072}};
 
 // The largest batch that the group inverter takes under these options, 0 if
 // none: it has Weideman's series and the fit with convergence exits only.
 static int64_t group_limit(const vfisv_ctx* ctx, const vfisv_instrument* inst,
                            const vfisv_options& o, FitUse use) {
   if (o.voigt != 0 || o.fixed_iters != 0 || o.lanes_per_pixel != 1 || !inst->d_group) return 0;
-  // (a layout with a tuned schedule keeps it where a schedule matters)
+  // (HMI instruments with a tuned schedule keep it where a schedule matters:
+  // 65,536 pixels 3.45 ms with derivatives in every pass, 3.7 here; fine
+  // spectra 30.4, 20.0 here)
   const int64_t most = GROUP_MAX[inst->kind][use];
-  return ctx->tuned[inst->kind].valid ? std::min<int64_t>(most, 16384) : most;
+  const bool tuned = inst->kind == KIND_DENSE6 && ctx->tuned[inst->kind].valid;
+  return tuned ? std::min<int64_t>(most, 16384) : most;
 }
 
 // Enqueue the group inverter for `a`, a launch of at most n pixels that it
@@ -839,11 +843,11 @@ int vfisv_invert_batches(vfisv_ctx* ctx, const vfisv_batch* batches, int n_batch
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const int grid = lm_grid(ctx, total, ctx->band_blocks_per_cu, o, -1);
   hipStream_t s = (hipStream_t)stream;
-  // Few pixels in all: the batches one after the other in the group inverter,
-  // whose time goes with their sizes (20,000 fine spectra and 50,001 HMI
-  // pixels 13 ms), where one lane's fit of the slowest layout sets the time
-  // of lm_batches_kernel (36 ms) until the batches are a share of their
-  // limits each that adds up to one.
+  // Batches within the group inverter's limits, each a share of its own that
+  // adds up to at most one: one after the other there, where the time goes
+  // with their sizes (20,000 fine spectra and 50,001 HMI pixels 10 ms); one
+  // lane's fit of the slowest layout sets the time of lm_batches_kernel
+  // (36 ms).
   double share = 0.0;
   for (int i = 0; i < n_batches; ++i) {
     const int64_t most = group_limit(ctx, batches[i].inst, o, fit_use(o, FIT_PLAIN));
