@@ -25,14 +25,15 @@
 // in LDS for the rejected trials after it.
 //
 // Few pixels are bound by one fit's serial chain (points, row sums, chi^2,
-// Cholesky: 8 us per trial), many by VALU issue, at about 760 wave
-// instructions per trial of an HMI pixel (lm_kernel: 510, with lanes and
+// Cholesky: 7 us per trial of an HMI pixel), many by VALU issue (79% of the
+// cycles at 65,536 HMI pixels, 88% at as many fine spectra), at about 620 wave
+// instructions per trial of an HMI pixel (lm_kernel: 500, with lanes and
 // derivative passes that wait for each other).  Eight slots share the solve,
 // the decisions and the set-up of a turn, which one lane each would otherwise
 // run alone (two pixels per wave, 32 lanes each: 1,750 instructions per
-// trial, 131,072 pixels in 18.2 ms instead of 7.6).  Measured, default
-// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.35 ms, 4,096 3.95 -> 0.62,
-// 65,536 4.7 -> 3.7; 1,000 fine spectra 29.5 -> 1.43 ms, 100,003 63.7 -> 30.2.
+// trial, 131,072 pixels in 18.2 ms instead of 6.9).  Measured, default
+// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.34 ms, 4,096 3.95 -> 0.60,
+// 65,536 4.7 -> 3.6; 1,000 fine spectra 29.5 -> 1.43 ms, 100,003 63.7 -> 30.2.
 #include <hip/hip_runtime.h>
 
 #include "group.h"
@@ -100,7 +101,7 @@ static_assert(GROUP_SLOTS[KIND_DENSE6] * TSTR_D <= CN / 4, "chi^2 terms");
 static_assert(4 * VB * TSTR_B <= TAIL_B && VB * BROWS * 4 <= BROWS * BASTR, "chi^2 terms");
 static_assert(TAIL_B + GROUP_SLOTS[KIND_BAND] * 4 * BPREV <= WN, "values-only tails");
 static_assert(GROUP_SLOTS[KIND_DENSE6] * NOBS_HMI <= 64 &&
-                  GROUP_SLOTS[KIND_DENSE6] * NOBS_HMI * 8 <= JB * NOBS_HMI * ASTR,
+                  GROUP_SLOTS[KIND_DENSE6] * NOBS_HMI * 4 <= JB * NOBS_HMI * ASTR,
               "values-only row sums of every slot");
 static_assert(4 * CN >= (int)sizeof(double) * WS_DOUBLES, "the eigen fallback's record fits");
 static_assert(sizeof(Lds<false>) <= 20480 && sizeof(Lds<true>) <= 20480, "eight waves on a CU");
@@ -345,8 +346,10 @@ template <bool BAND>
 struct Layout;
 
 // ---- dense layout ----------------------------------------------------------
-// At most 64 synthesis points: one per lane.  MFMA lane (col, kq) = (lane % 16,
-// lane / 16) feeds tap A[row = col][point 4 i + kq] and quantity B[col] at that
+// At most 64 synthesis points: one per lane.  Values only, four slots' four
+// quantities are the columns (with the five that a pass with derivatives sums,
+// three slots: 65,536 pixels 3.73 ms instead of 3.58).  MFMA lane (col, kq) =
+// (lane % 16, lane / 16) feeds tap A[row = col][point 4 i + kq] and quantity B[col] at that
 // point in step i, and receives rows 4 kq .. + 3 of quantity col.
 // The row sums of a launch in lane pairs (lm_kernel with two lanes per pixel)
 // are those of the even and of the odd records, added: the odd ones take MFMA
@@ -415,38 +418,37 @@ struct Layout<false> {
     col = lane & 15;
     kq = lane >> 4;
     for (unsigned m = lm; m != 0u;) {
-      // up to three slots share the 16 columns of the MFMA
+      // four slots share the 16 columns of the MFMA
       const unsigned m0 = m;
 #pragma unroll 1
-      for (int b = 0; b < 3 && m != 0u; ++b, m &= m - 1u) {
+      for (int b = 0; b < 4 && m != 0u; ++b, m &= m - 1u) {
         const Pix px = get_pix(S.slot[first_slot(m)]);
         float v[NACC];
         point_contrib<false>(dl, px, ga.A.C, v);
+        const float u[4] = {v[0], v[2], v[3], v[4]};  // what the Stokes values need
 #pragma unroll
-        for (int k = 0; k < 5; ++k) c[(5 * b + k) * CSTR + lane] = v[k];
+        for (int k = 0; k < 4; ++k) c[(4 * b + k) * CSTR + lane] = u[k];
       }
       wave_fence();
-      const int b = col < 15 ? col / 5 : 2;
-      unsigned mb = m0;
-      if (b > 0) mb &= mb - 1u;
-      if (b > 1) mb &= mb - 1u;
       // columns without a slot read the first slot's points
-      const bool ok = mb != 0u && col < 15;
-      const float* src = c + (ok ? col : 0) * CSTR + kq;
+      const int k = nth_slot(m0, col >> 2);
+      const float* src = c + (k >= 0 ? col : 0) * CSTR + kq;
+      float x[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[i] = src[4 * i];
+      issued();
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc = mfma4(tap[i], src[4 * i], acc);
+      for (int i = 0; i < 16; ++i) acc = mfma4(tap[i], x[i], acc);
       wave_fence();
-      const int k = ok ? __ffs((int)mb) - 1 : 0;
-      store_rows(acc, S.a + k * (NOBS_HMI * 8), 8, col - 5 * b, ok);
+      store_rows(acc, S.a + (k >= 0 ? k : 0) * (NOBS_HMI * 4), 4, col & 3, k >= 0);
     }
     wave_fence();
     double2* T = S.c2;
     const int k = lane / NOBS_HMI, q = lane - k * NOBS_HMI;
     if ((lm >> k) & 1u) {
-      const float* a = S.a + k * (NOBS_HMI * 8) + q * 8;
-      const float4 h = ld4(a);
-      const float av[5] = {h.x, h.y, h.z, h.w, a[4]};
+      const float4 h = ld4(S.a + (k * NOBS_HMI + q) * 4);
+      const float av[5] = {h.x, 0.f, h.y, h.z, h.w};
       const RowFactors rf = get_rf(S.slot[k]);
       float Sv[4], J[4][NPAR];
       assemble_sample<false>(av, rs, rf, Sv, J);
@@ -490,9 +492,19 @@ struct Layout<false> {
         const float* s1 = c + (col + 16 < NACC ? col + 16 : col) * CSTR + kq;
         f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          a0 = mfma4(tap[i], s0[4 * i], a0);
-          a1 = mfma4(tap[i], s1[4 * i], a1);
+        for (int h = 0; h < 16; h += 8) {
+          float x[8], y[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            x[i] = s0[4 * (h + i)];
+            y[i] = s1[4 * (h + i)];
+          }
+          issued();
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            a0 = mfma4(tap[h + i], x[i], a0);
+            a1 = mfma4(tap[h + i], y[i], a1);
+          }
         }
         wave_fence();
         float* a = S.a + nb * (NOBS_HMI * ASTR);
