@@ -166,16 +166,16 @@ static int grow_obs4(vfisv_ctx* ctx, size_t bytes) {
 
 // The pixels up to which the group inverter takes a launch, by layout and
 // use (FitUse), where it is faster than lm_kernel on 65,536 lanes.  Measured
-// (group / lm_kernel, ms): plain HMI fits 4,096 pixels 0.62 / 3.5, 65,536 3.7
-// / 4.0, 114,688 6.3 / 7.4, 131,072 7.1 / 6.9, 262,144 13.6 / 12.5; fine
-// spectra at any size, 1,000 pixels 1.43 / 27, 131,072 38 / 61, 262,144 74 /
+// (group / lm_kernel, ms): plain HMI fits 4,096 pixels 0.62 / 3.4, 65,536 3.6
+// / 4.0, 114,688 6.0 / 7.4, 139,264 7.2 / 7.5, 147,456 7.6 / 7.6, 262,144 13.1
+// / 12.5; fine spectra at any size, 1,000 pixels 1.43 / 27, 131,072 38 / 61, 262,144 74 /
 // 97, 1,000,000 277 / 306.  From the network's start more trials are accepted
 // and need their Jacobian, which lm_kernel computes ahead: short fits of HMI
 // pixels 20,011 0.58 / 1.09, 55,000 1.21 / 1.23, 60,000 1.34 / 1.27.  Re-fits,
 // which lm_kernel runs in lane pairs up to 36,044 pixels: 1,139 pixels 0.55 /
 // 2.33, 34,776 2.41 / 2.75, 46,630 2.79 / 3.34.
 constexpr int64_t GROUP_ANY = INT64_MAX;
-constexpr int64_t GROUP_MAX[2][4] = {{0, 122880, 57344, 57344}, {0, GROUP_ANY, 131072, 131072}};
+constexpr int64_t GROUP_MAX[2][4] = {{0, 139264, 57344, 57344}, {0, GROUP_ANY, 131072, 131072}};
 
 // The largest batch that the group inverter takes under these options, 0 if
 // none: it has Weideman's series and the fit with convergence exits only.
@@ -843,34 +843,43 @@ int vfisv_invert_batches(vfisv_ctx* ctx, const vfisv_batch* batches, int n_batch
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const int grid = lm_grid(ctx, total, ctx->band_blocks_per_cu, o, -1);
   hipStream_t s = (hipStream_t)stream;
-  // Batches within the group inverter's limits, each a share of its own that
-  // adds up to at most one: one after the other there, where the time goes
-  // with their sizes (20,000 fine spectra and 50,001 HMI pixels 10 ms); one
-  // lane's fit of the slowest layout sets the time of lm_batches_kernel
-  // (36 ms).
+  // One after the other in the group inverter: the batches that it takes at
+  // any size, and the others if their shares of their limits add up to at most
+  // one.  There the time goes with the sizes (20,000 fine spectra and 50,001
+  // HMI pixels 10 ms; lm_batches_kernel, whose time one lane's fit of the
+  // slowest layout sets, 36); 1,000,000 of each 318 ms, 339 all in
+  // lm_batches_kernel.
   double share = 0.0;
+  bool any[MAX_BATCHES] = {};  // faster there at any size
   for (int i = 0; i < n_batches; ++i) {
     const int64_t most = group_limit(ctx, batches[i].inst, o, fit_use(o, FIT_PLAIN));
-    share += batches[i].n == 0 ? 0.0 : most > 0 ? (double)batches[i].n / (double)most : 2.0;
+    any[i] = most == GROUP_ANY;
+    if (batches[i].n > 0 && !any[i])
+      share += most > 0 ? (double)batches[i].n / (double)most : 2.0;
   }
-  if (share <= 1.0) {
-    e = launch_reset(ctx->d_work, true, s);
-    for (int i = 0; i < n_batches && e == hipSuccess; ++i)
-      if (batches[i].n > 0)
-        e = enqueue_group(ctx, batches[i].inst, B.a[i], batches[i].n, batches[i].n, s);
-    if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches launch");
-    return VFISV_OK;
+  e = launch_reset(ctx->d_work, true, s);
+  bool left = false;
+  for (int i = 0; i < n_batches && e == hipSuccess; ++i) {
+    if (batches[i].n == 0) continue;
+    if (any[i] || share <= 1.0) {
+      e = enqueue_group(ctx, batches[i].inst, B.a[i], batches[i].n, batches[i].n, s);
+      B.a[i].n = 0;  // nothing left for lm_batches_kernel
+    } else {
+      left = true;
+    }
   }
+  if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches launch");
+  if (!left) return VFISV_OK;
   // banded batches read interleaved copies, side by side in one buffer
   size_t need = 0;
   for (int i = 0; i < n_batches; ++i)
-    if (B.kind[i] == KIND_BAND) need += (size_t)batches[i].n * (size_t)batches[i].inst->C.n_obs;
+    if (B.kind[i] == KIND_BAND) need += (size_t)B.a[i].n * (size_t)batches[i].inst->C.n_obs;
   if (need > 0) {
     const int rc = grow_obs4(ctx, sizeof(float4) * need);
     if (rc) return rc;
     float4* o4 = (float4*)ctx->d_obs4;
     for (int i = 0; i < n_batches; ++i) {
-      if (B.kind[i] != KIND_BAND || batches[i].n == 0) continue;
+      if (B.kind[i] != KIND_BAND || B.a[i].n == 0) continue;
       const int no = batches[i].inst->C.n_obs;
       e = launch_interleave(batches[i].stokes, o4, batches[i].n, no, s);
       if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches: interleave");
@@ -878,8 +887,6 @@ int vfisv_invert_batches(vfisv_ctx* ctx, const vfisv_batch* batches, int n_batch
       o4 += (size_t)batches[i].n * (size_t)no;
     }
   }
-  e = launch_reset(ctx->d_work, true, s);
-  if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches: counter reset");
   e = launch_lm_batches(B, grid, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches launch");
   return VFISV_OK;

@@ -168,3 +168,24 @@ def test_batches(ctx):
         _same(a, b, ("batches", i))
     for k in ("pixels", "trials", "accepts", "jacobians"):
         assert c[k] == cr[k], k
+
+
+def test_batches_of_both_kernels(ctx):
+    """More HMI pixels than the group inverter takes: they go to the lanes,
+    the spectra of the same call to the group inverter."""
+    dev = ctx.device
+    hs, fs = wl.hmi_instrument(), wl.fine_instrument()
+    hi, fi = vf.Instrument.from_spec(ctx, hs), vf.Instrument.from_spec(ctx, fs)
+    obs = torch.tensor(_obs(hs, 2000, 42), device=dev).repeat(71, 1, 1).contiguous()
+    batches = [dict(inst=hi, stokes=obs, W=torch.tensor(wl.weights(6), device=dev)),
+               dict(inst=fi, stokes=torch.tensor(_obs(fs, 70, 43), device=dev),
+                    W=torch.tensor(wl.weights(fs.n_obs), device=dev))]
+    print("[gpu] group batches of both kernels", flush=True)
+    ref = vf.invert_batches(ctx, batches, opts=vf.Options(**LANES))
+    cr = ctx.counters()
+    out = vf.invert_batches(ctx, batches)
+    c = ctx.counters()
+    for i, (a, b) in enumerate(zip(ref, out)):
+        _same(a, b, ("both kernels", i))
+    for k in ("pixels", "trials", "accepts", "jacobians"):
+        assert c[k] == cr[k], k
