@@ -63,7 +63,8 @@ LEARNED_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "lm_kernel_hmi_1M_learn
 LEARNED_SQ_PROFILE = os.path.join(ROOT, "profiles", "lm_kernel_hmi_1M_learned_sq_counters.md")
 FINE_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "lm_kernel_fine_1M_traffic.md")
 KERNEL_SOURCES = ("paper_0901_2702_amd/csrc/kernels.hip", "paper_0901_2702_amd/csrc/kernels.h",
-                  "paper_0901_2702_amd/csrc/me_device.h")
+                  "paper_0901_2702_amd/csrc/me_device.h", "paper_0901_2702_amd/csrc/group.h",
+                  "paper_0901_2702_amd/csrc/group.hip")
 
 
 def kernel_source_hash():
@@ -425,7 +426,7 @@ def main():
                       "executed": rate(sq.get("short_fit"), ph_ms["short_fit"]),
                       "fp64": round(census.fp64(sf) / (ph_ms["short_fit"] * 1e-3) / 1e12, 3),
                       "work": {k: sf[k] for k in WORK_KEYS}},
-        "refit": {"kernel": "lm_kernel<6> (re-fit of the pixels above tau, <= 50 trials)",
+        "refit": {"kernel": "lm_group_kernel<false> (re-fit of the pixels above tau, <= 50 trials)",
                   "ms": round(ph_ms["refit"], 4), "bound": "alu", "unit": "TFLOP/s",
                   "peak": PEAK_FP32_TFLOPS,
                   "achieved": round(alg(rf) / (ph_ms["refit"] * 1e-3) / 1e12, 3),
@@ -819,7 +820,7 @@ def fine_mixed(args, ctx, inst, spec, log):
                      "traffic_detail": None if tr_f is None else dict(
                          tr_f, algorithmic_bytes=n_f * (4 * fspec.n_obs * 4 + 56),
                          source=os.path.relpath(FINE_TRAFFIC_PROFILE, ROOT)),
-                     "kernel": "lm_kernel<0> (banded, fine pixels alone)",
+                     "kernel": "lm_group_kernel<true> (fine pixels alone)",
                      "kernel_ms": round(ev_f, 3), "census": census.record(),
                      "work_fine": {k: c_f[k] for k in WORK_KEYS},
                      "work_mixed": {k: c_mix[k] for k in WORK_KEYS}},
