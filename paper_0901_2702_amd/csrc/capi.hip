@@ -181,12 +181,13 @@ constexpr int64_t GROUP_MAX[2][4] = {{0, 139264, 57344, 57344}, {0, GROUP_ANY, 1
 // none: it has Weideman's series and the fit with convergence exits only.
 static int64_t group_limit(const vfisv_ctx* ctx, const vfisv_instrument* inst,
                            const vfisv_options& o, FitUse use) {
-  if (o.voigt != 0 || o.fixed_iters != 0 || o.lanes_per_pixel != 1 || !inst->d_group) return 0;
-  // (HMI instruments with a tuned schedule keep it where a schedule matters:
-  // 65,536 pixels 3.45 ms with derivatives in every pass, 3.7 here; fine
-  // spectra 30.4, 20.0 here)
+  if (o.voigt != 0 || o.fixed_iters != 0 || o.lanes_per_pixel != 1 || !inst->group.dl) return 0;
+  // (Plain HMI fits with a tuned schedule keep it where a schedule matters:
+  // 65,536 pixels 3.45 ms with derivatives in every pass, 3.6 here.  Short fits
+  // and re-fits have no tuned split, fine spectra are faster here than with
+  // any: 65,536 of them 30.4 ms, 20.0 here.)
   const int64_t most = GROUP_MAX[inst->kind][use];
-  const bool tuned = inst->kind == KIND_DENSE6 && ctx->tuned[inst->kind].valid;
+  const bool tuned = inst->kind == KIND_DENSE6 && use == FIT_PLAIN && ctx->tuned[inst->kind].valid;
   return tuned ? std::min<int64_t>(most, 16384) : most;
 }
 
@@ -654,13 +655,34 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
     }
     obs_x[(size_t)i] = sw > 0.0 ? (float)(swx / sw) : 0.f;
   }
-  e = hipMalloc(&inst->d_obs_x, sizeof(float) * (size_t)no);
+  // one upload for all tables of floats, each on a 16-byte boundary
+  std::vector<float> tabs(obs_x);
+  const auto put = [&](const std::vector<float>& v) {
+    tabs.resize((tabs.size() + 3) / 4 * 4, 0.f);
+    const size_t at = tabs.size();
+    tabs.insert(tabs.end(), v.begin(), v.end());
+    return at;
+  };
+  const size_t o_rows = put(mtab);
+  const bool group = inst->kind == KIND_BAND || inst->group.n_chunk == 1;
+  const size_t o_gdl = group ? put(gdl) : 0, o_gtaps = group ? put(gtaps) : 0;
+  e = hipMalloc(&inst->d_obs_x, sizeof(float) * tabs.size());
   if (e == hipSuccess)
-    e = hipMemcpy(inst->d_obs_x, obs_x.data(), sizeof(float) * (size_t)no, hipMemcpyHostToDevice);
+    e = hipMemcpy(inst->d_obs_x, tabs.data(), sizeof(float) * tabs.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     if (inst->d_obs_x) hipFree(inst->d_obs_x);
     delete inst;
-    return hip_fail(ctx, e, "instrument_create: sample table");
+    return hip_fail(ctx, e, "instrument_create: tables");
+  }
+  if (!mtab.empty()) {
+    const float* d_rows = inst->d_obs_x + o_rows;
+    inst->rows.t = (const float2*)d_rows;
+    inst->rows_nat.t = (const float2*)(d_rows + o_nat);
+    inst->rows.dl = inst->rows_nat.dl = d_rows + o_dl;
+  }
+  if (group) {
+    inst->group.dl = inst->d_obs_x + o_gdl;
+    inst->group.taps = inst->d_obs_x + o_gtaps;
   }
   if (inst->kind == KIND_DENSE6) {
     const size_t bytes = sizeof(Point) * (pts.empty() ? 1 : pts.size());
@@ -677,27 +699,8 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
       e = hipMemcpy(inst->d_row_sums, row_sum.data(), sizeof(float) * (size_t)no,
                     hipMemcpyHostToDevice);
   }
-  if (e == hipSuccess && !mtab.empty()) {
-    e = hipMalloc(&inst->d_rows, sizeof(float) * mtab.size());
-    if (e == hipSuccess)
-      e = hipMemcpy(inst->d_rows, mtab.data(), sizeof(float) * mtab.size(), hipMemcpyHostToDevice);
-    inst->rows.t = (const float2*)inst->d_rows;
-    inst->rows_nat.t = (const float2*)(inst->d_rows + o_nat);
-    inst->rows.dl = inst->rows_nat.dl = inst->d_rows + o_dl;
-  }
-  if (e == hipSuccess && (inst->kind == KIND_BAND || inst->group.n_chunk == 1)) {
-    std::vector<float> host(gdl);
-    host.insert(host.end(), gtaps.begin(), gtaps.end());
-    e = hipMalloc(&inst->d_group, sizeof(float) * host.size());
-    if (e == hipSuccess)
-      e = hipMemcpy(inst->d_group, host.data(), sizeof(float) * host.size(), hipMemcpyHostToDevice);
-    inst->group.dl = inst->d_group;
-    inst->group.taps = inst->d_group + gdl.size();
-  }
   if (e != hipSuccess) {
-    if (inst->d_group) hipFree(inst->d_group);
     if (inst->d_pts) hipFree(inst->d_pts);
-    if (inst->d_rows) hipFree(inst->d_rows);
     if (inst->d_blocks) hipFree(inst->d_blocks);
     if (inst->d_row_sums) hipFree(inst->d_row_sums);
     hipFree(inst->d_obs_x);
@@ -719,11 +722,9 @@ int vfisv_instrument_destroy(vfisv_instrument* inst) {
   hipSetDevice(inst->device);
   hipDeviceSynchronize();
   if (inst->d_pts) hipFree(inst->d_pts);
-  if (inst->d_rows) hipFree(inst->d_rows);
   if (inst->d_blocks) hipFree(inst->d_blocks);
   if (inst->d_row_sums) hipFree(inst->d_row_sums);
   if (inst->d_obs_x) hipFree(inst->d_obs_x);
-  if (inst->d_group) hipFree(inst->d_group);
   delete inst;
   return VFISV_OK;
 }

@@ -67,13 +67,11 @@ struct vfisv_instrument {
                    // instrument never reads the context
   int kind = vfisv::KIND_DENSE6;
   vfisv::Point* d_pts = nullptr;       // KIND_DENSE6
-  float* d_rows = nullptr;             // KIND_DENSE6: matrix-core tap tables of lm_kernel
-  vfisv::DenseTaps rows{}, rows_nat{};  // in d_rows
+  vfisv::DenseTaps rows{}, rows_nat{};  // KIND_DENSE6: matrix-core tap tables of lm_kernel (in d_obs_x)
   vfisv::Block* d_blocks = nullptr;    // KIND_BAND
   float* d_row_sums = nullptr;         // KIND_BAND
-  float* d_obs_x = nullptr;            // [n_obs] observed wavelength of each sample
-  float* d_group = nullptr;            // tables of the group inverter
-  vfisv::GroupTables group;
+  float* d_obs_x = nullptr;            // [n_obs] observed wavelength of each sample; further tables
+  vfisv::GroupTables group;            // tables of the group inverter (in d_obs_x; none: null)
   vfisv::Consts C;
   vfisv_instrument_info info;
 };
