@@ -9,7 +9,7 @@ LIB = os.path.join(HERE, "libvfisv.so")
 SOURCES = ["kernels.hip", "capi.hip", "mlp.hip", "mlp_capi.hip", "classical.hip",
            "group.hip"]
 HEADERS = ["me_device.h", "kernels.h", "mlp.h", "capi_internal.h", "classical.h",
-           "group.h"]
+           "group.h", "routes.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

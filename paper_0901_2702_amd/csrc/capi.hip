@@ -164,29 +164,17 @@ static int grow_obs4(vfisv_ctx* ctx, size_t bytes) {
   return VFISV_OK;
 }
 
-// The pixels up to which the group inverter takes a launch, by layout and
-// use (FitUse), where it is faster than lm_kernel on 65,536 lanes.  Measured
-// (group / lm_kernel, ms): plain HMI fits 4,096 pixels 0.62 / 3.4, 65,536 3.6
-// / 4.0, 114,688 6.0 / 7.4, 139,264 7.2 / 7.5, 147,456 7.6 / 7.6, 262,144 13.1
-// / 12.5; fine spectra at any size, 1,000 pixels 1.43 / 27, 131,072 38 / 61, 262,144 74 /
-// 97, 1,000,000 277 / 306.  From the network's start more trials are accepted
-// and need their Jacobian, which lm_kernel computes ahead: short fits of HMI
-// pixels 20,011 0.58 / 1.09, 55,000 1.21 / 1.23, 60,000 1.34 / 1.27.  Re-fits,
-// which lm_kernel runs in lane pairs up to 36,044 pixels: 1,139 pixels 0.55 /
-// 2.33, 34,776 2.41 / 2.75, 46,630 2.79 / 3.34.
-constexpr int64_t GROUP_ANY = INT64_MAX;
-constexpr int64_t GROUP_MAX[2][4] = {{0, 139264, 57344, 57344}, {0, GROUP_ANY, 131072, 131072}};
-
-// The largest batch that the group inverter takes under these options, 0 if
-// none: it has Weideman's series and the fit with convergence exits only.
+// The largest batch that the group inverter takes under these options
+// (fit_group_max), 0 if none: it has Weideman's series and the fit with
+// convergence exits only.
 static int64_t group_limit(const vfisv_ctx* ctx, const vfisv_instrument* inst,
                            const vfisv_options& o, FitUse use) {
-  if (o.voigt != 0 || o.fixed_iters != 0 || o.lanes_per_pixel != 1 || !inst->group.dl) return 0;
+  if (o.voigt != 0 || o.fixed_iters != 0 || o.lanes_per_pixel != 1) return 0;
   // (Plain HMI fits with a tuned schedule keep it where a schedule matters:
   // 65,536 pixels 3.45 ms with derivatives in every pass, 3.6 here.  Short fits
   // and re-fits have no tuned split, fine spectra are faster here than with
   // any: 65,536 of them 30.4 ms, 20.0 here.)
-  const int64_t most = GROUP_MAX[inst->kind][use];
+  const int64_t most = fit_group_max(inst->extent, use, o.max_iter);
   const bool tuned = inst->kind == KIND_DENSE6 && use == FIT_PLAIN && ctx->tuned[inst->kind].valid;
   return tuned ? std::min<int64_t>(most, 16384) : most;
 }
@@ -683,6 +671,9 @@ int vfisv_instrument_create(vfisv_ctx* ctx, const vfisv_instrument_desc* d,
   if (group) {
     inst->group.dl = inst->d_obs_x + o_gdl;
     inst->group.taps = inst->d_obs_x + o_gtaps;
+    inst->extent.band = inst->kind == KIND_BAND;
+    inst->extent.points = inst->kind == KIND_BAND ? BAND_S * (int)blocks.size() : (int)pts.size();
+    inst->extent.chunks = inst->group.n_chunk;
   }
   if (inst->kind == KIND_DENSE6) {
     const size_t bytes = sizeof(Point) * (pts.empty() ? 1 : pts.size());

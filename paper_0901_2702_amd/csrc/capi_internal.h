@@ -10,6 +10,7 @@
 
 #include "group.h"
 #include "kernels.h"
+#include "routes.h"
 #include "vfisv.h"
 
 namespace vfisv {
@@ -72,6 +73,7 @@ struct vfisv_instrument {
   float* d_row_sums = nullptr;         // KIND_BAND
   float* d_obs_x = nullptr;            // [n_obs] observed wavelength of each sample; further tables
   vfisv::GroupTables group;            // tables of the group inverter (in d_obs_x; none: null)
+  vfisv::Extent extent{};              // its synthesis points and their chunks (chunks 0: no tables)
   vfisv::Consts C;
   vfisv_instrument_info info;
 };
@@ -97,12 +99,8 @@ int ensure_vtab(vfisv_ctx* ctx);
 // the library allocate (the Taylor table before it exists).
 int check_options(vfisv_ctx* ctx, const vfisv_instrument* inst, const vfisv_options* opt,
                   vfisv_options* out, double* inv_dof, bool may_alloc = true);
-// What a fit is for, which decides with its size whether the group inverter
-// takes it: a launch whose schedule the caller chose (never), a plain fit,
-// the learned path's short fit and its re-fit.
-enum FitUse { FIT_SCHEDULED, FIT_PLAIN, FIT_SHORT, FIT_REFIT };
-// `use`, or FIT_SCHEDULED when the options fix the launch schedule.
-FitUse fit_use(const vfisv_options& o, FitUse use);
+// `use` (what the fit is for), or FIT_SCHEDULED when the options fix the launch schedule.
+vfisv::FitUse fit_use(const vfisv_options& o, vfisv::FitUse use);
 // Resolve the device address of the allocation-free path's scratch array on
 // ctx's device (current on the calling thread); once per device.
 int noalloc_scratch_setup(vfisv_ctx* ctx);
@@ -122,6 +120,6 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
                const float* W, int W_pp, const float* init, const vfisv_options& o,
                double inv_dof, float* params, double* chi2, int32_t* iters, int32_t* status,
                hipStream_t s, bool reset_all, int lpp_max = 1, bool may_alloc = true,
-               FitUse use = FIT_SCHEDULED);
+               vfisv::FitUse use = vfisv::FIT_SCHEDULED);
 
 }  // namespace vfisv_capi
