@@ -749,26 +749,20 @@ int vfisv_synthesize_voigt(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t
   a.C = inst->C;
   a.C.vtab = ctx->d_vtab;
   a.pts = inst->d_pts;
+  a.blocks = inst->d_blocks;
   a.row_sums = inst->d_row_sums;
   a.params = params;
   a.noise = noise;
   a.stokes = stokes;
   a.jac = jac;
   a.n = n;
-  // Waves of a few models each (group.hip), except where a model per lane is
-  // faster: HMI values without Jacobian once every SIMD has two waves of them
-  // (65,537 models 49 us, here 34; 131,072 56, here 58; 262,144 92, here 112;
-  // with Jacobian 262,144 416, here 355).  The Taylor table and dense
-  // instruments of more than one chunk of points are a model per lane's.
-  constexpr int64_t GROUP_VALUES_MAX = 114688;
-  const bool group = inst->kind == KIND_BAND ||
-                     (voigt == 0 && inst->group.n_chunk == 1 && (jac || n <= GROUP_VALUES_MAX));
-  if (group) {
+  // (the Taylor table is a model per lane's)
+  if (voigt == 0 && synth_by_group(inst->extent, n, jac != nullptr)) {
     e = launch_synth_group(a, inst->group, inst->kind, jac != nullptr, ctx->num_cus,
                            (hipStream_t)stream);
   } else {
     const int grid = grid_for(n, (int64_t)ctx->num_cus * 16);
-    e = launch_synth(a, voigt, jac != nullptr, grid, (hipStream_t)stream);
+    e = launch_synth(a, inst->kind, voigt, jac != nullptr, grid, (hipStream_t)stream);
   }
   if (e != hipSuccess) return hip_fail(ctx, e, "synthesize launch");
   return VFISV_OK;

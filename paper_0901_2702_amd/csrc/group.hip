@@ -1044,11 +1044,6 @@ __device__ __forceinline__ void setup_models(const SynthArgs& A, ModelLds* rec, 
   wave_fence();
 }
 
-// A Stokes value (rounded, as stored without noise) and its noise.
-__device__ __forceinline__ float plus_noise(float S, float noise) {
-#pragma clang fp contract(off)
-  return S + noise;
-}
 __device__ __forceinline__ void store_jac(float* J, const float* v) {
 #pragma unroll
   for (int p = 0; p < NPAR; ++p) J[p] = v[p];
@@ -1297,6 +1292,23 @@ __global__ __launch_bounds__(64, DERIV ? 3 : 4) void synth_group_band_kernel(con
   }
 }
 
+template <class K>
+static void launch_synth_pieces(K kernel, const SynthArgs& a, const GroupTables& t, int64_t per,
+                                hipStream_t s) {
+  // (a launch takes less than 2^32 lanes)
+  constexpr int64_t MAX_GRID = (int64_t)1 << 25;
+  const int64_t row = 4 * (int64_t)a.C.n_obs;
+  for (int64_t first = 0; first < a.n; first += MAX_GRID * per) {
+    SynthArgs p = a;
+    p.n = a.n - first < MAX_GRID * per ? a.n - first : MAX_GRID * per;
+    p.params += first * NPAR;
+    p.stokes += first * row;
+    if (p.noise) p.noise += first * row;
+    if (p.jac) p.jac += first * row * NPAR;
+    kernel<<<(int)((p.n + per - 1) / per), 64, 0, s>>>(p, t, (int)per);
+  }
+}
+
 hipError_t launch_synth_group(const SynthArgs& a, const GroupTables& t, int kind, bool deriv,
                               int num_cus, hipStream_t s) {
   // as many models per wave as leave the chip its waves (12 or 16 with
@@ -1304,13 +1316,12 @@ hipError_t launch_synth_group(const SynthArgs& a, const GroupTables& t, int kind
   const int64_t waves = (int64_t)num_cus * (deriv ? 8 : 16);
   int64_t per = (a.n + waves - 1) / waves;
   if (per > SYNTH_PER[kind]) per = SYNTH_PER[kind];
-  const int grid = (int)((a.n + per - 1) / per);
   if (kind == KIND_BAND) {
-    if (deriv) synth_group_band_kernel<true><<<grid, 64, 0, s>>>(a, t, (int)per);
-    else synth_group_band_kernel<false><<<grid, 64, 0, s>>>(a, t, (int)per);
+    if (deriv) launch_synth_pieces(synth_group_band_kernel<true>, a, t, per, s);
+    else launch_synth_pieces(synth_group_band_kernel<false>, a, t, per, s);
   } else {
-    if (deriv) synth_group_kernel<true><<<grid, 64, 0, s>>>(a, t, (int)per);
-    else synth_group_kernel<false><<<grid, 64, 0, s>>>(a, t, (int)per);
+    if (deriv) launch_synth_pieces(synth_group_kernel<true>, a, t, per, s);
+    else launch_synth_pieces(synth_group_kernel<false>, a, t, per, s);
   }
   return hipGetLastError();
 }

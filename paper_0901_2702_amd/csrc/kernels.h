@@ -74,6 +74,7 @@ struct BatchArgs {
 struct SynthArgs {
   Consts C;
   const Point* pts;
+  const Block* blocks;
   const float* row_sums;
   const float* params;
   const float* noise;
@@ -97,7 +98,8 @@ hipError_t launch_hist(const int32_t* iters, int64_t n, int n_bins, unsigned lon
                        int max_blocks, hipStream_t s);
 hipError_t launch_lm(const LMArgs& a, int kind, int voigt, int grid, hipStream_t s);
 hipError_t launch_lm_batches(const BatchArgs& b, int grid, hipStream_t s);
-hipError_t launch_synth(const SynthArgs& a, int voigt, bool deriv, int grid, hipStream_t s);
+hipError_t launch_synth(const SynthArgs& a, int kind, int voigt, bool deriv, int grid,
+                        hipStream_t s);
 hipError_t launch_solve(const SolveArgs& a, int grid, hipStream_t s);
 // out[p][j] = (I, Q, U, V) of sample j of pixel p, from in = [n][4][n_obs]
 hipError_t launch_interleave(const float* in, float4* out, int64_t n, int n_obs, hipStream_t s);

@@ -11,7 +11,8 @@
 //    pixels with few iterations do not leave lanes idle while other pixels
 //    in the wave still iterate.
 //  * synth_kernel: the same synthesis pass for given models (values and
-//    optional Jacobian), written out (dense; others in group.hip).
+//    optional Jacobian), written out; synth_band_kernel for banded filters.
+//    Small calls and full chunks of points go to group.hip (routes.h).
 //  * solve_kernel: the damped solve alone, for given normal equations.
 #include <hip/hip_runtime.h>
 
@@ -754,13 +755,42 @@ __global__ __launch_bounds__(64) void synth_kernel(const SynthArgs A) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const int64_t r = i * ROWS + s * NOBS + o;
-        A.stokes[r] = A.noise ? S[s] + A.noise[r] : S[s];
+        A.stokes[r] = A.noise ? plus_noise(S[s], A.noise[r]) : S[s];
         if (DERIV) {
 #pragma unroll
           for (int p = 0; p < NPAR; ++p) A.jac[r * NPAR + p] = J[s][p];
         }
       }
     }
+  }
+}
+
+// Synthesis through a banded instrument: rows are written as they complete.
+template <bool DERIV>
+__global__ __launch_bounds__(64) void synth_band_kernel(const SynthArgs A) {
+  const int no = A.C.n_obs;
+  for (int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x; i < A.n;
+       i += (int64_t)gridDim.x * 64) {
+    float M[NPAR];
+#pragma unroll
+    for (int q = 0; q < NPAR; ++q) M[q] = A.params[i * NPAR + q];
+    Pix px;
+    pix_setup(M, A.C, px);
+    RowFactors rf;
+    row_factors(M, px, A.C, rf);
+    band_accumulate<DERIV>(A.blocks, no, px, A.C, [](int) {}, [&](int j, const float* a) {
+      float S[4], J[4][NPAR];
+      assemble_sample<DERIV>(a, A.row_sums[j], rf, S, J);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int64_t r = i * (int64_t)(4 * no) + s * no + j;
+        A.stokes[r] = A.noise ? plus_noise(S[s], A.noise[r]) : S[s];
+        if (DERIV) {
+#pragma unroll
+          for (int p = 0; p < NPAR; ++p) A.jac[r * NPAR + p] = J[s][p];
+        }
+      }
+    });
   }
 }
 
@@ -883,8 +913,12 @@ hipError_t launch_lm_batches(const BatchArgs& b, int grid, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_synth(const SynthArgs& a, int voigt, bool deriv, int grid, hipStream_t s) {
-  if (voigt == 1) {
+hipError_t launch_synth(const SynthArgs& a, int kind, int voigt, bool deriv, int grid,
+                        hipStream_t s) {
+  if (kind == KIND_BAND) {
+    if (deriv) synth_band_kernel<true><<<grid, 64, 0, s>>>(a);
+    else synth_band_kernel<false><<<grid, 64, 0, s>>>(a);
+  } else if (voigt == 1) {
     if (deriv) synth_kernel<NOBS_HMI, true, 1><<<grid, 64, 0, s>>>(a);
     else synth_kernel<NOBS_HMI, false, 1><<<grid, 64, 0, s>>>(a);
   } else if (voigt == 2) {

@@ -84,6 +84,12 @@ __device__ __forceinline__ double rounded(double x) {
   return x;
 }
 
+// A Stokes value (rounded, as stored without noise) and its noise.
+__device__ __forceinline__ float plus_noise(float S, float noise) {
+#pragma clang fp contract(off)
+  return S + noise;
+}
+
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
 // Instrument tables are written once, before any launch, and only read by

@@ -1,6 +1,7 @@
 // Which kernel takes a call, by the sizes of the instrument and of the call:
-// the group inverter (group.hip: a wave per few pixels, a synthesis point per
-// lane) or a pixel per lane (kernels.hip).  The results are the same bits.  Host code that needs no HIP, so that the rules can be
+// the group inverter and its synthesis (group.hip: a wave per few pixels, a
+// synthesis point per lane) or a pixel per lane (kernels.hip).  The results
+// are the same bits.  Host code that needs no HIP, so that the rules can be
 // held against the measured times on the CPU.
 #pragma once
 
@@ -74,6 +75,40 @@ inline int64_t fit_group_max(const Extent& e, FitUse use, int max_iter) {
   else if (max_iter < 10) few = e.chunks > 1 ? 49152 : 24576;
   if (max_iter == 0 && e.chunks > 5) few = GROUP_ANY;
   return most < few ? most : few;
+}
+
+// Whether the synthesis of n models (Weideman's series) goes to waves of a few
+// models.  As above: a model per lane takes the points' time whatever n is, up
+// to 65,536 models and more, waves of a few models whole chunks' time per
+// model.  Measured, model per lane / here:
+//  dense, values: 7 points 8,192 1.00, 16,384 0.80, 1,000,000 0.36; 29 points
+//   30,011 1.04, 65,536 0.83; 59 points 90,000 1.14, 131,072 0.95; 64 points
+//   200,000 1.02.
+//  dense, with Jacobian: 7 points 8,192 0.96, 16,384 0.79; 29 points 30,011
+//   1.03, 45,000 0.91; 45 points 65,536 1.07, 131,072 0.89; 52 points and more
+//   at any size (52 262,144 1.05, 59 1.12).
+//  banded, values: 1 sample 16,384 1.44, 30,011 0.65, 1,000,000 0.30; 8 samples
+//   45,000 0.99; 10 45,000 1.08, 1,000,000 0.90; 13 (a full chunk) and more at
+//   any size except a mostly empty second chunk: 14 30,011 1.09, 45,000 0.92;
+//   16 30,011 1.20, 65,536 0.68; 20 1,000,000 1.49, 30 1.55, 112 2.10.
+//  banded, with Jacobian: 1 sample 8,192 1.09, 30,011 0.50, 1,000,000 0.23; 8
+//   samples 16,384 1.40, 45,000 0.67, 1,000,000 0.92; 14 16,384 1.24, 30,011
+//   0.86; instruments whose chunks are nearly full at any size but for a dip
+//   where the lanes are just filled: 20 30,011 1.10, 45,000 0.77, 65,536 0.82,
+//   114,688 1.10, 1,000,000 1.23; 30 45,000 0.73, 114,688 1.10, 1,000,000 1.25;
+//   46 45,000 0.96, 112 1.24.
+inline bool synth_by_group(const Extent& e, int64_t n, bool jac) {
+  if (e.chunks < 1) return false;
+  if (!e.band) {
+    if (e.points <= 29) return n <= (jac ? 1000 : 1200) * (int64_t)e.points;
+    if (jac) return e.points >= 50 || n <= 29000 + 3000 * (int64_t)(e.points - 29);
+    return n <= 34798 + 2663 * (int64_t)(e.points - 29);
+  }
+  const double fill = e.points / (64.0 * e.chunks);
+  if (n <= (jac ? 600 : 900) * (int64_t)e.points / e.chunks) return true;
+  if (!jac) return fill >= (e.chunks == 1 ? 0.95 : 0.64);
+  if (fill < (e.chunks == 1 ? 0.78 : 0.64)) return false;
+  return fill >= 0.95 || e.chunks > 3 || n >= (e.chunks == 1 ? 196608 : 98304);
 }
 
 }  // namespace vfisv

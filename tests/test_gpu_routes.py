@@ -1,6 +1,7 @@
-"""Which kernel a fit takes (csrc/routes.h), seen in the waves that the launch
-counted: the group inverter below its limit for the instrument's size, a pixel
-per lane (a wave per 64 pixels) above it, with the same bits in both."""
+"""Which kernel a call takes (csrc/routes.h).  Fits, seen in the waves that the
+launch counted: the group inverter below its limit for the instrument's size, a
+pixel per lane (a wave per 64 pixels) above it, with the same bits in both.
+Synthesis: the same bits on both sides of its limits."""
 import numpy as np
 import pytest
 import torch
@@ -50,3 +51,43 @@ def test_small_instruments_and_short_fits(ctx, name, spec, below, above, kw):
         assert (ctx.counters()["grid_waves"] == _lanes(ctx, n)) == lanes, n
         for k in ref:
             assert torch.equal(out[k], ref[k][:n]), (n, k)
+
+
+@pytest.mark.parametrize("name,spec,sizes", [
+    ("7 points", lambda: wl.hmi_instrument(n_fine=13), (5001, 7003, 20001)),
+    ("29 points", lambda: wl.hmi_instrument(n_fine=51), (20001, 31003, 60001)),
+    ("HMI", wl.hmi_instrument, (60001, 114689)),
+    ("1 sample", lambda: wl.fine_instrument(n_obs=1), (8001, 12003, 20001)),
+    ("5 samples", lambda: wl.fine_instrument(n_obs=5), (15001, 25003, 40001)),
+    ("14 samples", lambda: wl.fine_instrument(n_obs=14), (15001, 25003, 40001)),
+    ("20 samples", lambda: wl.fine_instrument(n_obs=20), (20001, 50003, 99001)),
+])
+def test_synthesis_on_both_sides(ctx, name, spec, sizes):
+    spec = spec()
+    inst = vf.Instrument.from_spec(ctx, spec)
+    n = sizes[-1]
+    P = wl.draw_params(n, 62).astype(np.float32)
+    P[3, 5], P[40, 0], P[77, 7] = 1e30, np.inf, np.nan
+    Pd = torch.tensor(P, device=ctx.device)
+    E = torch.tensor(wl.draw_noise(n, spec.n_obs, 63).astype(np.float32), device=ctx.device)
+    print("[gpu] routes synthesis %s" % name, flush=True)
+    S, J = vf.synthesize(ctx, inst, Pd, jac=True)
+    for m in sizes:
+        a = vf.synthesize(ctx, inst, Pd[:m])
+        b, Jb = vf.synthesize(ctx, inst, Pd[:m], noise=E[:m], jac=True)
+        c = vf.synthesize(ctx, inst, Pd[:m], noise=E[:m])
+        for x, y in ((a, S[:m]), (Jb, J[:m]), (b, S[:m] + E[:m]), (c, b)):
+            assert torch.equal(torch.nan_to_num(x, nan=7e33), torch.nan_to_num(y, nan=7e33)), m
+
+
+def test_more_models_than_a_launch_has_lanes_for(ctx):
+    """1,074,790,400 models: at 16 models per wave of 64 lanes more than 2^32 lanes."""
+    inst = vf.Instrument.from_spec(ctx, wl.fine_instrument(n_obs=1))
+    base = torch.tensor(wl.draw_params(1 << 20, 64).astype(np.float32), device=ctx.device)
+    print("[gpu] routes: 1025 x 2^20 models", flush=True)
+    ref = vf.synthesize(ctx, inst, base)
+    S = vf.synthesize(ctx, inst, base.repeat(1025, 1)).view(1025, 1 << 20, 4, 1)
+    for k in (0, 511, 1023, 1024):
+        assert torch.equal(S[k], ref), k
+    del S
+    torch.cuda.empty_cache()

@@ -51,6 +51,29 @@ FITS = [
     (1, 460, 8, "PLAIN", 3, 32768, 57344),
 ]
 
+# (band, points, chunks, with Jacobian, sizes faster in groups, sizes faster in lanes)
+SYNTH = [
+    (0, 7, 1, 0, (64, 4096, 8192), (16384, 131072, 1000000)),
+    (0, 7, 1, 1, (64, 4096), (16384, 131072, 524288)),
+    (0, 29, 1, 0, (64, 30011), (65536, 131072, 1000000)),
+    (0, 29, 1, 1, (64, 16384), (45000, 131072, 524288)),
+    (0, 45, 1, 1, (64, 65536), (131072,)),
+    (0, 59, 1, 0, (64, 65536, 114688), (114689, 131072, 262144)),
+    (0, 59, 1, 1, (64, 65536, 262144, 524288), ()),
+    (1, 16, 1, 0, (64, 8192), (30011, 131072, 1000000)),
+    (1, 16, 1, 1, (64, 8192), (16384, 131072, 1000000)),
+    (1, 32, 1, 0, (64, 16384), (45000, 131072, 1000000)),
+    (1, 44, 1, 1, (64, 16384), (45000, 131072, 1000000)),
+    (1, 64, 1, 0, (64, 30011, 131072, 1000000), ()),
+    (1, 64, 1, 1, (64, 30011, 131072, 1000000), ()),
+    (1, 68, 2, 0, (64, 30011), (65536, 131072, 1000000)),
+    (1, 68, 2, 1, (64, 16384), (30011, 65536, 1000000)),
+    (1, 92, 2, 0, (64, 30011, 131072, 1000000), ()),
+    (1, 92, 2, 1, (64, 16384, 131072, 1000000), (45000, 65536)),
+    (1, 460, 8, 0, (64, 30011, 131072, 1000000), ()),
+    (1, 460, 8, 1, (64, 30011, 65536, 262144), ()),
+]
+
 
 @pytest.fixture(scope="module")
 def answers(tmp_path_factory):
@@ -63,6 +86,11 @@ def answers(tmp_path_factory):
                    % (band, pts, ch, use, it))
     src.append('  printf("%lld\\n", (long long)fit_group_max({false, 59, 1}, FIT_SCHEDULED, 50));')
     src.append('  printf("%lld\\n", (long long)fit_group_max({false, 117, 0}, FIT_PLAIN, 50));')
+    for band, pts, ch, jac, group, lanes in SYNTH:
+        for n in group + lanes:
+            src.append('  printf("%%d\\n", (int)synth_by_group({%d, %d, %d}, %d, %d));'
+                       % (band, pts, ch, n, jac))
+    src.append('  printf("%d\\n", (int)synth_by_group({false, 117, 0}, 1, true));')
     (d / "r.cpp").write_text("\n".join(src + ["}"]))
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "r.cpp"), "-o",
                     str(d / "r")], check=True, capture_output=True)
@@ -78,4 +106,11 @@ def test_fits_go_where_they_were_measured_faster(answers, i):
 
 
 def test_schedules_and_instruments_without_tables_stay_with_the_lanes(answers):
-    assert answers[len(FITS):] == [0, 0]
+    assert answers[len(FITS):len(FITS) + 2] == [0, 0] and answers[-1] == 0
+
+
+def test_synthesis_goes_where_it_was_measured_faster(answers):
+    got = iter(answers[len(FITS) + 2:])
+    for band, pts, ch, jac, group, lanes in SYNTH:
+        for n in group + lanes:
+            assert next(got) == (n in group), (band, pts, ch, jac, n)
