@@ -753,8 +753,11 @@ __device__ __forceinline__ double over(double s, const Root& R) {
 }
 
 // Cholesky factorisation of L (packed, lower) and both substitutions for the
-// right-hand side y, in place.  Returns 0, or 1 where it has broken down or
-// root_of and over do not give IEEE's bits (solve_wave then takes the step).
+// right-hand side y, in place.  Returns 0; 1 where root_of and over may not
+// give IEEE's bits (solve_wave then takes the step); 3 where it has broken down
+// in IEEE's bits too: the first pivot out of order (root NaN) is not positive,
+// or infinite or NaN, and all before it are exact (left to the plain
+// factorisation first, 300,000 singular systems took 31.1 ms instead of 26.2).
 __device__ __forceinline__ int factor_solve(double* L, double* y) {
   Root R[NPAR];
   bool ok = true;
@@ -775,7 +778,14 @@ __device__ __forceinline__ int factor_solve(double* L, double* y) {
       L[pk(i, j)] = s * R[j].rl;
     }
   }
-  if (!ok || ones == ~0u) return 1;
+  if (!ok || ones == ~0u) {
+#pragma unroll
+    for (int j = 0; j < NPAR; ++j) {
+      if (R[j].l != R[j].l) return 3;
+      if (!(R[j].l > 1e-100 && R[j].l < 1e100) || all_ones(R[j].l) == ~0u) return 1;
+    }
+    return 1;
+  }
 #pragma unroll
   for (int i = 0; i < NPAR; ++i) {
     double s = y[i];
@@ -797,8 +807,8 @@ __device__ __forceinline__ int factor_solve(double* L, double* y) {
 // Damped solve in float64 (Eqs. 3-5 with the diagonal scaled by 1 + eps):
 // equilibrate C = D^-1/2 H D^-1/2, Cholesky of C + eps I; frozen or
 // leverage-free parameters are decoupled (unit row, zero right-hand side).
-// Returns 0 on success, 1 if the caller is to run solve_wave, 2 if nothing is
-// free.
+// Returns 0 on success, 1 or 3 if the caller is to run solve_wave (3: its
+// eigen fallback), 2 if nothing is free.
 __device__ __forceinline__ int solve_cholesky(const float* H, const float* g, double eps,
                                               uint32_t free_mask, double* delta) {
   double maxd = 0.0;
@@ -823,7 +833,8 @@ __device__ __forceinline__ int solve_cholesky(const float* H, const float* g, do
     L[pk(p, p)] = (sc[p] != 0.0) ? 1.0 + eps : 1.0;
     y[p] = sc[p] * (double)g[p];
   }
-  if (factor_solve(L, y) != 0) return 1;
+  const int left = factor_solve(L, y);
+  if (left != 0) return left;
 #pragma unroll
   for (int p = 0; p < NPAR; ++p) delta[p] = rounded(sc[p] * y[p]);
   return 0;
@@ -1004,10 +1015,12 @@ __device__ __noinline__ bool solve_plain_wave(const float* H, int hs, const floa
 }
 
 // A step that factor_solve has left: solve_plain_wave's, or if that breaks
-// down the eigen fallback's (returns true).
+// down, as the first factorisation may have already, the eigen fallback's
+// (returns true).
 __device__ __forceinline__ bool solve_wave(const float* H, int hs, const float* g, int gs,
-                                           double eps, uint32_t free_mask, double* sws, int lane) {
-  if (solve_plain_wave(H, hs, g, gs, eps, free_mask, sws)) return false;
+                                           double eps, uint32_t free_mask, bool broken, double* sws,
+                                           int lane) {
+  if (!broken && solve_plain_wave(H, hs, g, gs, eps, free_mask, sws)) return false;
   solve_eigen_wave(H, hs, g, gs, eps, free_mask, sws, lane);
   return true;
 }
