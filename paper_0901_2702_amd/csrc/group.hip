@@ -240,7 +240,8 @@ __device__ __forceinline__ void scale_entry(EqLds& E, int e, int p, int q) {
   else E.b[p] = E.sc[p] * (double)E.hg[55 + p];
 }
 
-// The step of solve_cholesky from an equilibrated system, and what it returns.
+// The step of solve_cholesky from an equilibrated system.  Returns 0, 1 (left
+// to solve_wave) or 2 (nothing free).
 __device__ __forceinline__ int solve_equilibrated(const EqLds& E, double eps, double* delta) {
   double L[55], y[NPAR];
   bool any = false;
@@ -255,8 +256,7 @@ __device__ __forceinline__ int solve_equilibrated(const EqLds& E, double eps, do
     L[pk(p, p)] = (sc != 0.0) ? 1.0 + eps : 1.0;
   }
   if (!any) return 2;
-  const int left = factor_solve(L, y);
-  if (left != 0) return left;
+  if (factor_solve(L, y) != 0) return 1;
 #pragma unroll
   for (int p = 0; p < NPAR; ++p) delta[p] = rounded(E.sc[p] * y[p]);
   return 0;
@@ -867,8 +867,7 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
       const int L = first_slot(fbm);
       double* sws = reinterpret_cast<double*>(S.c2);
       const float* hg = S.slot[L].eq.hg;
-      const bool eigen = solve_wave(hg, 1, hg + 55, 1, __shfl(eps, L), A.free_mask,
-                                    __shfl(Mc[0], L) == 3.f, sws, lane);
+      const bool eigen = solve_wave(hg, 1, hg + 55, 1, __shfl(eps, L), A.free_mask, sws, lane);
       if (lane == L) {
         if (eigen) ++n_fb;
         double Mt[NPAR];
@@ -963,10 +962,8 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
     // ---- damped float64 steps from the best models --------------------------
     if (live) {
       double delta[NPAR];
-      const int code = solve_equilibrated(S.slot[lane].eq, eps, delta);
-      if (code & 1) {
+      if (solve_equilibrated(S.slot[lane].eq, eps, delta) == 1) {
         need_fb = true;  // taken at the top of the next turn, by the whole wave
-        Mc[0] = (float)code;
       } else {
         double Mt[NPAR];
 #pragma unroll

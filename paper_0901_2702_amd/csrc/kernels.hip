@@ -399,8 +399,7 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
   int bad = 0, kr = 0;
   bool pending = false, restart_eval = false;
   // the damped step is left to solve_wave (the eigen fallback): done with the
-  // whole wave at the top of the next turn, where every lane is active; Mc[0]
-  // keeps the code until then
+  // whole wave at the top of the next turn, where every lane is active
   bool need_fb = false;
   // derivative pass due (Fig. 6: derivatives only at accepted models): an
   // accepted trial of a values-only pass waits for the next derivative pass
@@ -479,7 +478,7 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
     for (unsigned long long fbm = __ballot(need_fb); fbm != 0ull; fbm &= fbm - 1ull) {
       const int L = __ffsll((unsigned long long)fbm) - 1;
       const bool eigen = solve_wave(&sHG[L], 64, &sHG[55 * 64 + L], 64, __shfl(eps, L),
-                                    A.free_mask, sHG[HG_MC * 64 + L] == 3.f, sws, lane);
+                                    A.free_mask, sws, lane);
       if (lane == L) {
         if (leader && eigen) ev |= EV_FB;
         double Mt[NPAR];
@@ -659,9 +658,8 @@ __device__ __forceinline__ void lm_loop(const LMArgs& A, float* sHG, float4* sHa
       for (int e = 0; e < NPAR; ++e) g[e] = sHG[(55 + e) * 64 + lane];
       double delta[NPAR];
       const int code = solve_cholesky(H, g, eps, A.free_mask, delta);
-      if (code & 1) {
+      if (code == 1) {
         need_fb = true;  // the step is taken at the top of the next turn
-        Mc[0] = (float)code;
       } else {
         double Mt[NPAR];
 #pragma unroll
@@ -815,13 +813,13 @@ __global__ __launch_bounds__(64) void solve_kernel(const SolveArgs A) {
       eps = A.eps[i];
       code = solve_cholesky(H, g, eps, A.free_mask, delta);
     }
-    for (unsigned long long fbm = __ballot(valid && (code & 1)); fbm != 0ull; fbm &= fbm - 1ull) {
+    for (unsigned long long fbm = __ballot(valid && code == 1); fbm != 0ull; fbm &= fbm - 1ull) {
       const int L = __ffsll((unsigned long long)fbm) - 1;
       const int64_t iL = base + L;
       const bool eigen = solve_wave(A.H + iL * 55, 1, A.g + iL * NPAR, 1, __shfl(eps, L),
-                                    A.free_mask, __shfl(code, L) == 3, sws, lane);
+                                    A.free_mask, sws, lane);
       if (lane == L) {
-        code = eigen ? 1 : 0;
+        if (!eigen) code = 0;
 #pragma unroll
         for (int q = 0; q < NPAR; ++q) delta[q] = sws[200 + q];
       }

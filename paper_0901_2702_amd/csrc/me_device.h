@@ -753,11 +753,8 @@ __device__ __forceinline__ double over(double s, const Root& R) {
 }
 
 // Cholesky factorisation of L (packed, lower) and both substitutions for the
-// right-hand side y, in place.  Returns 0; 1 where root_of and over may not
-// give IEEE's bits (solve_wave then takes the step); 3 where it has broken down
-// in IEEE's bits too: the first pivot out of order (root NaN) is not positive,
-// or infinite or NaN, and all before it are exact (left to the plain
-// factorisation first, 300,000 singular systems took 31.1 ms instead of 26.2).
+// right-hand side y, in place.  Returns 0, or 1 where it has broken down or
+// root_of and over do not give IEEE's bits (solve_wave then takes the step).
 __device__ __forceinline__ int factor_solve(double* L, double* y) {
   Root R[NPAR];
   bool ok = true;
@@ -778,14 +775,7 @@ __device__ __forceinline__ int factor_solve(double* L, double* y) {
       L[pk(i, j)] = s * R[j].rl;
     }
   }
-  if (!ok || ones == ~0u) {
-#pragma unroll
-    for (int j = 0; j < NPAR; ++j) {
-      if (R[j].l != R[j].l) return 3;
-      if (!(R[j].l > 1e-100 && R[j].l < 1e100) || all_ones(R[j].l) == ~0u) return 1;
-    }
-    return 1;
-  }
+  if (!ok || ones == ~0u) return 1;
 #pragma unroll
   for (int i = 0; i < NPAR; ++i) {
     double s = y[i];
@@ -807,8 +797,8 @@ __device__ __forceinline__ int factor_solve(double* L, double* y) {
 // Damped solve in float64 (Eqs. 3-5 with the diagonal scaled by 1 + eps):
 // equilibrate C = D^-1/2 H D^-1/2, Cholesky of C + eps I; frozen or
 // leverage-free parameters are decoupled (unit row, zero right-hand side).
-// Returns 0 on success, 1 or 3 if the caller is to run solve_wave (3: its
-// eigen fallback), 2 if nothing is free.
+// Returns 0 on success, 1 if the caller is to run solve_wave, 2 if nothing is
+// free.
 __device__ __forceinline__ int solve_cholesky(const float* H, const float* g, double eps,
                                               uint32_t free_mask, double* delta) {
   double maxd = 0.0;
@@ -833,8 +823,7 @@ __device__ __forceinline__ int solve_cholesky(const float* H, const float* g, do
     L[pk(p, p)] = (sc[p] != 0.0) ? 1.0 + eps : 1.0;
     y[p] = sc[p] * (double)g[p];
   }
-  const int left = factor_solve(L, y);
-  if (left != 0) return left;
+  if (factor_solve(L, y) != 0) return 1;
 #pragma unroll
   for (int p = 0; p < NPAR; ++p) delta[p] = rounded(sc[p] * y[p]);
   return 0;
@@ -959,68 +948,63 @@ __device__ __noinline__ void solve_eigen_wave(const float* H, int hs, const floa
   __syncthreads();
 }
 
-// The Cholesky step in IEEE's own square roots and quotients, in rolled loops
-// and the same on every lane (all write the same values to the same places).
-// Returns whether the factorisation held.
+__device__ __forceinline__ double from_lane(double x, int k) {  // k the same on every lane
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), k),
+                          __builtin_amdgcn_readlane(__double2loint(x), k));
+}
+
+// The Cholesky step in IEEE's own square roots and quotients, for the whole
+// wave: lane p < 10 holds row p.  Returns whether the factorisation held.
+// (A row per lane: with the rows one after the other on every lane it was a
+// sixth of the eigen fallback's time, which mostly follows it: 262,144 HMI
+// fits with three weighted samples, 196,429 fallbacks, 42.5 ms.)
 __device__ __noinline__ bool solve_plain_wave(const float* H, int hs, const float* g, int gs,
-                                              double eps, uint32_t free_mask, double* sws) {
-  double *L = sws, *rl = sws + 55, *y = sws + 60, *sc = sws + 100;
+                                              double eps, uint32_t free_mask, double* sws, int lane) {
+  const int p = lane < NPAR ? lane : NPAR - 1;
   double maxd = 0.0;
-#pragma unroll 1
-  for (int p = 0; p < NPAR; ++p)
-    if ((free_mask >> p) & 1u) maxd = fmax(maxd, (double)H[pk(p, p) * hs]);
-#pragma unroll 1
-  for (int p = 0; p < NPAR; ++p) {
-    const double d = (double)H[pk(p, p) * hs];
-    const bool act = ((free_mask >> p) & 1u) && maxd > 0.0 && d > 1e-30 * maxd;
-    sc[p] = act ? 1.0 / sqrt(d) : 0.0;
-    y[p] = sc[p] * (double)g[p * gs];
+#pragma unroll
+  for (int k = 0; k < NPAR; ++k)
+    if ((free_mask >> k) & 1u) maxd = fmax(maxd, (double)H[pk(k, k) * hs]);
+  const double d = (double)H[pk(p, p) * hs];
+  const bool act = ((free_mask >> p) & 1u) && maxd > 0.0 && d > 1e-30 * maxd;
+  const double sc = act ? 1.0 / sqrt(d) : 0.0;
+  double y = sc * (double)g[p * gs];
+  double L[NPAR], l[NPAR];  // row p (its first p elements count); the pivots' roots
+#pragma unroll
+  for (int j = 0; j < NPAR; ++j) {
+    double s = p > j ? sc * (double)H[pk(p, p > j ? j : p) * hs] * from_lane(sc, j)
+                     : sc != 0.0 ? 1.0 + eps : 1.0;
+#pragma unroll
+    for (int k = 0; k < j; ++k) s = fma(-L[k], from_lane(L[k], j), s);
+    const double piv = from_lane(s, j);
+    if (!(piv > 0.0 && piv < 1.0e300)) return false;
+    l[j] = sqrt(fmax(piv, 1e-300));
+    const double rl = 1.0 / l[j];
+    L[j] = s * rl;
   }
-  bool ok = true;
-#pragma unroll 1
-  for (int j = 0; j < NPAR; ++j)
-#pragma unroll 1
-    for (int i = j; i < NPAR; ++i) {
-      double s = i > j ? sc[i] * (double)H[pk(i, j) * hs] * sc[j] : sc[j] != 0.0 ? 1.0 + eps : 1.0;
-#pragma unroll 1
-      for (int k = 0; k < j; ++k) s = fma(-L[pk(i, k)], L[pk(j, k)], s);
-      if (i == j) {
-        ok = ok && s > 0.0 && s < 1.0e300;
-        s = sqrt(fmax(s, 1e-300));
-        *rl = 1.0 / s;
-      } else {
-        s = s * *rl;
-      }
-      L[pk(i, j)] = s;
-    }
-  if (ok) {
-#pragma unroll 1
-    for (int i = 0; i < NPAR; ++i) {
-      double s = y[i];
-#pragma unroll 1
-      for (int k = 0; k < i; ++k) s = fma(-L[pk(i, k)], y[k], s);
-      y[i] = s / L[pk(i, i)];
-    }
-#pragma unroll 1
-    for (int i = NPAR - 1; i >= 0; --i) {
-      double s = y[i];
-#pragma unroll 1
-      for (int k = i + 1; k < NPAR; ++k) s = fma(-L[pk(k, i)], y[k], s);
-      y[i] = s / L[pk(i, i)];
-      sws[200 + i] = sc[i] * y[i];
-    }
+  double z[NPAR];
+#pragma unroll
+  for (int i = 0; i < NPAR; ++i) {
+    z[i] = from_lane(y, i) / l[i];
+    y = fma(-L[i], z[i], y);
+  }
+#pragma unroll
+  for (int i = NPAR - 1; i >= 0; --i) {
+    double s = z[i];
+#pragma unroll
+    for (int k = i + 1; k < NPAR; ++k) s = fma(-from_lane(L[i], k), z[k], s);
+    z[i] = s / l[i];
+    sws[200 + i] = from_lane(sc, i) * z[i];
   }
   __syncthreads();
-  return ok;
+  return true;
 }
 
 // A step that factor_solve has left: solve_plain_wave's, or if that breaks
-// down, as the first factorisation may have already, the eigen fallback's
-// (returns true).
+// down the eigen fallback's (returns true).
 __device__ __forceinline__ bool solve_wave(const float* H, int hs, const float* g, int gs,
-                                           double eps, uint32_t free_mask, bool broken, double* sws,
-                                           int lane) {
-  if (!broken && solve_plain_wave(H, hs, g, gs, eps, free_mask, sws)) return false;
+                                           double eps, uint32_t free_mask, double* sws, int lane) {
+  if (solve_plain_wave(H, hs, g, gs, eps, free_mask, sws, lane)) return false;
   solve_eigen_wave(H, hs, g, gs, eps, free_mask, sws, lane);
   return true;
 }

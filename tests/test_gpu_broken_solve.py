@@ -1,5 +1,5 @@
 """Damped systems whose factorisation breaks down at one pivot after the other
-go to the eigen fallback, with the pseudo-inverse's step (singular values below
+end in the eigen fallback, with the pseudo-inverse's step (singular values below
 1e-12 of the largest discarded); systems with a tiny or a huge pivot, which it
 leaves to plain divisions, keep the Cholesky step."""
 import numpy as np
