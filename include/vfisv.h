@@ -208,7 +208,8 @@ typedef struct {
   int64_t accepts;        /* accepted trials                                */
   int64_t passes;         /* synthesis passes executed (trials + initial)   */
   int64_t svd_fallbacks;  /* solves that needed the eigen/SVD fallback      */
-  int64_t grid_waves;     /* waves launched                                 */
+  int64_t grid_waves;     /* waves launched, less those of a kernel that ended */
+                          /* at once because another had the pixels          */
   int64_t hessians;       /* J^T W J updates: initial, restart and accepted */
                           /* models, less those kept by hess_reuse          */
   int64_t derivative_passes; /* passes that computed the Jacobian (all of   */

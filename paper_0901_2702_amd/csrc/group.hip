@@ -801,7 +801,7 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
   const int lane = threadIdx.x;
   const bool serve = n_total <= (unsigned long long)ga.n_max;
   if (A.n_dev && blockIdx.x == 0 && lane == 0) A.work[GROUP_LEFT_SLOT] = serve ? 0ull : n_total;
-  if (!serve) return;
+  if (!serve || blockIdx.x >= n_total) return;
   // the launch's own rule for lane pairs, whose sums differ by rounding
   const bool pair = A.lpp_max >= 2 && n_total <= (unsigned long long)A.pair_max;
   Layout<BAND> lay(S, ga, lane, pair);

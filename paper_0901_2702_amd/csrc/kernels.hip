@@ -703,8 +703,9 @@ __global__ __launch_bounds__(64) void lm_kernel(const LMArgs A) {
   double* sws = ws_record(sHa);
   const int lane = threadIdx.x;
   const int64_t glane = (int64_t)blockIdx.x * 64 + lane;
+  const unsigned long long n_total = A.n_dev ? *A.n_dev : (unsigned long long)A.n;
+  if (n_total == 0) return;
   if constexpr (NOBS > 0) {
-    const unsigned long long n_total = A.n_dev ? *A.n_dev : (unsigned long long)A.n;
     const bool pairs = A.lpp_max >= 2 && n_total <= (unsigned long long)A.pair_max;
     if (pairs != (LPP == 2)) return;
   }
@@ -726,6 +727,7 @@ __global__ __launch_bounds__(64) void lm_batches_kernel(const BatchArgs B) {
   const int64_t glane = (int64_t)blockIdx.x * 64 + lane;
   WaveCounters wc;
   for (int i = 0; i < B.n_batches; ++i) {
+    if (B.a[i].n == 0) continue;  // empty, or the group inverter's
     if (B.kind[i] == KIND_DENSE6)
       lm_loop<NOBS_HMI, 1, 0, false, SPLIT>(B.a[i], sHG, sHa, sws, lane, glane, wc);
     else

@@ -1,7 +1,9 @@
 """Which kernel a call takes (csrc/routes.h).  Fits, seen in the waves that the
 launch counted: the group inverter below its limit for the instrument's size, a
 pixel per lane (a wave per 64 pixels) above it, with the same bits in both.
-Synthesis: the same bits on both sides of its limits."""
+Re-fits, whose count only the device knows: the kernel that has nothing to do
+ends at once and counts no waves.  Synthesis: the same bits on both sides of its
+limits."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +13,7 @@ import workloads as wl
 pytestmark = pytest.mark.gpu
 
 vf = pytest.importorskip("paper_0901_2702_amd")
+from paper_0901_2702_amd import learned  # noqa: E402
 
 LANES = dict(chunk_log2=8)  # an explicit schedule: a pixel per lane
 
@@ -51,6 +54,36 @@ def test_small_instruments_and_short_fits(ctx, name, spec, below, above, kw):
         assert (ctx.counters()["grid_waves"] == _lanes(ctx, n)) == lanes, n
         for k in ref:
             assert torch.equal(out[k], ref[k][:n]), (n, k)
+
+
+@pytest.mark.parametrize("n,refit,kernels", [
+    (3000, False, ("group",)),
+    (3000, True, ("group", "group")),
+    (60001, False, ("lanes",)),          # above the short fit's limit, nothing to re-fit
+    (60001, True, ("lanes", "lanes")),   # more re-fits than the group inverter takes
+])
+def test_learned_path_counts_the_waves_that_worked(ctx, n, refit, kernels):
+    """An untrained network: every fit is above (refit) or below the threshold."""
+    inst, o, W = _inputs(ctx, wl.hmi_instrument(), 3000, 65)
+    o = o.repeat(21, 1, 1)[:n].contiguous()
+    rng = np.random.default_rng(66)
+    net = learned.Mlp(ctx, 24, rng.normal(size=24) * 0.01, np.full(24, 0.05),
+                      np.array([0.0, 35.0, 0.25, 15.5, 0.3, 0.7, 0.6]),
+                      np.array([1.7, 8.7, 0.14, 8.4, 0.12, 0.12, 0.23]), seed=1)
+    tau = 1e-9 if refit else 1e30
+    print("[gpu] routes learned n=%d refit=%s" % (n, refit), flush=True)
+    ref = learned.invert_learned(ctx, inst, net, o, W, opts=vf.Options(**LANES), chi2_accept=tau)
+    out = learned.invert_learned(ctx, inst, net, o, W, chi2_accept=tau)
+    waves = ctx.counters()["grid_waves"]
+    for k in ref:
+        assert torch.equal(out[k], ref[k]), k
+    assert int((out["status"] & vf.FALLBACK_USED).ne(0).sum()) == (n if refit else 0)
+    cus = torch.cuda.get_device_properties(ctx.device).multi_processor_count
+    group = waves // len(kernels)
+    want = {"lanes": _lanes(ctx, n), "group": group}
+    assert waves == sum(want[k] for k in kernels)
+    if "group" in kernels:  # one or two full waves of it per SIMD
+        assert group in (min(n, 4 * cus), min(n, 8 * cus))
 
 
 @pytest.mark.parametrize("name,spec,sizes", [
