@@ -43,7 +43,8 @@ constexpr int64_t GROUP_ANY = INT64_MAX;
 //  banded, short: 5 samples 16,384 1.41, 32,768 0.81; 14 32,768 1.16, 65,536
 //   0.75; 20 57,344 1.08, 131,072 0.97; 112 131,072 1.29, 262,144 1.07.
 //   Re-fits: 8 samples 57,344 1.00; 14 98,304 1.04, 163,840 0.88; 20 262,144
-//   1.05; 112 262,144 1.44.
+//   1.05; 112 262,144 1.44; after a network that has learned nothing (more
+//   trials each) 14 32,768 1.25, 65,536 0.77; 20 57,344 1.11, 65,536 0.95.
 // A banded limit is n0 rho / (1 - rho), rho being the ratio of the two costs
 // per pixel in large launches and n0 the pixels that the flat part is worth.
 // (131,072 in the learned path is no crossover for wide spectra: both sides
@@ -58,7 +59,7 @@ inline int64_t fit_group_max(const Extent& e, FitUse use, int max_iter) {
   const bool plain = use == FIT_PLAIN;
   int64_t most;
   if (e.band) {
-    const double n0[3][3] = {{26e3, 35e3, 58e3}, {18e3, 20e3, 20e3}, {26e3, 60e3, 60e3}};
+    const double n0[3][3] = {{26e3, 35e3, 58e3}, {18e3, 20e3, 20e3}, {26e3, 30e3, 45e3}};
     const double rho = (0.6 * e.points + 10.0) / (32.0 * e.chunks + 22.0);
     most = plain ? GROUP_ANY : 131072;
     if (rho < 0.97) {

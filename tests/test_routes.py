@@ -40,6 +40,7 @@ FITS = [
     (1, 92, 2, "SHORT", 15, 57344, 262144),
     (1, 460, 8, "SHORT", 15, 131072, None),
     (1, 44, 1, "REFIT", 50, 45056, 163840),
+    (1, 68, 2, "REFIT", 50, 32768, 65536),
     (1, 460, 8, "REFIT", 50, 131072, None),
     # few trials: the set-up of a pixel counts
     (0, 59, 1, "PLAIN", 0, 64, 1024),
