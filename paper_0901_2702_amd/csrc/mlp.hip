@@ -169,7 +169,8 @@ constexpr size_t train_lds_bytes(int K0) {
 // there (in float32) for the way back.  256 workgroups for a batch of 4,096
 // (RB = 1); RB = 2 halves the weights' reads, which tells only where they are
 // the larger part of the traffic: 524,288 rows 4.3 ms with RB = 1, 4.05 with
-// RB = 2, 65,536 equal, 16,384 138 us against 142.
+// RB = 2, 65,536 equal, 16,384 138 us against 142.  (RB = 2 does not fit the
+// registers: 256 bytes of scratch per lane, in those times.)
 template <int RB>
 __global__ __launch_bounds__(TW * 64, 2) void train_rows_kernel(const TrainRowsArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -186,9 +187,13 @@ __global__ __launch_bounds__(TW * 64, 2) void train_rows_kernel(const TrainRowsA
   const unsigned nb = gridDim.x, b = blockIdx.x;
   const int64_t m0 = (int64_t)(nb % 8 == 0 ? (b % 8) * (nb / 8) + b / 8 : b) * R;
   constexpr int NH = MLP_H / 32;
-  TrainW<1> w1;
+  // the first layer's weights, NF k-steps ahead (a step of 32 rows of 1,248
+  // inputs 90 us with one at a time, 78 like this)
+  constexpr int NF = 4;
+  TrainW<1> w0[NF];
+  TrainW<1>& w1 = w0[0];
   TrainW<NH> wa, wb;
-  const bool one_step = a.K0 == 32;
+  const int steps = a.K0 / 32;
   // inputs, and the targets of this thread's outputs
   for (int i = tid; i < R * a.K0; i += NT) {
     const int r = i / a.K0, k = i - r * a.K0;
@@ -203,7 +208,12 @@ __global__ __launch_bounds__(TW * 64, 2) void train_rows_kernel(const TrainRowsA
     const int64_t src = a.rows ? (int64_t)a.rows[m0 + r] : m0 + r;
     target[i] = c < MLP_NCODE ? a.targets[src * MLP_NCODE + c] : 0.f;
   }
-  if (one_step) w1.fetch(a.Wt[0], 32, wave, l);
+  w1.fetch(a.Wt[0], a.K0, wave, l);
+  if (steps > 1) {
+#pragma unroll
+    for (int i = 1; i < NF; ++i)
+      if (i < steps) w0[i].fetch(a.Wt[0] + 32 * i, a.K0, wave, l);
+  }
   float bias[3][TCB];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -229,12 +239,16 @@ __global__ __launch_bounds__(TW * 64, 2) void train_rows_kernel(const TrainRowsA
   f32x4 acc[RB][TCB];
   // first layer: xs -> h0
   zero(acc);
-  if (one_step) {
+  if (steps == 1) {
     train_product<RB, 1>(xs, ldx, w1, acc, l);
   } else {
-    for (int k = 0; k < a.K0; k += 32) {
-      w1.fetch(a.Wt[0] + k, a.K0, wave, l);
-      train_product<RB, 1>(xs + k, ldx, w1, acc, l);
+    for (int k = 0; k < steps; k += NF) {
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        if (k + i >= steps) break;
+        train_product<RB, 1>(xs + 32 * (k + i), ldx, w0[i], acc, l);
+        if (k + i + NF < steps) w0[i].fetch(a.Wt[0] + 32 * (k + i + NF), a.K0, wave, l);
+      }
     }
   }
   const auto hidden = [&](int layer, bf16* h) {
