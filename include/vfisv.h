@@ -206,7 +206,9 @@ typedef struct {
   int64_t pixels;         /* pixels finished                                */
   int64_t trials;         /* trial syntheses (sum of iters)                 */
   int64_t accepts;        /* accepted trials                                */
-  int64_t passes;         /* synthesis passes executed (trials + initial)   */
+  int64_t passes;         /* synthesis passes executed: starts, trials and,  */
+                          /* where trials run without derivatives, the       */
+                          /* derivative passes of accepted models            */
   int64_t svd_fallbacks;  /* solves that needed the eigen/SVD fallback      */
   int64_t grid_waves;     /* waves launched, less those of a kernel that ended */
                           /* at once because another had the pixels          */

@@ -956,6 +956,7 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
     const unsigned keep = (unsigned)__ballot(want_j && keep_h);
     if (want_j) {
       ++n_jac;
+      if (it > 0) ++n_pass;  // (a start's values and Jacobian count as one pass)
       if (!keep_h) ++n_hess;
     }
     if (jm != 0u) lay.normal(jm, keep, pix, cp, cq);

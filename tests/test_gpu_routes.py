@@ -56,6 +56,23 @@ def test_small_instruments_and_short_fits(ctx, name, spec, below, above, kw):
             assert torch.equal(out[k], ref[k][:n]), (n, k)
 
 
+@pytest.mark.parametrize("name,spec", [("HMI", wl.hmi_instrument), ("spectra", wl.fine_instrument)])
+def test_derivative_passes_are_passes(ctx, name, spec):
+    """The group inverter's trials run without derivatives; each accepted model
+    that goes on has a derivative pass, a start has one pass for both."""
+    inst, o, W = _inputs(ctx, spec(), 500, 67)
+    print("[gpu] routes: passes of %s" % name, flush=True)
+    vf.invert(ctx, inst, o, W)
+    c = ctx.counters()
+    assert c["derivative_passes"] == c["jacobians"]
+    assert c["passes"] == c["trials"] + c["jacobians"] and c["jacobians"] > c["pixels"] == 500
+    vf.invert(ctx, inst, o, W, opts=vf.Options(deriv_split=4))
+    d = ctx.counters()
+    for k in ("trials", "accepts", "jacobians"):
+        assert d[k] == c[k], k
+    assert d["derivative_passes"] >= c["derivative_passes"] and d["passes"] > d["derivative_passes"]
+
+
 @pytest.mark.parametrize("n,refit,kernels", [
     (3000, False, ("group",)),
     (3000, True, ("group", "group")),
