@@ -339,10 +339,19 @@ int vfisv_invert_batches(vfisv_ctx *ctx, const vfisv_batch *batches, int n_batch
  * most 8 pixels per lane on the default grid, one factor for every
  * candidate), so that every lane inverts as many pixels as
  * in the whole launch and the tail weighs about as much as it will there.
- * The fastest is kept for this
- * instrument's layout in the context; later inversions with grid_waves == 0,
- * chunk_log2 == -1 and deriv_split == -1 use it.  default_ms is the time of
- * the untuned default (split VFISV_DERIV_SPLIT_DEFAULT, default schedule).
+ * Where the sample is the whole batch, the group kernel that fits few pixels
+ * (grid_waves above) is timed too, if an untuned context would use it there.
+ * The fastest is kept for this instrument's layout in the context.  Later
+ * inversions that run a pixel per lane take the schedule for every field of
+ * their options that is automatic (grid_waves 0, chunk_log2 -1, deriv_split
+ * -1).  With all three automatic the group kernel goes on taking the launches
+ * that an untuned context gives it, except plain fits of at least n and at most
+ * 1.25 n pixels, above 16,384, where the schedule is kept unless the group
+ * kernel was timed and was faster, or is faster at any size (wide spectra).
+ * So a sample smaller than the batch chooses among schedules alone.
+ * default_ms is the time of an untuned context (the group kernel's, or split
+ * VFISV_DERIV_SPLIT_DEFAULT at the default schedule); the other results
+ * describe the schedule also where the group kernel was faster.
  * Results go to library scratch (the caller's outputs are not touched) and
  * are identical for every candidate, so only speed changes.  Allocates and
  * synchronises: call it at set-up, not under graph capture.  out may be

@@ -394,7 +394,8 @@ def autotune(ctx, inst, stokes, W, opts=None, sample=0):
     """Pick the derivative-pass split, persistent grid and pixel-queue block
     for this instrument's layout by timing them on the first ``sample``
     pixels; later inversions with automatic scheduling options use the
-    choice.  Returns a dict."""
+    choice where they run a pixel per lane (vfisv.h says where that is).
+    Returns a dict."""
     dev = ctx.device
     o = (opts or Options()).c()
     t = _Tuning()

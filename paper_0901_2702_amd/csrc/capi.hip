@@ -165,18 +165,20 @@ static int grow_obs4(vfisv_ctx* ctx, size_t bytes) {
 }
 
 // The largest batch that the group inverter takes under these options
-// (fit_group_max), 0 if none: it has Weideman's series and the fit with
-// convergence exits only.
+// (fit_group_max), 0 if none, for a launch of n pixels: it has Weideman's
+// series and the fit with convergence exits only.
 static int64_t group_limit(const vfisv_ctx* ctx, const vfisv_instrument* inst,
-                           const vfisv_options& o, FitUse use) {
+                           const vfisv_options& o, FitUse use, int64_t n) {
   if (o.voigt != 0 || o.fixed_iters != 0 || o.lanes_per_pixel != 1) return 0;
-  // (Plain HMI fits with a tuned schedule keep it where a schedule matters:
-  // 65,536 pixels 3.45 ms with derivatives in every pass, 3.6 here.  Short fits
-  // and re-fits have no tuned split, fine spectra are faster here than with
-  // any: 65,536 of them 30.4 ms, 20.0 here.)
   const int64_t most = fit_group_max(inst->extent, use, o.max_iter);
-  const bool tuned = inst->kind == KIND_DENSE6 && use == FIT_PLAIN && ctx->tuned[inst->kind].valid;
-  return tuned ? std::min<int64_t>(most, 16384) : most;
+  // A schedule tuned for lm_kernel keeps plain fits of the size it was tuned
+  // for (up to a quarter more) from 16,384 pixels on, unless the group inverter
+  // was faster on that batch, or is at any size.  (HMI pixels in lm_kernel's
+  // best schedule against here: 16,384 3.3 ms, 1.2; 57,344 3.35, 3.3; 65,536
+  // 3.4, 3.6; 98,304 6.4, 5.2.)
+  const vfisv_ctx::Tuned& t = ctx->tuned[inst->kind];
+  const bool own = use == FIT_PLAIN && t.valid && !t.group && n >= t.n && n - t.n <= t.n / 4;
+  return own && most != GROUP_ANY ? std::min<int64_t>(most, 16384) : most;
 }
 
 // Enqueue the group inverter for `a`, a launch of at most n pixels that it
@@ -219,7 +221,7 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
   // Few pixels: a wave per pixel pass (the same results).  A count that only
   // the device knows is compared there: the group kernel exits at once when
   // it is above the limit, and tells lm_kernel what is left to do.
-  const int64_t group_max = group_limit(ctx, inst, o, use);
+  const int64_t group_max = group_limit(ctx, inst, o, use, n);
   hipError_t e = launch_reset(ctx->d_work, reset_all, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "invert: counter reset");
   if (group_max > 0 && (n_dev || n <= group_max)) {
@@ -838,7 +840,8 @@ int vfisv_invert_batches(vfisv_ctx* ctx, const vfisv_batch* batches, int n_batch
   double share = 0.0;
   bool any[MAX_BATCHES] = {};  // faster there at any size
   for (int i = 0; i < n_batches; ++i) {
-    const int64_t most = group_limit(ctx, batches[i].inst, o, fit_use(o, FIT_PLAIN));
+    const int64_t most =
+        group_limit(ctx, batches[i].inst, o, fit_use(o, FIT_PLAIN), batches[i].n);
     any[i] = most == GROUP_ANY;
     if (batches[i].n > 0 && !any[i])
       share += most > 0 ? (double)batches[i].n / (double)most : 2.0;
@@ -919,13 +922,13 @@ int vfisv_autotune(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
   best.best_ms = 1e300;
   best.default_ms = -1.0;
   int cand = 0;
-  auto time_one = [&](const vfisv_options& oc, float* ms) {
+  auto time_one = [&](const vfisv_options& oc, float* ms, FitUse use = FIT_SCHEDULED) {
     *ms = 1e30f;
     for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
       e = hipEventRecord(ev0, s);
       if (e != hipSuccess) break;
       rc = enqueue_lm(ctx, inst, m, nullptr, nullptr, stokes, W, W_per_pixel, nullptr, oc,
-                      inv_dof, params, chi2, iters, nullptr, s, true);
+                      inv_dof, params, chi2, iters, nullptr, s, true, 1, true, use);
       if (rc) break;
       e = hipEventRecord(ev1, s);
       if (e == hipSuccess) e = hipEventSynchronize(ev1);
@@ -991,6 +994,26 @@ int vfisv_autotune(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
       }
     }
   }
+  // The group inverter, where an untuned context would use it and the sample is
+  // the whole batch (two of its waves share a SIMD, so that a scaled grid would
+  // not take a scaled batch's time).
+  vfisv_ctx::Tuned& t = ctx->tuned[inst->kind];
+  bool group = false;
+  if (e == hipSuccess && !rc && m == n) {
+    const vfisv_ctx::Tuned before = t;
+    t.valid = false;
+    vfisv_options oc = o;
+    oc.grid_waves = 0;
+    oc.chunk_log2 = oc.deriv_split = -1;
+    if (n <= group_limit(ctx, inst, oc, FIT_PLAIN, n)) {
+      float ms;
+      time_one(oc, &ms, FIT_PLAIN);
+      best.default_ms = ms;
+      group = ms < best.best_ms;
+      if (group) best.best_ms = ms;
+    }
+    t = before;
+  }
   if (ev0) hipEventDestroy(ev0);
   if (ev1) hipEventDestroy(ev1);
   if (params) hipFree(params);
@@ -1000,8 +1023,9 @@ int vfisv_autotune(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
   if (e != hipSuccess) return hip_fail(ctx, e, "autotune");
   best.candidates = cand;
   best.sample = m;
-  vfisv_ctx::Tuned& t = ctx->tuned[inst->kind];
   t.valid = true;
+  t.n = n;
+  t.group = group;
   t.grid_waves = best.grid_waves;
   t.chunk_log2 = best.chunk_log2;
   t.deriv_split = best.deriv_split;

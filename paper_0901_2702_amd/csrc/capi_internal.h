@@ -42,6 +42,8 @@ struct vfisv_ctx {
     int grid_waves = 0;
     int chunk_log2 = 8;
     int deriv_split = VFISV_DERIV_SPLIT_DEFAULT;
+    int64_t n = 0;       // pixels of the batch it was picked for
+    bool group = false;  // the group inverter was timed on that batch and was faster
   } tuned[2];
   // learned-start scratch (grown on demand)
   void* d_learn = nullptr;

@@ -56,6 +56,26 @@ def test_small_instruments_and_short_fits(ctx, name, spec, below, above, kw):
             assert torch.equal(out[k], ref[k][:n]), (n, k)
 
 
+def test_a_tuned_context_is_no_slower_than_an_untuned_one():
+    """Tuned on its whole batch, a context keeps the group inverter where that
+    is faster; tuned on a sample, it keeps the schedule for the size it was
+    tuned for and no other."""
+    for n, sample, lanes in ((24001, 0, ()), (30001, 4096, (30001, 36001))):
+        ctx = vf.Context(0)
+        inst, o, W = _inputs(ctx, wl.hmi_instrument(), 40001, 68)
+        ref = vf.invert(ctx, inst, o, W)
+        print("[gpu] routes: autotune on %d of %d" % (sample or n, n), flush=True)
+        t = vf.autotune(ctx, inst, o[:n].contiguous(), W, sample=sample)
+        print("[gpu] routes: %s" % t, flush=True)
+        assert 0 < t["best_ms"] <= t["default_ms"] * 1.02
+        for m in (5001, 16384, 24001, 30001, 36001, 40001):
+            out = vf.invert(ctx, inst, o[:m], W)
+            waves = ctx.counters()["grid_waves"]
+            assert (waves == min(t["grid_waves"], (m + 63) // 64)) == (m in lanes), (n, m, waves)
+            for k in ref:
+                assert torch.equal(out[k], ref[k][:m]), (n, m, k)
+
+
 @pytest.mark.parametrize("name,spec", [("HMI", wl.hmi_instrument), ("spectra", wl.fine_instrument)])
 def test_derivative_passes_are_passes(ctx, name, spec):
     """The group inverter's trials run without derivatives; each accepted model
