@@ -222,6 +222,13 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
   // the device knows is compared there: the group kernel exits at once when
   // it is above the limit, and tells lm_kernel what is left to do.
   const int64_t group_max = group_limit(ctx, inst, o, use, n);
+  // (a whole banded batch in the lanes reads an interleaved copy, whose buffer
+  // grows before anything is enqueued)
+  const bool copy = inst->kind == KIND_BAND && !idx && !n_dev && n > group_max && may_alloc;
+  if (copy) {
+    const int rc = grow_obs4(ctx, sizeof(float4) * (size_t)n * (size_t)inst->C.n_obs);
+    if (rc) return rc;
+  }
   hipError_t e = launch_reset(ctx->d_work, reset_all, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "invert: counter reset");
   if (group_max > 0 && (n_dev || n <= group_max)) {
@@ -230,14 +237,10 @@ int enqueue_lm(vfisv_ctx* ctx, const vfisv_instrument* inst, int64_t n,
     if (n <= group_max) return VFISV_OK;
     a.n_dev = ctx->d_work + GROUP_LEFT_SLOT;
   }
-  if (inst->kind == KIND_BAND && !idx && !n_dev && n > 0 && may_alloc) {
-    // a whole banded batch: the pass reads an interleaved copy
-    const int no = inst->C.n_obs;
-    const int rc = grow_obs4(ctx, sizeof(float4) * (size_t)n * (size_t)no);
-    if (rc) return rc;
+  if (copy) {
     float4* o4 = (float4*)ctx->d_obs4;
-    hipError_t e0 = launch_interleave(stokes, o4, n, no, s);
-    if (e0 != hipSuccess) return hip_fail(ctx, e0, "invert: interleave");
+    e = launch_interleave(stokes, o4, n, inst->C.n_obs, s);
+    if (e != hipSuccess) return hip_fail(ctx, e, "invert: interleave");
     a.stokes4 = o4;
   }
   e = launch_lm(a, inst->kind, o.voigt, grid, s);
@@ -846,35 +849,36 @@ int vfisv_invert_batches(vfisv_ctx* ctx, const vfisv_batch* batches, int n_batch
     if (batches[i].n > 0 && !any[i])
       share += most > 0 ? (double)batches[i].n / (double)most : 2.0;
   }
-  e = launch_reset(ctx->d_work, true, s);
-  bool left = false;
-  for (int i = 0; i < n_batches && e == hipSuccess; ++i) {
+  bool group[MAX_BATCHES] = {}, left = false;
+  size_t need = 0;  // samples of the banded batches left to the lanes
+  for (int i = 0; i < n_batches; ++i) {
     if (batches[i].n == 0) continue;
-    if (any[i] || share <= 1.0) {
-      e = enqueue_group(ctx, batches[i].inst, B.a[i], batches[i].n, batches[i].n, s);
-      B.a[i].n = 0;  // nothing left for lm_batches_kernel
-    } else {
-      left = true;
-    }
+    group[i] = any[i] || share <= 1.0;
+    left = left || !group[i];
+    if (!group[i] && B.kind[i] == KIND_BAND)
+      need += (size_t)batches[i].n * (size_t)batches[i].inst->C.n_obs;
+  }
+  if (need > 0) {  // before anything is enqueued
+    const int rc = grow_obs4(ctx, sizeof(float4) * need);
+    if (rc) return rc;
+  }
+  e = launch_reset(ctx->d_work, true, s);
+  for (int i = 0; i < n_batches && e == hipSuccess; ++i) {
+    if (!group[i]) continue;
+    e = enqueue_group(ctx, batches[i].inst, B.a[i], batches[i].n, batches[i].n, s);
+    B.a[i].n = 0;  // nothing left for lm_batches_kernel
   }
   if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches launch");
   if (!left) return VFISV_OK;
   // banded batches read interleaved copies, side by side in one buffer
-  size_t need = 0;
-  for (int i = 0; i < n_batches; ++i)
-    if (B.kind[i] == KIND_BAND) need += (size_t)B.a[i].n * (size_t)batches[i].inst->C.n_obs;
-  if (need > 0) {
-    const int rc = grow_obs4(ctx, sizeof(float4) * need);
-    if (rc) return rc;
-    float4* o4 = (float4*)ctx->d_obs4;
-    for (int i = 0; i < n_batches; ++i) {
-      if (B.kind[i] != KIND_BAND || B.a[i].n == 0) continue;
-      const int no = batches[i].inst->C.n_obs;
-      e = launch_interleave(batches[i].stokes, o4, batches[i].n, no, s);
-      if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches: interleave");
-      B.a[i].stokes4 = o4;
-      o4 += (size_t)batches[i].n * (size_t)no;
-    }
+  float4* o4 = (float4*)ctx->d_obs4;
+  for (int i = 0; i < n_batches; ++i) {
+    if (B.kind[i] != KIND_BAND || B.a[i].n == 0) continue;
+    const int no = batches[i].inst->C.n_obs;
+    e = launch_interleave(batches[i].stokes, o4, batches[i].n, no, s);
+    if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches: interleave");
+    B.a[i].stokes4 = o4;
+    o4 += (size_t)batches[i].n * (size_t)no;
   }
   e = launch_lm_batches(B, grid, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "invert_batches launch");

@@ -123,6 +123,22 @@ def test_learned_path_counts_the_waves_that_worked(ctx, n, refit, kernels):
         assert group in (min(n, 4 * cus), min(n, 8 * cus))
 
 
+def test_batches_left_to_the_lanes(ctx):
+    """Wide spectra go to the group inverter, the other batches, together over
+    their limits, to the lanes: two banded ones with their interleaved copies."""
+    made = [_inputs(ctx, spec, n, 70 + i) for i, (spec, n) in enumerate(
+        ((wl.fine_instrument(), 70), (wl.fine_instrument(n_obs=5), 40001),
+         (wl.hmi_instrument(), 901), (wl.fine_instrument(n_obs=14), 20003)))]
+    print("[gpu] routes: batches", flush=True)
+    out = vf.invert_batches(ctx, [dict(inst=i, stokes=o, W=W) for i, o, W in made])
+    waves = ctx.counters()["grid_waves"]
+    assert waves == 70 + _lanes(ctx, 70 + 40001 + 901 + 20003)
+    for (i, o, W), got in zip(made, out):
+        alone = vf.invert(ctx, i, o, W, opts=vf.Options(**LANES))
+        for k in alone:
+            assert torch.equal(alone[k], got[k]), (i.n_obs, k)
+
+
 @pytest.mark.parametrize("name,spec,sizes", [
     ("7 points", lambda: wl.hmi_instrument(n_fine=13), (5001, 7003, 20001)),
     ("29 points", lambda: wl.hmi_instrument(n_fine=51), (20001, 31003, 60001)),
