@@ -105,6 +105,10 @@ def committed_traffic(n, profile=TRAFFIC_PROFILE):
         return None
 
 
+# Largest short fit and re-fit of HMI pixels that the group inverter takes
+# (csrc/routes.h).
+LEARNED_GROUP_MAX = 57344
+
 WORK_KEYS = ("pixels", "trials", "accepts", "passes", "derivative_passes", "jacobians")
 
 
@@ -418,15 +422,20 @@ def main():
         if w is None or abs(w - c["trials"]) > 0.01 * c["trials"]:
             sq.pop(key, None)
     mlp_flop = n * MLP_FLOP_PER_PIXEL
+
+    def fit_kernel(c):
+        return "lm_group_kernel<false>" if c["pixels"] <= LEARNED_GROUP_MAX else "lm_kernel<6>"
+
     launches = {
-        "short_fit": {"kernel": "lm_kernel<6> (learned start, <= %d trials)" % args.learned_max_iter,
+        "short_fit": {"kernel": "%s (learned start, <= %d trials)"
+                                % (fit_kernel(sf), args.learned_max_iter),
                       "ms": round(ph_ms["short_fit"], 4), "bound": "alu", "unit": "TFLOP/s",
                       "peak": PEAK_FP32_TFLOPS,
                       "achieved": round(alg(sf) / (ph_ms["short_fit"] * 1e-3) / 1e12, 3),
                       "executed": rate(sq.get("short_fit"), ph_ms["short_fit"]),
                       "fp64": round(census.fp64(sf) / (ph_ms["short_fit"] * 1e-3) / 1e12, 3),
                       "work": {k: sf[k] for k in WORK_KEYS}},
-        "refit": {"kernel": "lm_group_kernel<false> (re-fit of the pixels above tau, <= 50 trials)",
+        "refit": {"kernel": fit_kernel(rf) + " (re-fit of the pixels above tau, <= 50 trials)",
                   "ms": round(ph_ms["refit"], 4), "bound": "alu", "unit": "TFLOP/s",
                   "peak": PEAK_FP32_TFLOPS,
                   "achieved": round(alg(rf) / (ph_ms["refit"] * 1e-3) / 1e12, 3),
