@@ -1,5 +1,5 @@
-// Kernel argument block and launch helper of the group inverter (group.hip):
-// a wave per pixel pass, for launches with fewer pixels than lanes.
+// Kernel argument block and launch helpers of the group inverter (group.hip): a
+// wave per pixel pass.  routes.h says which launches it is for.
 #pragma once
 
 #include <hip/hip_runtime.h>

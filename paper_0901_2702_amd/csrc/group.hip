@@ -32,8 +32,11 @@
 // the decisions and the set-up of a turn, which one lane each would otherwise
 // run alone (two pixels per wave, 32 lanes each: 1,750 instructions per
 // trial, 131,072 pixels in 18.2 ms instead of 6.9).  Measured, default
-// options: 37 HMI pixels 3.86 ms (lm_kernel) -> 0.34 ms, 4,096 3.95 -> 0.60,
-// 65,536 4.7 -> 3.6; 1,000 fine spectra 29.5 -> 1.43 ms, 100,003 63.7 -> 30.2.
+// options: 37 HMI pixels 3.77 ms (lm_kernel) -> 0.32 ms, 4,096 4.25 -> 0.57,
+// 65,536 4.6 -> 3.56; 1,000 fine spectra 30.3 -> 1.42 ms, 100,003 64.0 -> 29.6.
+// A chunk costs its 64 points' time however many of them there are, so fits
+// through few points, and those of few trials, whose set-up counts, are slower
+// here from fewer pixels on (routes.h).
 #include <hip/hip_runtime.h>
 
 #include "group.h"
@@ -801,7 +804,7 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
   const int lane = threadIdx.x;
   const bool serve = n_total <= (unsigned long long)ga.n_max;
   if (A.n_dev && blockIdx.x == 0 && lane == 0) A.work[GROUP_LEFT_SLOT] = serve ? 0ull : n_total;
-  if (!serve || blockIdx.x >= n_total) return;
+  if (!serve) return;
   // the launch's own rule for lane pairs, whose sums differ by rounding
   const bool pair = A.lpp_max >= 2 && n_total <= (unsigned long long)A.pair_max;
   Layout<BAND> lay(S, ga, lane, pair);
@@ -811,7 +814,10 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
   const int rows = 4 * A.C.n_obs;
   int cp, cq;
   chain_of(lane, cp, cq);
-  bool live = false, fresh = false, exhausted = lane >= slots, need_fb = false;
+  bool live = false, fresh = false, need_fb = false;
+  // (waves beyond the pixels touch no queue and no counter)
+  const bool idle = blockIdx.x >= n_total;
+  bool exhausted = idle || lane >= slots;
   bool monotone = false;
   int64_t pix = 0;
   float Mb[NPAR], Mc[NPAR];
@@ -947,6 +953,7 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
           if (A.status) A.status[pix] = done;
         }
         ++n_pix;
+        if (it == 0) ++n_pass;  // ended at its start: see the passes below
         live = false;
       }
       want_j = live && new_best;
@@ -956,7 +963,6 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
     const unsigned keep = (unsigned)__ballot(want_j && keep_h);
     if (want_j) {
       ++n_jac;
-      if (it > 0) ++n_pass;  // (a start's values and Jacobian count as one pass)
       if (!keep_h) ++n_hess;
     }
     if (jm != 0u) lay.normal(jm, keep, pix, cp, cq);
@@ -979,12 +985,13 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
   const unsigned long long tp = wave_total(n_pix), tt = wave_total(n_trial), ta = wave_total(n_acc),
                            ts = wave_total(n_pass), tf = wave_total(n_fb), tj = wave_total(n_jac),
                            th = wave_total(n_hess);
-  if (lane == 0) {
+  if (lane == 0 && !idle) {
     atomicAdd(&A.work[0], tj);
     atomicAdd(&A.work[1], tp);
     atomicAdd(&A.work[2], tt);
     atomicAdd(&A.work[3], ta);
-    atomicAdd(&A.work[4], ts);
+    // trials, starts and Jacobians, of which a start's is no pass of its own
+    atomicAdd(&A.work[4], ts + tj - tp);
     if (tf) atomicAdd(&A.work[5], tf);
     atomicAdd(&A.work[6], 1ull);
     atomicAdd(&A.work[7], th);
@@ -1000,8 +1007,10 @@ __global__ __launch_bounds__(64, 2) void lm_group_kernel(const GroupArgs ga) {
 // latencies up to 65,536 models.  Bound by VALU issue from there on (620 wave
 // instructions per HMI model with its Jacobian, 2,100 per fine spectrum).
 // Measured, a model per lane -> here: 1,000 HMI models with Jacobian 66 -> 11
-// us, 65,537 172 -> 100; 30,011 fine spectra 406 -> 99, with Jacobian 937 ->
-// 380.  (Jacobian rows through LDS, to store whole lines, take as long.)
+// us, 65,537 170 -> 88; 30,011 fine spectra 425 -> 97, with Jacobian 599 ->
+// 363.  (Jacobian rows through LDS, to store whole lines, take as long.)
+// Through filters that leave a chunk partly empty a model per lane is faster
+// from some thousands of models on (routes.h).
 namespace {
 
 constexpr int SYNTH_PER[2] = {32, 16};  // most models of a wave, per layout

@@ -715,8 +715,8 @@ static_assert(hzero_matches(), "hzero lists the entries of H with a zero factor"
 // anew for each quotient (about 18 + 11 and 11 instructions; here 14 and 6).
 // Both bits are the same wherever no intermediate leaves the normal range.
 // One step of an HMI pixel was a third of a trial's latency where few pixels
-// are fitted (37: 0.373 ms, now 0.345) and a tenth of its instructions
-// (65,536: 3.95 ms, now 3.72; a pixel per lane, 1,000,000: 40.6, now 40.0).
+// are fitted (37: 0.373 ms before, 0.334 with these) and a tenth of its
+// instructions (65,536: 3.95 ms, 3.72; a pixel per lane, 1,000,000: 40.6, 40.0).
 struct Root {
   double l, rl;  // sqrt(d), 1 / sqrt(d) (of the rounded root)
 };
