@@ -53,7 +53,11 @@ constexpr int64_t GROUP_ANY = INT64_MAX;
 // with max_iter 0 1,024 0.76 and 16,384 0.58, max_iter 2 1,024 1.69 and 16,384
 // 0.92, near the minimum max_iter 3 16,384 1.09 and 32,768 0.93, max_iter 5
 // 32,768 1.16 and 57,344 0.84; 112 samples max_iter 0 262,144 1.84, max_iter 1
-// 16,384 1.60, 32,768 1.05, 57,344 0.72, max_iter 3 32,768 1.31, 57,344 0.83.
+// 16,384 1.60, 32,768 1.05, 57,344 0.72, max_iter 3 32,768 1.31, 49,152 0.91.
+// Partly filled chunks cross far earlier, as lm_kernel's latency goes with the
+// points: 19 points max_iter 0 512 0.84, max_iter 2 2,048 0.52, max_iter 3 2,048
+// 0.73; 14 samples max_iter 3 32,768 0.81; full ones do not: 13 samples max_iter
+// 3 32,768 1.02, 29 samples 49,152 0.98.
 inline int64_t fit_group_max(const Extent& e, FitUse use, int max_iter) {
   if (use == FIT_SCHEDULED || e.chunks < 1) return 0;
   const bool plain = use == FIT_PLAIN;
@@ -71,9 +75,14 @@ inline int64_t fit_group_max(const Extent& e, FitUse use, int max_iter) {
   } else {
     most = e.points > 3 ? 1006 * (int64_t)e.points - 2010 : 1024;
   }
+  const double fill = e.points / (64.0 * e.chunks), fill2 = fill * fill;
   int64_t few = GROUP_ANY;
-  if (max_iter < 3) few = (int64_t)(max_iter < 2 ? 512 : 2048) << (e.chunks < 7 ? e.chunks - 1 : 6);
-  else if (max_iter < 10) few = e.chunks > 1 ? 49152 : 24576;
+  if (max_iter < 3) {
+    const int64_t n = (int64_t)(max_iter < 2 ? 512 : 2048) << (e.chunks < 7 ? e.chunks - 1 : 6);
+    few = (int64_t)((n < 32768 ? n : 32768) * fill2);
+  } else if (max_iter < 10) {
+    few = (int64_t)((e.chunks > 1 ? 40960 : 24576) * fill2 * fill2);
+  }
   if (max_iter == 0 && e.chunks > 5) few = GROUP_ANY;
   return most < few ? most : few;
 }
@@ -82,7 +91,7 @@ inline int64_t fit_group_max(const Extent& e, FitUse use, int max_iter) {
 // models.  As above: a model per lane takes the points' time whatever n is, up
 // to 65,536 models and more, waves of a few models whole chunks' time per
 // model.  Measured, model per lane / here:
-//  dense, values: 7 points 8,192 1.00, 16,384 0.80, 1,000,000 0.36; 29 points
+//  dense, values: 7 points 1,024 1.37, 4,096 0.88, 1,000,000 0.36; 29 points
 //   30,011 1.04, 65,536 0.83; 59 points 90,000 1.14, 131,072 0.95; 64 points
 //   200,000 1.02.
 //  dense, with Jacobian: 7 points 8,192 0.96, 16,384 0.79; 29 points 30,011
@@ -101,7 +110,7 @@ inline int64_t fit_group_max(const Extent& e, FitUse use, int max_iter) {
 inline bool synth_by_group(const Extent& e, int64_t n, bool jac) {
   if (e.chunks < 1) return false;
   if (!e.band) {
-    if (e.points <= 29) return n <= (jac ? 1000 : 1200) * (int64_t)e.points;
+    if (e.points <= 29) return n <= (jac ? 1000 : 41 * e.points) * (int64_t)e.points;
     if (jac) return e.points >= 50 || n <= 29000 + 3000 * (int64_t)(e.points - 29);
     return n <= 34798 + 2663 * (int64_t)(e.points - 29);
   }

@@ -41,7 +41,8 @@ def _lanes(ctx, n):
     ("3 samples", lambda: wl.fine_instrument(n_obs=3), 16001, 40001, {}),
     ("14 samples", lambda: wl.fine_instrument(n_obs=14), 40001, 90001, {}),
     ("no trial", wl.hmi_instrument, 300, 3001, dict(max_iter=0)),
-    ("five trials", wl.hmi_instrument, 20001, 60001, dict(max_iter=5)),
+    ("five trials", wl.hmi_instrument, 15001, 60001, dict(max_iter=5)),
+    ("19 points, three trials", lambda: wl.hmi_instrument(n_fine=33), 101, 2001, dict(max_iter=3)),
 ])
 def test_small_instruments_and_short_fits(ctx, name, spec, below, above, kw):
     inst, o, W = _inputs(ctx, spec(), above, 61)

@@ -43,18 +43,25 @@ FITS = [
     (1, 68, 2, "REFIT", 50, 32768, 65536),
     (1, 460, 8, "REFIT", 50, 131072, None),
     # few trials: the set-up of a pixel counts
-    (0, 59, 1, "PLAIN", 0, 64, 1024),
+    (0, 59, 1, "PLAIN", 0, 256, 1024),
     (0, 59, 1, "PLAIN", 2, 1024, 16384),
     (0, 59, 1, "PLAIN", 5, 16384, 57344),
+    (0, 19, 1, "PLAIN", 0, 16, 512),
+    (0, 19, 1, "PLAIN", 2, 64, 2048),
+    (0, 19, 1, "PLAIN", 3, 128, 2048),
+    (1, 32, 1, "PLAIN", 3, 512, 2048),
+    (1, 68, 2, "PLAIN", 3, 2048, 32768),
     (1, 64, 1, "PLAIN", 1, 64, 4096),
+    (1, 64, 1, "PLAIN", 3, 16384, 57344),
     (1, 460, 8, "PLAIN", 0, 262144, None),
     (1, 460, 8, "PLAIN", 1, 16384, 57344),
-    (1, 460, 8, "PLAIN", 3, 32768, 57344),
+    (1, 460, 8, "PLAIN", 2, 16384, 49152),
+    (1, 460, 8, "PLAIN", 3, 24576, 49152),
 ]
 
 # (band, points, chunks, with Jacobian, sizes faster in groups, sizes faster in lanes)
 SYNTH = [
-    (0, 7, 1, 0, (64, 4096, 8192), (16384, 131072, 1000000)),
+    (0, 7, 1, 0, (64, 1024), (4096, 16384, 131072, 1000000)),
     (0, 7, 1, 1, (64, 4096), (16384, 131072, 524288)),
     (0, 29, 1, 0, (64, 30011), (65536, 131072, 1000000)),
     (0, 29, 1, 1, (64, 16384), (45000, 131072, 524288)),
