@@ -181,7 +181,7 @@ def main():
                     default="learned",
                     help="learned: the learned-start vs plain LM line (default); full-disk: "
                          "plain LM over the 13.2M-pixel disk with clustered active regions; "
-                         "fine-mixed: 1M fine-spectrum + 1M HMI pixels in one launch; "
+                         "fine-mixed: 1M fine-spectrum + 1M HMI pixels in one call; "
                          "parity: per-parameter differences from the FP64 oracle on the "
                          "262,144-pixel HMI set; init-compare: default / classical / network "
                          "starts; hess-reuse: plain LM with the Hessian kept near the minimum; "
@@ -740,8 +740,8 @@ def full_disk(args, ctx, inst, spec, log):
 
 def fine_mixed(args, ctx, inst, spec, log):
     """1M fine-spectrum pixels (112 samples, banded 15-tap filter, 464-point
-    grid) and 1M HMI-shaped pixels inverted by plain LM in one launch, against
-    the same work as two launches."""
+    grid) and 1M HMI-shaped pixels inverted by plain LM in one call, against
+    the same work as two calls."""
     import numpy as np
     import torch
 

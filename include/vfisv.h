@@ -108,8 +108,9 @@ typedef struct {
                        /* vfisv_autotune choice for the instrument's layout */
                        /* if there is one, else CUs x occupancy.  With every */
                        /* scheduling field automatic, launches of few pixels */
-                       /* take a pixel per wave pass instead of per lane     */
-                       /* (the same results)                                */
+                       /* (how few goes with the instrument's synthesis      */
+                       /* points; wide spectra: any number) take a pixel per */
+                       /* wave pass instead of per lane (the same results)  */
   int chunk_log2;      /* pixel queue block = 2^chunk_log2 consecutive      */
                        /* pixels, 0..20, or -1 = auto (default: the tuned   */
                        /* value, else 8).  Scheduling only: the per-pixel   */
@@ -293,25 +294,30 @@ int vfisv_synthesize_voigt(vfisv_ctx *ctx, const vfisv_instrument *inst, int64_t
  *   status: dev [n] status word, or NULL.
  * Per-pixel numerical trouble never fails the call; it is reported in
  * status.  n == 0 enqueues nothing.  4*n_obs - (free parameters) must be
- * > 0.  With a banded instrument the pass reads an interleaved copy of
- * stokes (16 bytes per pixel and sample) that the call makes first, in a
- * context buffer that grows when a larger batch comes (the growth
- * allocates and waits for the device; calls after it allocate nothing). */
+ * > 0.  With a banded instrument, launches with a pixel per lane (see
+ * grid_waves) read an interleaved copy of stokes (16 bytes per pixel and
+ * sample) that the call makes first, in a context buffer that grows when a
+ * larger batch comes (the growth allocates and waits for the device; calls
+ * after it allocate nothing). */
 int vfisv_invert(vfisv_ctx *ctx, const vfisv_instrument *inst, int64_t n,
                  const float *stokes, const float *W, int W_per_pixel,
                  const float *init, const vfisv_options *opt, float *params,
                  double *chi2, int32_t *iters, int32_t *status, void *stream);
 
-/* Several batches in one persistent launch (e.g. fine-spectrum and
- * HMI-shaped pixels together).  Each batch has its own instrument, pixels,
- * weights, optional start and outputs, with the same meaning as the
- * arguments of vfisv_invert; all share opt (the degrees of freedom of
- * Eq. 1 follow each batch's instrument).  Every wave of the launch works
- * through the batches in the order given, moving on when the current
- * batch has no pixel left, so put the batch with the most work per pixel
- * first: the later batches then fill the waves that the earlier ones leave
- * idle.  1 <= n_batches <= 4; batches with n == 0 are allowed.  The
- * per-pixel results equal those of vfisv_invert on each batch alone. */
+/* Several batches in one call (e.g. fine-spectrum and HMI-shaped pixels
+ * together).  Each batch has its own instrument, pixels, weights, optional
+ * start and outputs, with the same meaning as the arguments of vfisv_invert;
+ * all share opt (the degrees of freedom of Eq. 1 follow each batch's
+ * instrument).  With automatic scheduling (see grid_waves), batches that take
+ * a pixel per wave pass at any size are launched one after the other; so are
+ * the others if each one's share of the most pixels that it would take so by
+ * itself add up to at most one.  What is left, everything under a given
+ * schedule, shares one persistent launch: every wave works through those
+ * batches in the order given, moving on when the current batch has no pixel
+ * left, so put the batch with the most work per pixel first: the later
+ * batches then fill the waves that the earlier ones leave idle.
+ * 1 <= n_batches <= 4; batches with n == 0 are allowed.  The per-pixel
+ * results equal those of vfisv_invert on each batch alone. */
 typedef struct {
   const vfisv_instrument *inst;
   int64_t n;

@@ -326,7 +326,8 @@ def _out_ptrs(out, n, dev):
 
 
 def invert_batches(ctx, batches, opts=None):
-    """Several batches in one launch.  ``batches``: list of dicts with keys
+    """Several batches in one call (how they are launched: vfisv.h).
+    ``batches``: list of dicts with keys
     inst, stokes [n, 4, n_obs], W ([4, n_obs] or [n, 4, n_obs]), and
     optionally init [n, 10] and out (as returned by ``invert``).  Returns
     the list of output dicts, in order."""
