@@ -56,8 +56,8 @@ constexpr int64_t GROUP_ANY = INT64_MAX;
 // 16,384 1.60, 32,768 1.05, 57,344 0.72, max_iter 3 32,768 1.31, 49,152 0.91.
 // Partly filled chunks cross far earlier, as lm_kernel's latency goes with the
 // points: 19 points max_iter 0 512 0.84, max_iter 2 2,048 0.52, max_iter 3 2,048
-// 0.73; 14 samples max_iter 3 32,768 0.81; full ones do not: 13 samples max_iter
-// 3 32,768 1.02, 29 samples 49,152 0.98.
+// 0.73; 14 samples max_iter 3 32,768 0.81; full ones do not: near the minimum 13
+// samples max_iter 3 16,384 1.21, 32,768 0.97, 29 samples 49,152 0.93.
 inline int64_t fit_group_max(const Extent& e, FitUse use, int max_iter) {
   if (use == FIT_SCHEDULED || e.chunks < 1) return 0;
   const bool plain = use == FIT_PLAIN;
